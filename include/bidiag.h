@@ -162,10 +162,8 @@ void bb_plan_destroy(bb_plan* plan);
  *   ws_bytes : scheduler state (error flag, ticket and done counters, one
  *              dependency counter per task, the optional trace) followed by
  *              the copy of the task graph that each execution uploads
- *              (tasks, successor lists, unit order) and, for nb = 256, the
- *              panels' scratch (512 KiB per workgroup of a persistent launch,
- *              or per panel of the widest level).  Contents are not kept
- *              between executions.
+ *              (tasks, successor lists, unit order).  Contents are not
+ *              kept between executions.
  */
 int bb_plan_workspace(const bb_plan* plan, size_t* vt_bytes, size_t* ws_bytes);
 
@@ -199,8 +197,9 @@ int bb_execute(bb_plan* plan, void* A, int64_t lda, void* vt, size_t vt_bytes, v
  * array of BB_NOALLOC_WS_MAX bytes, one per device, kept until the process
  * ends; the call itself allocates nothing (no hipMalloc, hipFree or
  * allocating library routine) and records no timing events.  A plan whose
- * bb_plan_workspace ws_bytes exceeds BB_NOALLOC_WS_MAX is rejected with
- * BB_EWORKSPACE (every nb = 256 plan: its panel scratch alone exceeds it).
+ * bb_plan_workspace ws_bytes, plus 512 KiB per workgroup (level schedule: per
+ * panel of the widest level) for nb = 256, exceeds BB_NOALLOC_WS_MAX is
+ * rejected with BB_EWORKSPACE (every nb = 256 plan on a whole device).
  * Every call on a device shares that device's array, so
  * calls whose executions overlap on one device (other streams, other
  * threads) race; calls in one stream order do not.  Arguments as

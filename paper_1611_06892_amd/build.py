@@ -36,8 +36,9 @@ def _jobs():
     """(object, command) for every translation unit."""
     hipcc = _hipcc()
     common = ["-O3", "-fPIC", "-std=c++17", "-Wall", "-I", os.path.join(HERE, "..", "include")]
-    device = [hipcc, "-x", "hip", "--offload-arch=" + ARCH, "-munsafe-fp-atomics", "-Wno-unneeded-internal-declaration",
-              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", *common]
+    device = [hipcc, "-x", "hip", "--offload-arch=" + ARCH, "-munsafe-fp-atomics",
+              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", *common,
+              "-Wno-unneeded-internal-declaration"]
     jobs = []
     kern = os.path.join(CSRC, "kernels.hip")
     for nb in (0,) + TILE_SIZES:        # 0: the kernels of batches mixing tile sizes 32 .. 128

@@ -17,14 +17,15 @@
 // upper triangular, and an update applies Q^T: C <- C - V T^T V^T C.
 //
 // One workgroup of 512 threads (8 wave64, two per SIMD) executes one work
-// unit.  Panels are blocked by 16 columns (a register-resident leaf on four
-// waves plus MFMA trailing updates on all eight); updates apply the 16-column
+// unit.  Panels are blocked by 16 columns, each factored by one wave in its
+// registers and applied by the others with MFMA; updates apply the 16-column
 // blocks of a panel's reflectors with FP64 MFMA (v_mfma_f64_16x16x4) to
 // register-resident 16-column slices of the trailing tile(s), one slice per
 // wave.  Two waves per SIMD let one wave's MFMA chain run while the other
 // waits on a dependency.
 #include <mutex>
 #include <type_traits>
+#include <utility>
 
 #include "../../include/bidiag.h"
 #include "kernels.hpp"
@@ -35,21 +36,22 @@ namespace {
 
 constexpr int NT = 512;          // threads per workgroup
 typedef double d4 __attribute__((ext_vector_type(4)));
+typedef double d2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 
 enum : int { K_GEQRT = 0, K_TSQRT = 1, K_TTQRT = 2, K_UNMQR = 3, K_TSMQR = 4, K_TTMQR = 5, K_HQ = 3 };
 
 template <int NB>
 struct Shape {
     static constexpr int MT = NB / 16;                 // 16 x 16 tiles per tile side
-    static constexpr int LDL = NB + 1;                 // LDS stride of the leaf (odd: conflict-free)
-    // doubles used by a panel: leaf buffer(s) (two at nb = 256), then the
-    // reflector broadcast, taus, G, T_b and R1's diagonal entries
-    // (nb = 256: two leaf buffers, the block's reflector ring, taus, G, two
-    // T_b and the role counters)
-    static constexpr int PANEL = NB > 128 ? 32 * LDL + 16 * NB + 16 + 256 + 512 + 2048 + 4
-                                          : 16 * LDL + 2 * NB + 16 + 768;
-    static constexpr int UPDATE = 2 * (16 * LDL + 256);           // ... and by an update
-    static constexpr int LDS = PANEL > UPDATE ? PANEL : UPDATE;
+    static constexpr int LDV = NB + 2;                 // LDS column stride of an update's block V_b: 16-byte
+                                                       // aligned, and rows and columns spread over the banks
+    // doubles: a panel's block U_b with its T_b, and all of a panel (two of
+    // those, a diagonal block of column stride 17 per column tile of a round,
+    // the Gram columns); an update's two staged blocks V_b, T_b take less
+    static constexpr int UBUF = MT * 336 + 256;
+    static constexpr int LDS = 2 * UBUF + (MT < 8 ? MT : 8) * 272 + 274;
+    static_assert(LDS >= 2 * (16 * LDV + 256), "update buffers");
 };
 
 // Keeps the scheduler from hoisting loads of later 16-row steps of a fully
@@ -86,21 +88,118 @@ __device__ __forceinline__ void gstore(double* p, double v) {
     else *q = v;
 }
 
-// A tile seen in the logical frame.  vr/vc: logical rows/columns that exist in
-// the matrix (the rest of the nb x nb tile is zero padding, never accessed).
+// v, opaque to the compiler: what is formed from it (addresses, lane masks)
+// stays where it is used.  Hoisted out of the scheduler's loop or a panel's
+// it would be held through code that leaves no registers for it at nb = 256.
+__device__ __forceinline__ int here(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+// A tile seen in the logical frame: logical element (r, c) is base[r rs + c cs].
+// vr/vc: logical rows/columns that exist in the matrix (the rest of the nb x nb
+// tile is zero padding, never accessed).
 struct TileView {
     double* base;
-    int64_t ld;
-    int trans, vr, vc;
-    __device__ __forceinline__ double* ptr(int r, int c) const {
-        return trans ? base + c + (int64_t)r * ld : base + r + (int64_t)c * ld;
+    int64_t rs, cs;
+    int vr, vc;
+};
+
+// One lane's part of the 16 columns from c0: column c0 + lane % 16, rows
+// 16 i + 4 (lane / 16) .. + 3 of row tile i, read and written four at a time.
+// Whole tiles whose columns are contiguous and 16-byte aligned (QR steps)
+// take 16-byte buffer accesses: one byte offset per lane, the row in the
+// instruction.  Everything else (LQ steps, ragged or unaligned tiles) is
+// addressed by element; in a ragged tile a load of a missing element reads
+// the tile's first one instead and yields zero, so that no load is behind a
+// branch.
+struct TileLane {
+    __amdgpu_buffer_rsrc_t rsrc;
+    int voff;
+    bool vec, whole;
+    gdouble *p, *first;
+    int64_t rs;
+    int rlim;                       // rows r0 + r < rlim exist (r0 a multiple of 16, r < 4)
+    __device__ __forceinline__ TileLane(const TileView& t, int c0, int nb) {
+        const int lane = here(threadIdx.x) & 63, c = c0 + (lane & 15), r = 4 * (lane >> 4);
+        // whole, contiguous columns, aligned, within a buffer's 32-bit offsets
+        whole = t.vr == nb && t.vc == nb;
+        vec = whole && t.rs == 1 && ((uint64_t)t.base & 15) == 0 && (t.cs & 1) == 0 && t.cs * nb < (1 << 27);
+        rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)t.base, (short)0, 0x7fffffff, 0x00020000);
+        voff = 8 * (r + c * (int)t.cs);
+        first = gptr(t.base);
+        p = first + r * t.rs + c * t.cs;
+        rs = t.rs;
+        rlim = c < t.vc ? t.vr - r : 0;
     }
-    __device__ __forceinline__ double get(int r, int c) const {
-        return (r < vr && c < vc) ? *gptr(ptr(r, c)) : 0.0;
+    // Keeps addresses formed from this lane's offsets from being hoisted
+    // above this point.
+    __device__ __forceinline__ void renew() { asm volatile("" : "+v"(p), "+v"(voff)); }
+    template <int MT>
+    __device__ __forceinline__ void load(int r0, d4 (&x)[MT]) const {
+        if (vec) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                const u4 lo = __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, 8 * (r0 + 16 * i), 0);
+                const u4 hi = __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff + 16, 8 * (r0 + 16 * i), 0);
+                const d2 l = __builtin_bit_cast(d2, lo), h = __builtin_bit_cast(d2, hi);
+                x[i] = d4{l[0], l[1], h[0], h[1]};
+            }
+        } else if (whole) {
+            gdouble* q = p + r0 * rs;
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    x[i][r] = *q;
+                    q += r < 3 ? rs : 13 * rs;
+                }
+            }
+        } else {
+            gdouble* q = p + r0 * rs;
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    x[i][r] = *(r0 + 16 * i + r < rlim ? q : first);
+                    q += r < 3 ? rs : 13 * rs;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) x[i][r] = r0 + 16 * i + r < rlim ? x[i][r] : 0.0;
+        }
+    }
+    __device__ __forceinline__ d4 load(int r0) const {
+        d4 x[1];
+        load<1>(r0, x);
+        return x[0];
     }
     template <bool CO>
-    __device__ __forceinline__ void put(int r, int c, double v) const {
-        if (r < vr && c < vc) gstore<CO>(ptr(r, c), v);
+    __device__ __forceinline__ void store(int r0, d4 x) const {
+        if (vec) {
+            // cache policy 16 (sc1): performed at the agent's coherence point,
+            // as gstore's agent-scope stores
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, d2{x[0], x[1]}), rsrc, voff, 8 * r0,
+                                                   CO ? 16 : 0);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, d2{x[2], x[3]}), rsrc, voff + 16, 8 * r0,
+                                                   CO ? 16 : 0);
+        } else if (whole) {
+            gdouble* q = p + r0 * rs;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                gstore<CO>((double*)q, x[r]);
+                q += rs;
+            }
+        } else {
+            gdouble* q = p + r0 * rs;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if (r0 + r < rlim) gstore<CO>((double*)q, x[r]);
+                q += rs;
+            }
+        }
     }
 };
 
@@ -141,8 +240,8 @@ __device__ __forceinline__ TileView view(const MatDesc& d, const DevTask& tk, in
     const int trans = tk.trans & 1;
     TileView t;
     t.base = d.A + (int64_t)pr * nb + (int64_t)pc * nb * d.lda;
-    t.ld = d.lda;
-    t.trans = trans;
+    t.rs = trans ? d.lda : 1;
+    t.cs = trans ? 1 : d.lda;
     int prow = (int)min((int64_t)nb, d.m - (int64_t)pr * nb);
     int pcol = (int)min((int64_t)nb, d.n - (int64_t)pc * nb);
     t.vr = trans ? pcol : prow;
@@ -150,49 +249,27 @@ __device__ __forceinline__ TileView view(const MatDesc& d, const DevTask& tk, in
     return t;
 }
 
-// Register ("accumulator") layout of a 16-column slice of a tile, shared by
-// every MFMA of this file: element r (0..3) of lane l of row tile i holds
-// logical (16 i + 4 r + l/16, c0 + l%16).  That is the result layout of
-// v_mfma_f64_16x16x4, and element r of row tile i is also exactly the second
-// operand of the k-step covering rows 16 i + 4 r .. 16 i + 4 r + 3, so a slice
-// held this way feeds the next product without any data movement.
+// Register layout of a 16-column slice of a tile, shared by every MFMA of this
+// file: element r (0..3) of lane l of row tile i holds logical
+// (16 i + 4 (l/16) + r, c0 + l%16), four consecutive rows a lane.
+// v_mfma_f64_16x16x4 returns its row m = 4 r + l/16 in element r of lane l and
+// takes the k index k = l/16 of its step from lane l, so with row m of the
+// first operand taken as row perm16(m) = 4 (m % 4) + m / 4, results come in this layout,
+// and element r is the second operand of the k-step that covers rows
+// 4 (l/16) + r: a slice held this way feeds the next product without any
+// data movement.
+__device__ __forceinline__ int perm16(int m) { return 4 * (m & 3) + (m >> 2); }
+
 template <int MT>
-__device__ __forceinline__ void load_slice(const TileView& t, int c0, d4 (&x)[MT]) {
-    const int lane = threadIdx.x & 63, j = lane & 15, g = lane >> 4;
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) x[i][r] = t.get(16 * i + 4 * r + g, c0 + j);
+__device__ __forceinline__ void load_slice(const TileLane& t, d4 (&x)[MT]) {
+    t.load<MT>(0, x);
 }
 
 template <bool CO, int MT>
-__device__ __forceinline__ void store_slice(const TileView& t, int c0, const d4 (&x)[MT]) {
-    const int lane = threadIdx.x & 63, j = lane & 15, g = lane >> 4;
+__device__ __forceinline__ void store_slice(const TileLane& t, const d4 (&x)[MT]) {
 #pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) t.put<CO>(16 * i + 4 * r + g, c0 + j, x[i][r]);
+    for (int i = 0; i < MT; ++i) t.store<CO>(16 * i, x[i]);
 }
-
-__device__ __forceinline__ d4 load16(const TileView& t, int r0, int c0) {
-    const int lane = threadIdx.x & 63, j = lane & 15, g = lane >> 4;
-    d4 x;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) x[r] = t.get(r0 + 4 * r + g, c0 + j);
-    return x;
-}
-
-template <bool CO>
-__device__ __forceinline__ void store16(const TileView& t, int r0, int c0, d4 x) {
-    const int lane = threadIdx.x & 63, j = lane & 15, g = lane >> 4;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) t.put<CO>(r0 + 4 * r + g, c0 + j, x[r]);
-}
-
-// Whole-vector accesses of 32 bytes (global memory).
-typedef __attribute__((address_space(1))) d4 gd4;
-__device__ __forceinline__ d4 load_d4(const double* p) { return *(const gd4*)p; }
-__device__ __forceinline__ void store_d4(double* p, d4 v) { *(gd4*)p = v; }
 
 // Reads of one V/T record through a buffer descriptor: every load of a
 // product shares one per-lane byte offset and adds a wave-uniform constant,
@@ -208,63 +285,6 @@ struct Rec {
         return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rsrc, voff, soff, 0));
     }
 };
-
-// Cross-lane move inside rows of 16 lanes (DPP), on both halves of a double.
-template <int CTRL>
-__device__ __forceinline__ double dpp(double v) {
-    const long long b = __builtin_bit_cast(long long, v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, true);
-    return __builtin_bit_cast(double, ((long long)hi << 32) | (long long)(unsigned int)lo);
-}
-
-// Sum over the 16 lanes of a DPP row (lanes l with equal l/16): swap with
-// lane^1 and lane^2 (quad permutes), then with the mirrored lane in the half
-// row and in the row.  Every lane ends with the same bits (each step adds two
-// equal partial sums in either order).  All 16 lanes of the row must be active.
-__device__ __forceinline__ double sum16(double v) {
-    v += dpp<0xB1>(v);     // quad_perm [1,0,3,2]
-    v += dpp<0x4E>(v);     // quad_perm [2,3,0,1]
-    v += dpp<0x141>(v);    // row_half_mirror
-    v += dpp<0x140>(v);    // row_mirror
-    return v;
-}
-
-// sqrt(t) and 1/x for positive normal t and nonzero normal x, from the
-// hardware approximations (v_rsq_f64, v_rcp_f64):
-//  - sqrt: one step of Goldschmidt's coupled iteration for s ~ sqrt(t) and
-//    h ~ 1/(2 sqrt(t)) (residual e = 1/2 - h s, then s += s e, h += h e),
-//    followed by two Newton-Raphson corrections s += h (t - s^2);
-//  - 1/x: two Newton-Raphson steps r += r (1 - x r).
-// Both end within an ulp, without the special-value and scaling paths of the
-// IEEE library forms, which the Householder steps never need.
-__device__ __forceinline__ double refined_sqrt(double t) {
-    const double r = __builtin_amdgcn_rsq(t);
-    double s = t * r, h = 0.5 * r;
-    const double e = fma(-h, s, 0.5);
-    s = fma(s, e, s);
-    h = fma(h, e, h);
-    double d = fma(-s, s, t);
-    s = fma(d, h, s);
-    d = fma(-s, s, t);
-    return fma(d, h, s);
-}
-
-__device__ __forceinline__ double refined_rcp(double x) {
-    double r = __builtin_amdgcn_rcp(x);
-    double e = fma(-x, r, 1.0);
-    r = fma(r, e, r);
-    e = fma(-x, r, 1.0);
-    return fma(r, e, r);
-}
-
-// Value of lane `src` (wave-uniform) of a double.
-__device__ __forceinline__ double readlane64(double v, int src) {
-    const long long b = __builtin_bit_cast(long long, v);
-    const int lo = __builtin_amdgcn_readlane((int)b, src);
-    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), src);
-    return __builtin_bit_cast(double, ((long long)hi << 32) | (long long)(unsigned int)lo);
-}
 
 // The unit a workgroup of the persistent scheduler finished last, whose
 // output stores may still be in flight.  The next unit retires it once its own
@@ -386,14 +406,14 @@ __device__ __forceinline__ void retire(const KArgs& a, Prev& p) {
 // record block's loads are issued.
 // ---------------------------------------------------------------------------
 template <int NB, int NBLK, int KIND, bool CO, bool HQ>
-__device__ __forceinline__ void apply_blocks(const Rec& rec, const TileView& T1, int c0, bool active,
-                                             d4* c2, double* lds, const KArgs& a, Prev& prev) {
+__device__ __forceinline__ void apply_blocks(const Rec& rec, const TileLane& T1, bool active, d4* c2,
+                                             double* lds, const KArgs& a, Prev& prev) {
     constexpr int MT = NB / 16;
-    constexpr int LDV = NB + 1;
+    constexpr int LDV = Shape<NB>::LDV;
     constexpr int BUF = 16 * LDV + 256;       // V_b (NB x 16, stride LDV) then T_b^T (16 x 16)
     constexpr int PRE = 16 * NB / NT + 1;     // staged doubles per thread and block
     constexpr bool HASC1 = KIND != K_UNMQR;
-    const int tid = threadIdx.x, lane = tid & 63, j = lane & 15, g = lane >> 4;
+    const int tid = here(threadIdx.x), lane = tid & 63, j = lane & 15, g = lane >> 4, pj = perm16(j);
 
     // Block b of the record: V(:, 16b..16b+15) is contiguous (column-major),
     // T_b^T follows the nb x nb matrix.  Thread t stages elements t + NT k of
@@ -419,7 +439,7 @@ __device__ __forceinline__ void apply_blocks(const Rec& rec, const TileView& T1,
     retire(a, prev);
     stage(0, pre);
     d4 C1n = {0.0, 0.0, 0.0, 0.0};
-    if (HASC1 && active) C1n = load16(T1, 16 * blk(0), c0);
+    if (HASC1 && active) C1n = T1.load(16 * blk(0));
     lds_barrier();
 #pragma unroll
     for (int st = 0; st < NBLK; ++st) {
@@ -428,7 +448,7 @@ __device__ __forceinline__ void apply_blocks(const Rec& rec, const TileView& T1,
         const double* Ts = Vs + 16 * LDV;
         if (st + 1 < NBLK) fetch(blk(st + 1), pre);
         const d4 C1b = C1n;
-        if (HASC1 && active && st + 1 < NBLK) C1n = load16(T1, 16 * blk(st + 1), c0);
+        if (HASC1 && active && st + 1 < NBLK) C1n = T1.load(16 * blk(st + 1));
         if (active) {
             // Two accumulators halve the dependent-MFMA chain of W.
             d4 Wp[2] = {C1b, {0.0, 0.0, 0.0, 0.0}};
@@ -438,7 +458,7 @@ __device__ __forceinline__ void apply_blocks(const Rec& rec, const TileView& T1,
                 if (KIND == K_TTMQR && i > b) continue;
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    Wp[r & 1] = mfma(Vs[(16 * i + 4 * r + g) + j * LDV], c2[i][r], Wp[r & 1]);
+                    Wp[r & 1] = mfma(Vs[(16 * i + 4 * g + r) + pj * LDV], c2[i][r], Wp[r & 1]);
                 // at nb = 256 the slice takes half the registers: keep the
                 // operand loads of later row tiles from being hoisted
                 if (MT > 8 && (i & 1)) SCHED_FENCE();
@@ -448,16 +468,16 @@ __device__ __forceinline__ void apply_blocks(const Rec& rec, const TileView& T1,
             // Ts holds T_b^T column-major: T_b(k, i) at i + 16 k.
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                W2 = mfma(-(HQ ? Ts[(4 * r + g) + 16 * j] : Ts[j + 16 * (4 * r + g)]), W[r], W2);
+                W2 = mfma(-(HQ ? Ts[(4 * g + r) + 16 * pj] : Ts[pj + 16 * (4 * g + r)]), W[r], W2);
             // W2 holds -T_b^T W: negating the 4 T operands spares negating
             // the V operands of the update below.
-            if (HASC1) store16<CO>(T1, 16 * b, c0, C1b + W2);
+            if (HASC1) T1.store<CO>(16 * b, C1b + W2);
 #pragma unroll
             for (int i = 0; i < MT; ++i) {
                 if (KIND == K_UNMQR && i < b) continue;
                 if (KIND == K_TTMQR && i > b) continue;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) c2[i] = mfma(Vs[(16 * i + j) + (4 * r + g) * LDV], W2[r], c2[i]);
+                for (int r = 0; r < 4; ++r) c2[i] = mfma(Vs[(16 * i + pj) + (4 * g + r) * LDV], W2[r], c2[i]);
                 if (MT > 8 && (i & 1)) SCHED_FENCE();
             }
         }
@@ -477,634 +497,562 @@ __device__ __forceinline__ void apply_blocks(const Rec& rec, const TileView& T1,
 // diagonal made explicit for GEQRT), which are full for TS and upper
 // triangular for TT.
 //
-// Columns are processed in blocks of 16 (the paper's inner blocking ib):
-//  1. leaf: the 16 columns of block b are factored one column at a time by
-//     the 256 threads of waves 0-3 (thread (c, q) holds rows q, q+16, ... of
-//     leaf column c in registers; one barrier per column).  The dot products of each new
-//     reflector with the finished ones give G_b = U_b^T U_b, from which
-//     T_b (16 x 16 upper, Q_b = I - U_b T_b U_b^T) follows by the forward
-//     recurrence T(c,c) = tau_c, T(0:c-1,c) = -tau_c T(0:c-1,0:c-1) G(0:c-1,c).
-//     Waves 4-7, idle in the leaf, form T_b meanwhile, one column behind it.
-//  2. trailing: Q_b^T is applied to the column tiles right of the block with
-//     three 16-wide MFMA products (W = U_b^T X, W = T_b^T W, X -= U_b W).
+// Column tile w (nb x 16) stays in the registers of wave w, in the MFMA
+// result layout, from its first load to its factorization.  Block b (the
+// paper's inner blocking ib = 16):
+//  1. leaf: wave b factors its own column tile alone (leaf_columns) and writes
+//     U_b and T_b to LDS; one workgroup barrier.
+//  2. the waves right of it apply Q_b^T to their tiles with three 16-wide MFMA
+//     products (W = R1 + U_b^T X, W = T_b^T W, X -= U_b W), wave b + 1 first
+//     (it holds the next leaf), while wave b writes the block's outputs.
 // Record (FP64): V (nb x nb, column-major), then the nb/16 blocks T_b^T
 // (16 x 16 column-major) -- the same blocked compact-WY form the update
 // kernels apply.
 // ---------------------------------------------------------------------------
 
-// Step cc of the forward recurrence for T_b on waves 4-7: thread
-// (i, l) = (tid/16 - 16, tid%16) holds T(i, l); column cc is formed once
-// G(:, cc) is complete.
-__device__ __forceinline__ void t_step(double& til, int cc, const double* taus, const double* Gs, int lj, int lq) {
-    const int ti = lj - 16;
-    const double tcv = taus[cc];
-    const double gv = Gs[lq + 16 * cc];
-    const double sm = sum16((lq >= ti && lq < cc) ? til * gv : 0.0);
-    const double tic = cc < ti ? 0.0 : (cc == ti ? tcv : -tcv * sm);
-    if (lq == cc) til = tic;
+// Broadcasts within rows of 16 lanes: DPP row_newbcast, the 64-bit DPP control,
+// as the first operand of an FMA (dst += src0[lane C of the row] * src1).  The
+// compiler does not fold its broadcast moves into FMAs, and unfolded they
+// double the leaf's instructions, so these are written out.  A DPP operand
+// must not have been written by the two preceding instructions, which the
+// compiler does not check for inline assembly: every block starts with two
+// wait states, and inside a block an operand is written at least three
+// instructions before it is broadcast.
+#define BB_BC " row_newbcast:%c[c] row_mask:0xf bank_mask:0xf\n\t"
+#define BB_BN " row_newbcast:%c[n] row_mask:0xf bank_mask:0xf\n\t"
+
+// Lane C's value in the whole row.  WAIT: wait states before the read, two
+// after a vector instruction; six after the 4 x 4 x 4 matrix product (which
+// the compiler keeps only for its own instructions).
+template <int C, int WAIT = 2>
+__device__ __forceinline__ double bcast16(double v) {
+    double r;
+    asm("s_nop %[w]\n\tv_mov_b64_dpp %[r], %[v]" BB_BC : [r] "=v"(r) : [v] "v"(v), [c] "n"(C), [w] "n"(WAIT - 1));
+    return r;
 }
 
-// The 16 columns of leaf block B (one barrier per column).  lw selects the
-// role: the leaf waves factor (x: their leaf slots, r1: PAIR's R1 entry),
-// the other waves form T_b one column behind (til).  The column loop is
-// instantiated per block index B, which fixes at compile time where each
-// register slot s (rows lq + 16 s) lies relative to the block's diagonal
-// rows 16 B .. 16 B + 15: only slot B straddles the diagonal and needs
-// per-lane masks.  Slots that can hold no reflector entry (above the
-// diagonal block for GEQRT, below it for the triangle of TTQRT) are left out
-// of every step.
-template <int NB, int KIND, int B>
-__device__ __forceinline__ void leaf_columns(bool lw, double (&x)[NB / 16], double& r1, double& til, double* vbuf,
-                                             double* taus, double* Gs, int lj, int lq) {
-    constexpr int SR = NB / 16;
-    constexpr bool PAIR = KIND != K_GEQRT;
-    constexpr bool TT = KIND == K_TTQRT;
-    constexpr int S0 = PAIR ? 0 : B;        // live slots [S0, S1)
-    constexpr int S1 = TT ? B + 1 : SR;
-    constexpr int NL = S1 - S0;
-    for (int c = 0; c < 16; ++c) {
-        double* vb = vbuf + (c & 1) * NB;
-        if (lw && lj == c) {
-            // Reflector entry in slot s: rows below the diagonal (GEQRT),
-            // the whole tile (TSQRT) or rows up to it (TTQRT).
-            auto tail = [&](int s) {
-                if (!PAIR) return s > B || lq > c;
-                if (TT) return s < B || lq <= c;
-                return true;
-            };
-            // sum of squares in up to four partial sums
-            constexpr int NQ = NL < 4 ? NL : 4;
-            double q[NQ], al = 0.0;
-#pragma unroll
-            for (int k = 0; k < NQ; ++k) q[k] = 0.0;
-#pragma unroll
-            for (int k = 0; k < NL; ++k) {
-                const int s = S0 + k;
-                if (tail(s)) q[k % NQ] = fma(x[s], x[s], q[k % NQ]);
-            }
-            if (!PAIR && lq == c) al = x[B];
-#pragma unroll
-            for (int h = 1; h < NQ; h *= 2)
-#pragma unroll
-                for (int k = 0; k + h < NQ; k += 2 * h) q[k] += q[k + h];
-            if (PAIR && lq == c) al = r1;
-            const double ss = sum16(q[0]);
-            // alpha sits in the lane with row phase c of this column's 16
-            // lanes (lane 16 (c % 4) + c of the wave): read it there.
-            al = readlane64(al, 16 * (c & 3) + c);
-            double tau = 0.0, beta = al, scale = 0.0;
-            if (ss != 0.0) {
-                // tau = (beta - al) / beta and scale = 1 / (al - beta) from
-                // one reciprocal: with d = al - beta, 1 / (beta d) gives
-                // tau = -d^2 / (beta d) and scale = beta / (beta d).
-                const double nrm = refined_sqrt(fma(al, al, ss));
-                beta = al >= 0.0 ? -nrm : nrm;
-                const double d = al - beta;
-                const double inv = refined_rcp(beta * d);
-                tau = -(d * d) * inv;
-                scale = beta * inv;
-            }
-#pragma unroll
-            for (int k = 0; k < NL; ++k) {
-                const int s = S0 + k;
-                double vv;
-                if (!PAIR && s == B) {
-                    const bool t = lq > c, dg = lq == c;
-                    if (t) x[s] *= scale;
-                    if (dg) x[s] = beta;
-                    vv = t ? x[s] : (dg ? 1.0 : 0.0);
-                } else if (TT && s == B) {
-                    const bool t = lq <= c;
-                    if (t) x[s] *= scale;
-                    vv = t ? x[s] : 0.0;
-                } else {
-                    x[s] *= scale;
-                    vv = x[s];
-                }
-                vb[lq + 16 * s] = vv;
-            }
-            if (PAIR && lq == c) r1 = beta;
-            if (lq == 0) taus[c] = tau;
-        }
-        lds_barrier();
-        if (!lw) {
-            // G(:, c-1) was completed before this barrier
-            if (c > 0) t_step(til, c - 1, taus, Gs, lj, lq);
-        } else {
-            // the reflector and tau_c are read together (one LDS latency)
-            const double tc = taus[c];
-            double vv[SR];
-#pragma unroll
-            for (int k = 0; k < NL; ++k) vv[S0 + k] = vb[lq + 16 * (S0 + k)];
-            // tau_c is needed only after the dot product's reduction; holding
-            // it here keeps its read in the same batch as the reflector's
-            // instead of after the reduction.
-            asm volatile("" ::"v"(tc));
-            // tau_c = 0 (H_c = I) needs no branch: it zeroes the update and
-            // every T entry that G(:, c) feeds.
-            if (lj != c) {
-                double dp[2] = {0.0, 0.0};
-#pragma unroll
-                for (int k = 0; k < NL; ++k) dp[k & 1] = fma(vv[S0 + k], x[S0 + k], dp[k & 1]);
-                double d = dp[0] + dp[1];
-                if (PAIR && lj > c && lq == c) d += r1;     // e_c meets row c of R1
-                d = sum16(d);
-                if (lj > c) {
-                    const double wv = tc * d;
-#pragma unroll
-                    for (int k = 0; k < NL; ++k) x[S0 + k] -= wv * vv[S0 + k];
-                    if (PAIR && lq == c) r1 -= wv;
-                } else if (lq == 0) {
-                    Gs[lj + 16 * c] = d;            // u_lj . u_c
-                }
-            }
-        }
-    }
+// v += coef * (lane C's v) for eight values, then acc += (lane C + 1's v) * v
+// (two sums: an FMA's result is ready for the next but one).
+template <int C>
+__device__ __forceinline__ void update_dot8(double* v, double coef, double (&acc)[2]) {
+    asm volatile(
+        "s_nop 1\n\t"
+        "v_fmac_f64_dpp %[v0], %[v0], %[f]" BB_BC "v_fmac_f64_dpp %[v1], %[v1], %[f]" BB_BC
+        "v_fmac_f64_dpp %[v2], %[v2], %[f]" BB_BC "v_fmac_f64_dpp %[v3], %[v3], %[f]" BB_BC
+        "v_fmac_f64_dpp %[v4], %[v4], %[f]" BB_BC "v_fmac_f64_dpp %[v5], %[v5], %[f]" BB_BC
+        "v_fmac_f64_dpp %[v6], %[v6], %[f]" BB_BC "v_fmac_f64_dpp %[v7], %[v7], %[f]" BB_BC
+        "v_fmac_f64_dpp %[a0], %[v0], %[v0]" BB_BN "v_fmac_f64_dpp %[a1], %[v1], %[v1]" BB_BN
+        "v_fmac_f64_dpp %[a0], %[v2], %[v2]" BB_BN "v_fmac_f64_dpp %[a1], %[v3], %[v3]" BB_BN
+        "v_fmac_f64_dpp %[a0], %[v4], %[v4]" BB_BN "v_fmac_f64_dpp %[a1], %[v5], %[v5]" BB_BN
+        "v_fmac_f64_dpp %[a0], %[v6], %[v6]" BB_BN "v_fmac_f64_dpp %[a1], %[v7], %[v7]" BB_BN
+        : [v0] "+v"(v[0]), [v1] "+v"(v[1]), [v2] "+v"(v[2]), [v3] "+v"(v[3]), [v4] "+v"(v[4]), [v5] "+v"(v[5]),
+          [v6] "+v"(v[6]), [v7] "+v"(v[7]), [a0] "+v"(acc[0]), [a1] "+v"(acc[1])
+        : [f] "v"(coef), [c] "n"(C), [n] "n"(C + 1));
 }
 
-// Dispatch of leaf block b (runtime) to its instantiation, for the blocks
-// BASE .. BASE + COUNT - 1 (COUNT <= 8).
-template <int NB, int KIND, int BASE, int COUNT>
-__device__ __forceinline__ void leaf_block(int b, bool lw, double (&x)[NB / 16], double& r1, double& til,
-                                           double* vbuf, double* taus, double* Gs, int lj, int lq) {
-    constexpr int MT = NB / 16;
-    auto go = [&](auto bc) {
-        constexpr int B = decltype(bc)::value;
-        if constexpr (B < MT && B < BASE + COUNT) leaf_columns<NB, KIND, B>(lw, x, r1, til, vbuf, taus, Gs, lj, lq);
+// v += coef * (lane C's v) for four values (two wait states at the end: a
+// matrix product reads them next).
+template <int C>
+__device__ __forceinline__ void update4(double (&v)[4], double coef) {
+    asm volatile(
+        "s_nop 1\n\t"
+        "v_fmac_f64_dpp %[v0], %[v0], %[f]" BB_BC "v_fmac_f64_dpp %[v1], %[v1], %[f]" BB_BC
+        "v_fmac_f64_dpp %[v2], %[v2], %[f]" BB_BC "v_fmac_f64_dpp %[v3], %[v3], %[f]" BB_BC
+        "s_nop 1"
+        : [v0] "+v"(v[0]), [v1] "+v"(v[1]), [v2] "+v"(v[2]), [v3] "+v"(v[3])
+        : [f] "v"(coef), [c] "n"(C));
+}
+
+// acc += (lane C's v) * v for four values.
+template <int C>
+__device__ __forceinline__ void dot4(const double* v, double (&acc)[2]) {
+    asm volatile(
+        "s_nop 1\n\t"
+        "v_fmac_f64_dpp %[a0], %[v0], %[v0]" BB_BC "v_fmac_f64_dpp %[a1], %[v1], %[v1]" BB_BC
+        "v_fmac_f64_dpp %[a0], %[v2], %[v2]" BB_BC "v_fmac_f64_dpp %[a1], %[v3], %[v3]" BB_BC
+        : [a0] "+v"(acc[0]), [a1] "+v"(acc[1])
+        : [v0] "v"(v[0]), [v1] "v"(v[1]), [v2] "v"(v[2]), [v3] "v"(v[3]), [c] "n"(C));
+}
+
+// s += sum of (lane L .. L + 3's v) * u[0 .. 3], in two sums.
+template <int L>
+__device__ __forceinline__ void row_dot4(double v, const double* u, double (&s)[2]) {
+    asm("s_nop 1\n\t"
+        "v_fmac_f64_dpp %[s0], %[v], %[u0] row_newbcast:%c[l0] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %[s1], %[v], %[u1] row_newbcast:%c[l1] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %[s0], %[v], %[u2] row_newbcast:%c[l2] row_mask:0xf bank_mask:0xf\n\t"
+        "v_fmac_f64_dpp %[s1], %[v], %[u3] row_newbcast:%c[l3] row_mask:0xf bank_mask:0xf"
+        : [s0] "+v"(s[0]), [s1] "+v"(s[1])
+        : [v] "v"(v), [u0] "v"(u[0]), [u1] "v"(u[1]), [u2] "v"(u[2]), [u3] "v"(u[3]), [l0] "n"(L), [l1] "n"(L + 1),
+          [l2] "n"(L + 2), [l3] "n"(L + 3));
+}
+
+// f(0), f(1), .. f(N - 1) with the index as a compile-time constant (the lane
+// of a DPP broadcast is part of the instruction).
+template <class F, int... I>
+__device__ __forceinline__ void for_constants_of(F f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void for_constants(F f) {
+    for_constants_of(f, std::make_integer_sequence<int, N>{});
+}
+
+// Sum over the four rows of 16 lanes (f = 1), or row k's value (f = 1 in row k's
+// lanes, else 0), in every lane: four 4 x 4 x 4 matrix products whose k index
+// is the row, one instruction where lane exchanges take a dozen.
+__device__ __forceinline__ double across_rows(double f, double v) {
+    return __builtin_amdgcn_mfma_f64_4x4x4f64(f, v, 0.0, 0, 0, 0);
+}
+
+// LDS words through which the leaf of a block hands its T_b column by column
+// to the wave that forms it: G(l, c) at 16 c + l, tau_c, and the number of
+// columns handed over since the panel began.
+struct GramLds {
+    double* G;                      // 256
+    double* tau;                    // 16
+    int* done;
+};
+
+// Factors one column tile in the registers of one wave.  Lane (g, j) =
+// (lane / 16, lane % 16) holds column j: in x rows 16 i + 4 g + r (element r
+// of row tile i) below the block's diagonal 16 x 16 block, in xd that block's
+// rows 4 g + r (GEQRT) and in LDS at D[row + 17 j] the block itself (TS/TT:
+// the rows of R1, zero below its diagonal, so that reflectors have no entries
+// there).  Only row tiles clo CH .. chi CH - 1 of x can be nonzero.
+//
+// One pass over the rows per column: the dot products of column c with every
+// column j give the reflector's norm (j = c), the products w_j that update
+// the columns right of it (j > c) and its Gram column with the finished
+// reflectors (j < c), which T_b needs and another wave works on meanwhile.
+// Reflector tails stay unscaled; lane j keeps column j's factor
+// 1 / (alpha - beta) in sc.  The update with column c and the dot products
+// of column c + 1 share a loop.  Row c of the diagonal block is taken out of
+// xd before column c's dot products and finished in D.
+//
+// What bounds it: the issue of one wave, about 2 (rows / 4) + 50 FP64
+// instructions a column at five cycles each, with a chain of about 16
+// dependent ones (eight cycles each) between two columns.  A column needs no
+// signal from another wave and no barrier.
+//
+// On return D holds R on and above the diagonal (and GEQRT's unscaled tails
+// below).
+template <int MT>
+__device__ __forceinline__ void leaf_columns(double (&x)[4 * MT], double (&xd)[4], double* D, double& sc, bool pair,
+                                             int clo, int chi, const GramLds& gram, int done0) {
+    constexpr int CH = MT < 4 ? MT : 4, NC = MT / CH;   // row tiles per chunk, chunks
+    const int lane = threadIdx.x & 63;
+    // Row R of the diagonal block, taken out of xd.
+    auto take_row = [&](auto rc) {
+        constexpr int R = decltype(rc)::value;
+        const bool in = (here(lane) >> 4) == R / 4;
+        const double v = across_rows(in ? 1.0 : 0.0, xd[R % 4]);
+        xd[R % 4] = in ? 0.0 : xd[R % 4];
+        return v;
     };
-    if (b < BASE || b >= BASE + COUNT) return;      // uniform
-    switch (b - BASE) {
-        case 0: go(std::integral_constant<int, BASE + 0>{}); break;
-        case 1: go(std::integral_constant<int, BASE + 1>{}); break;
-        case 2: go(std::integral_constant<int, BASE + 2>{}); break;
-        case 3: go(std::integral_constant<int, BASE + 3>{}); break;
-        case 4: go(std::integral_constant<int, BASE + 4>{}); break;
-        case 5: go(std::integral_constant<int, BASE + 5>{}); break;
-        case 6: go(std::integral_constant<int, BASE + 6>{}); break;
-        default: go(std::integral_constant<int, BASE + 7>{}); break;
+    double acc[2] = {0.0, 0.0};
+    double a = D[17 * (lane & 15)];
+    if (!pair) {
+        a = take_row(std::integral_constant<int, 0>{});
+        dot4<0>(xd, acc);
     }
-}
-
-// Panel for nb <= 128: the whole tile is register-resident, column tile J
-// on wave J for the whole kernel; all eight waves apply the trailing
-// products.
-template <int NB, int KIND, bool CO>
-__device__ __forceinline__ void panel_resident(const KArgs& a, const DevTask& tk, double* lds, Prev& prev) {
-    using S = Shape<NB>;
-    constexpr int MT = S::MT, LDL = S::LDL;
-    static_assert(MT <= 8, "one column tile per wave");
-    constexpr int SR = NB / 16;             // leaf rows per thread
-    constexpr bool PAIR = KIND != K_GEQRT;
-    constexpr bool TT = KIND == K_TTQRT;
-    double* Lf = lds;                       // leaf: NB x 16, stride LDL
-    double* vbuf = Lf + 16 * LDL;           // 2 x NB: broadcast of the current reflector
-    double* taus = vbuf + 2 * NB;           // 16
-    double* Gs = taus + 16;                 // G(l, c) at l + 16 c
-    double* TbT = Gs + 256;                 // T(k, i) at i + 16 k
-    double* R1s = TbT + 256;                // PAIR: R1(16b + lq, 16b + lj) of the next block, per leaf thread
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, j = lane & 15, g = lane >> 4;
-    const int lj = tid >> 4, lq = tid & 15; // leaf column, row phase
-    const bool lw = tid < 256;              // waves 0-3 run the leaf, waves 4-7 form T_b
-    const bool own = w < MT;                // the wave holds column tile w
-
-    const MatDesc md = mat_desc(a, tk.mat);
-    const TileView T1 = view(md, tk, tk.r1, tk.c1, NB);
-    const TileView TX = PAIR ? view(md, tk, tk.r2, tk.c2, NB) : T1;
-    double* rec = record<NB>(md, tk);
-    double* gV = rec;
-    double* gTt = rec + NB * NB;
-
-    d4 xt[MT];
-    if (own) load_slice<MT>(TX, 16 * w, xt);
-    // R1's row block b is changed by no block before b (the reflectors of
-    // block b' touch rows of block b' only), so the diagonal entries the leaf
-    // of block b + 1 starts from are read during block b, before that block's
-    // stores: with one in-order counter for loads and stores, a load issued
-    // after the stores would also wait for them.  Each leaf thread keeps its
-    // own entry in LDS until it is needed.
-    if (PAIR && lw) R1s[tid] = T1.get(lq, lj);
-    retire(a, prev);
-
-    for (int b = 0; b < MT; ++b) {
-        // Column tile b goes to the leaf buffer.
-        if (w == b) {
 #pragma unroll
-            for (int i = 0; i < MT; ++i)
+    for (int k = 0; k < NC; ++k)
+        if (k >= clo && k < chi) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r) Lf[(16 * i + 4 * r + g) + j * LDL] = xt[i][r];
+            for (int e = 4 * CH * k; e < 4 * CH * (k + 1); e += 4) dot4<0>(x + e, acc);
         }
-        if (lw) Gs[tid] = 0.0;
-        lds_barrier();
-
-        // 1. Leaf (waves 0-3), T_b one column behind (waves 4-7).
-        double x[SR];
-        double r1 = 0.0, til = 0.0;
-        if (lw) {
-#pragma unroll
-            for (int s = 0; s < SR; ++s) x[s] = Lf[(lq + 16 * s) + lj * LDL];
-            if (PAIR) r1 = R1s[tid];
+    sc = 0.0;
+    for_constants<16>([&](auto cc) {
+        constexpr int C = decltype(cc)::value;
+        const int j = here(lane) & 15;
+        const double dot = across_rows(1.0, acc[0] + acc[1]);
+        // With nrm = sqrt(al^2 + ss) and r = 1 / nrm: beta = -sign(al) nrm,
+        // tau = (beta - al) / beta = 1 + |al| r, scale = 1 / (al - beta).
+        // r and the reciprocal each take one step of third order from the
+        // hardware approximations (r (1 + e/2 + 3 e^2/8), y (1 + e + e^2)),
+        // the second's from an approximation formed beside the first's step;
+        // s0 and s1 (~ nrm) carry al's sign.
+        const double al = bcast16<C, 6>(a), ss = bcast16<C, 6>(dot);
+        const double tn = fma(al, al, ss), ts = copysign(tn, al), r0 = __builtin_amdgcn_rsq(tn);
+        const double s0 = ts * r0;
+        const double y0 = __builtin_amdgcn_rcp(al + s0);
+        const double e0 = fma(-fabs(s0), r0, 1.0);
+        const double r = fma(r0 * e0, fma(e0, 0.375, 0.5), r0);
+        const double s1 = ts * r;
+        const double e1 = fma(-(al + s1), y0, 1.0);
+        double tau = fma(fabs(al), r, 1.0), scale = fma(y0, fma(e1, e1, e1), y0);
+        double bt = -fma(fma(-s1, s1, tn), copysign(0.5 * r, al), s1);
+        if (__builtin_amdgcn_ballot_w64(ss == 0.0) != 0) {      // zero tail: H_c = I
+            asm volatile("");                                   // (a branch, not selects)
+            tau = 0.0;
+            scale = 0.0;
+            bt = al;
         }
-        leaf_block<NB, KIND, 0, MT>(b, lw, x, r1, til, vbuf, taus, Gs, lj, lq);
-        // Loads ahead of the leaf outputs' stores: the next block's diagonal
-        // entry of R1 and this block's rows of R1 in the trailing tiles.
-        double r1n = 0.0;
-        if (PAIR && lw && b + 1 < MT) r1n = T1.get(16 * (b + 1) + lq, 16 * (b + 1) + lj);
-        const bool act = own && w > b;
-        d4 R1b = {0.0, 0.0, 0.0, 0.0}, W;
-        if (PAIR && act) R1b = load16(T1, 16 * b, 16 * w);
-        // Leaf outputs, each thread on the leaf slots it read: explicit U_b
-        // into the leaf buffer and the record, R (GEQRT) or zeros (TS/TT)
-        // into the matrix.
-        if (lw) {
-            const int col = 16 * b + lj;
-#pragma unroll
-            for (int s = 0; s < SR; ++s) {
-                const int row = lq + 16 * s;
-                double vv;
-                if (PAIR) vv = (TT && row > col) ? 0.0 : x[s];
-                else vv = row > col ? x[s] : (row == col ? 1.0 : 0.0);
-                Lf[row + lj * LDL] = vv;
-                gstore<CO>(gV + row + (int64_t)col * NB, vv);
-                TX.put<CO>(row, col, PAIR ? 0.0 : (row <= col ? x[s] : 0.0));
+        const double h = fma(scale, dot, a);            // u_c . column j
+        const double tj = j > C ? tau : 0.0;            // columns right of c
+        const double coef = h * (-tj * scale);
+        double an = 0.0;
+        if constexpr (C < 15) {
+            acc[0] = acc[1] = 0.0;
+            an = D[C + 1 + 17 * j];
+            if (!pair) {
+                update4<C>(xd, coef);
+                an = take_row(std::integral_constant<int, C + 1>{});
+                dot4<C + 1>(xd, acc);
             }
-            if (PAIR) T1.put<CO>(16 * b + lq, 16 * b + lj, r1);
-            if (PAIR && b + 1 < MT) R1s[tid] = r1n;
-        }
-        lds_barrier();
-
-        // 2. Trailing update of the column tiles right of block b:
-        // W = R1 + U_b^T X, then W = T_b^T W, then X -= U_b W.
-        W = R1b;
-        double la[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) la[r] = Lf[(4 * r + g) + j * LDL];
+            for (int k = 0; k < NC; ++k)
+                if (k >= clo && k < chi) {
 #pragma unroll
-        for (int i = 0; i < MT; ++i) {
-            double ln[4];
-            if (i + 1 < MT) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) ln[r] = Lf[(16 * (i + 1) + 4 * r + g) + j * LDL];
-            }
-            const bool rows = (PAIR || i >= b) && (!TT || i <= b);
-            if (act && rows) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) W = mfma(la[r], xt[i][r], W);
-            }
-            SCHED_FENCE();
-            if (i + 1 < MT) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) la[r] = ln[r];
-            }
-        }
-        if (!lw) {
-            t_step(til, 15, taus, Gs, lj, lq);
-            TbT[lq + 16 * (lj - 16)] = til;     // T(i, l)
-            gstore<CO>(gTt + 256 * b + (tid - 256), til);
-        }
-        lds_barrier();
-        if (act) {
-            d4 W2 = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int r = 0; r < 4; ++r) W2 = mfma(TbT[j + 16 * (4 * r + g)], W[r], W2);
-            if (PAIR) store16<CO>(T1, 16 * b, 16 * w, R1b - W2);
-            W = W2;
-        }
-#pragma unroll
-        for (int i = 0; i < MT; ++i) {
-            if (!PAIR && i < b) continue;
-            if (TT && i > b) continue;
-            double lu[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) lu[r] = -Lf[(16 * i + j) + (4 * r + g) * LDL];
-            if (act) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) xt[i] = mfma(lu[r], W[r], xt[i]);
-            }
-            SCHED_FENCE();
-        }
-        lds_barrier();
-    }
-}
-
-// Synchronization inside one workgroup through LDS words, for code where the
-// waves of the workgroup follow different paths (no workgroup barrier).
-// wait_geq: wait until *f >= target; false once the watchdog has expired
-// (the error word is then set and the caller gives up).  post: make this
-// wave's earlier LDS writes visible, then add 1 to *f.
-__device__ __forceinline__ bool wait_geq(const int* f, int target, const KArgs& a) {
-    uint64_t t0 = 0;
-    for (int spin = 0;; ++spin) {
-        const int v = __builtin_amdgcn_readfirstlane(
-            __hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
-        if (v >= target) break;
-        __builtin_amdgcn_s_sleep(1);        // leave issue slots to the working waves
-        // the clock (a scalar memory read) only every 128 polls
-        if ((spin & 127) == 0) {
-            const uint64_t t = wall_clock64();
-            if (spin == 0) {
-                t0 = t;
-            } else if ((int64_t)(t - t0) > a.watchdog_ticks) {
-                if ((threadIdx.x & 63) == 0)
-                    __hip_atomic_store(&a.ctrl[CTRL_ERROR], 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                return false;
-            }
-        }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-    return true;
-}
-
-__device__ __forceinline__ void post(int* f) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    if ((threadIdx.x & 63) == 0) __hip_atomic_fetch_add(f, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
-// Panel for nb = 256 (16 column tiles of 256 x 16, each taking half of a
-// wave's registers, so no tile can stay resident next to the leaf).  The
-// waves split into two roles that run side by side and meet only through
-// LDS counters:
-//  - leaf role (waves 0-3): factors block b from the LDS copy of column
-//    tile b.  Columns are handed on through a per-column counter instead of
-//    a workgroup barrier; the 16 reflectors of the block stay in an LDS ring.
-//    Then it writes U_b (explicit), the record's V, and R or zeros.
-//  - tile role (waves 4-7): forms T_b from the dot products (each 16-lane row
-//    of T on its own), then applies Q_b^T first to tile b + 1, which it hands
-//    to the next leaf through LDS (look-ahead), and then to the other tiles
-//    right of b, which it streams from and back to memory.  Tile J always
-//    goes to wave 4 + J % 4, so every lane reads back only what it stored.
-// The leaf of block b + 1 therefore runs while the tile role is still
-// applying block b to tiles b + 2 ... 15.
-template <int NB, int KIND, bool CO>
-__device__ __forceinline__ void panel_split(const KArgs& a, const DevTask& tk, double* lds, Prev& prev) {
-    using S = Shape<NB>;
-    constexpr int MT = S::MT, LDL = S::LDL;
-    constexpr int SR = NB / 16;
-    constexpr bool PAIR = KIND != K_GEQRT;
-    constexpr bool TT = KIND == K_TTQRT;
-    double* buf0 = lds;                     // column tile of the leaf, by block parity: NB x 16, stride LDL
-    double* vring = lds + 32 * LDL;         // the 16 reflectors of the current block, NB each
-    double* taus = vring + 16 * NB;
-    double* Gs = taus + 16;                 // G(l, c) at l + 16 c
-    double* TbT0 = Gs + 256;                // T_b (T(k, i) at i + 16 k), by block parity
-    double* Wpart = TbT0 + 512;             // the four tile waves' partial W, by tile parity
-    int* flags = (int*)(Wpart + 2 * 1024);  // counters
-    static_assert(32 * LDL + 16 * NB + 16 + 256 + 512 + 2048 + 4 <= S::LDS, "LDS layout");
-    enum { F_COL = 0, F_LEAF = 1, F_TB = 2, F_TILE = 3, F_WA = 4, F_WORDS = 8 };
-    const int tid = threadIdx.x, lane = tid & 63, j = lane & 15, g = lane >> 4;
-    const int lj = tid >> 4, lq = tid & 15;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-
-    const MatDesc md = mat_desc(a, tk.mat);
-    const TileView T1 = view(md, tk, tk.r1, tk.c1, NB);
-    const TileView TX = PAIR ? view(md, tk, tk.r2, tk.c2, NB) : T1;
-    double* rec = record<NB>(md, tk);
-    double* gV = rec;
-    double* gTt = rec + NB * NB;
-
-    // column tile 0 into the first leaf buffer; counters to zero
-#pragma unroll
-    for (int k = 0; k < NB * 16 / NT; ++k) {
-        const int e = tid + NT * k, r = e % NB, c = e / NB;
-        buf0[r + c * LDL] = TX.get(r, c);
-    }
-    if (tid < F_WORDS) flags[tid] = 0;
-    retire(a, prev);                        // (a workgroup barrier)
-    lds_barrier();
-
-    if (w < 4) {
-        // ---- leaf role -------------------------------------------------
-        double r1 = PAIR ? T1.get(lq, lj) : 0.0;
-        for (int b = 0; b < MT; ++b) {
-            if (!wait_geq(&flags[F_TILE], b, a)) break;         // column tile b is in its buffer
-            double* Lf = buf0 + (b & 1) * 16 * LDL;
-            double x[SR];
-#pragma unroll
-            for (int s = 0; s < SR; ++s) x[s] = Lf[(lq + 16 * s) + lj * LDL];
-            bool ok = true;
-            auto leaf = [&](auto bc) {
-                constexpr int B = decltype(bc)::value;
-                constexpr int S0 = PAIR ? 0 : B;        // live slots [S0, S1)
-                constexpr int S1 = TT ? B + 1 : SR;
-                constexpr int NL = S1 - S0;
-                for (int c = 0; c < 16 && ok; ++c) {
-                    double* vb = vring + c * NB;
-                    if (lj == c) {
-                        auto tail = [&](int s) {
-                            if (!PAIR) return s > B || lq > c;
-                            if (TT) return s < B || lq <= c;
-                            return true;
-                        };
-                        constexpr int NQ = NL < 4 ? NL : 4;
-                        double q[NQ], al = 0.0;
-#pragma unroll
-                        for (int k = 0; k < NQ; ++k) q[k] = 0.0;
-#pragma unroll
-                        for (int k = 0; k < NL; ++k) {
-                            const int s = S0 + k;
-                            if (tail(s)) q[k % NQ] = fma(x[s], x[s], q[k % NQ]);
-                        }
-                        if (!PAIR && lq == c) al = x[B];
-#pragma unroll
-                        for (int h = 1; h < NQ; h *= 2)
-#pragma unroll
-                            for (int k = 0; k + h < NQ; k += 2 * h) q[k] += q[k + h];
-                        if (PAIR && lq == c) al = r1;
-                        const double ss = sum16(q[0]);
-                        al = readlane64(al, 16 * (c & 3) + c);
-                        double tau = 0.0, beta = al, scale = 0.0;
-                        if (ss != 0.0) {
-                            const double nrm = refined_sqrt(fma(al, al, ss));
-                            beta = al >= 0.0 ? -nrm : nrm;
-                            const double d = al - beta;
-                            const double inv = refined_rcp(beta * d);
-                            tau = -(d * d) * inv;
-                            scale = beta * inv;
-                        }
-#pragma unroll
-                        for (int k = 0; k < NL; ++k) {
-                            const int s = S0 + k;
-                            double vv;
-                            if (!PAIR && s == B) {
-                                const bool t = lq > c, dg = lq == c;
-                                if (t) x[s] *= scale;
-                                if (dg) x[s] = beta;
-                                vv = t ? x[s] : (dg ? 1.0 : 0.0);
-                            } else if (TT && s == B) {
-                                const bool t = lq <= c;
-                                if (t) x[s] *= scale;
-                                vv = t ? x[s] : 0.0;
-                            } else {
-                                x[s] *= scale;
-                                vv = x[s];
-                            }
-                            vb[lq + 16 * s] = vv;
-                        }
-                        if (PAIR && lq == c) r1 = beta;
-                        if (lq == 0) taus[c] = tau;
-                    }
-                    if (w == (c >> 2)) post(&flags[F_COL]);            // the owner wave
-                    if (!wait_geq(&flags[F_COL], 16 * b + c + 1, a)) { ok = false; break; }
-                    if (lj != c) {
-                        const double tc = taus[c];
-                        double vv[SR];
-#pragma unroll
-                        for (int k = 0; k < NL; ++k) vv[S0 + k] = vb[lq + 16 * (S0 + k)];
-                        double dp[2] = {0.0, 0.0};
-#pragma unroll
-                        for (int k = 0; k < NL; ++k) dp[k & 1] = fma(vv[S0 + k], x[S0 + k], dp[k & 1]);
-                        double d = dp[0] + dp[1];
-                        if (PAIR && lj > c && lq == c) d += r1;     // e_c meets row c of R1
-                        d = sum16(d);
-                        if (lj > c) {
-                            const double wv = tc * d;
-#pragma unroll
-                            for (int k = 0; k < NL; ++k) x[S0 + k] -= wv * vv[S0 + k];
-                            if (PAIR && lq == c) r1 -= wv;
-                        } else if (lq == 0) {
-                            Gs[lj + 16 * c] = d;            // u_lj . u_c
-                        }
-                    }
+                    for (int e = 4 * CH * k; e < 4 * CH * (k + 1); e += 8) update_dot8<C>(x + e, coef, acc);
                 }
-            };
-            switch (b) {
-#define BB_LEAF_CASE(K) case K: leaf(std::integral_constant<int, K>{}); break;
-                BB_LEAF_CASE(0) BB_LEAF_CASE(1) BB_LEAF_CASE(2) BB_LEAF_CASE(3)
-                BB_LEAF_CASE(4) BB_LEAF_CASE(5) BB_LEAF_CASE(6) BB_LEAF_CASE(7)
-                BB_LEAF_CASE(8) BB_LEAF_CASE(9) BB_LEAF_CASE(10) BB_LEAF_CASE(11)
-                BB_LEAF_CASE(12) BB_LEAF_CASE(13) BB_LEAF_CASE(14)
-                default: leaf(std::integral_constant<int, 15>{}); break;
-#undef BB_LEAF_CASE
-            }
-            if (!ok) break;
-            // R1's next diagonal entry: no block before b + 1 changes it
-            double r1n = 0.0;
-            if (PAIR && b + 1 < MT) r1n = T1.get(16 * (b + 1) + lq, 16 * (b + 1) + lj);
-            const int col = 16 * b + lj;
-#pragma unroll
-            for (int s = 0; s < SR; ++s) {
-                const int row = lq + 16 * s;
-                double vv;
-                if (PAIR) vv = (TT && row > col) ? 0.0 : x[s];
-                else vv = row > col ? x[s] : (row == col ? 1.0 : 0.0);
-                Lf[row + lj * LDL] = vv;
-                gstore<CO>(gV + row + (int64_t)col * NB, vv);
-                TX.put<CO>(row, col, PAIR ? 0.0 : (row <= col ? x[s] : 0.0));
-            }
-            if (PAIR) T1.put<CO>(16 * b + lq, 16 * b + lj, r1);
-            r1 = r1n;
-            post(&flags[F_LEAF]);                                   // U_b, taus, G complete
         }
-    } else {
-        // ---- tile role -------------------------------------------------
-        // Tile J belongs to wave 4 + J % 4 for the whole panel, which applies
-        // Q_b^T to it alone (W = R1 + U_b^T X over all rows, W = T_b^T W,
-        // X -= U_b W): no partial sums between waves.  Only the row tiles a
-        // block changes are loaded, updated and stored (all of them for TS;
-        // those at or below block b for GEQRT, at or above it in TTQRT's
-        // triangle), except for tile b + 1, which its owner hands to the next
-        // leaf whole, through LDS.  Between blocks the tiles wait in the
-        // panel's scratch (this workgroup's alone, each lane's values side by
-        // side, whole-line stores); a row tile comes from the matrix the first
-        // time a block changes it or the leaf needs it.  The next tile is
-        // loaded as soon as the current one is stored.
-        const int u = w - 4;
-        const int ti = lj - 16;             // this thread's row of T_b (and l = lq)
-        bool ok = true;
-        double* scr = a.pscratch + (int64_t)blockIdx.x * panel_scratch_doubles(NB) + 4 * lane;
-        auto scr_at = [&](int J, int i) { return scr + (J * MT + i) * 256; };
-        auto active = [&](int i, int bb) { return PAIR ? (!TT || i <= bb) : i >= bb; };
-        // block in which row tile i is first changed
-        auto first = [&](int i) { return TT ? i : 0; };
-        d4 x[MT], R1b = {0.0, 0.0, 0.0, 0.0};
-        // tile J as block bb needs it
-        auto fetch = [&](int J, int bb) {
-            const bool whole = J == bb + 1;
-            if (PAIR) R1b = load16(T1, 16 * bb, 16 * J);
+        // hand over G(:, c) and tau_c; LDS writes of a wave complete in order
+        gram.G[16 * C + j] = sc * h;
+        gram.tau[C] = tau;
+        asm volatile("" ::: "memory");
+        __hip_atomic_store(gram.done, done0 + C + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        asm volatile("" ::: "memory");
+        D[C + 17 * j] = j == C ? bt : fma(-tj, h, a);
+        sc = j == C ? scale : sc;
+        a = an;
+        asm volatile("" : "+v"(sc));                    // (formed here, not where it is used)
+    });
+}
+
+// Forms T_b beside the leaf of block b, one column behind it, by the forward
+// recurrence T(c,c) = tau_c, T(0:c-1,c) = -tau_c T(0:c-1,0:c-1) G(0:c-1,c):
+// lane j (of each row of 16) holds row j of T.  Writes T(i, l) to Tb[l + 16 i].
+// The leaf waits for nothing, so neither wait here can last.
+__device__ __forceinline__ void form_t(const GramLds& gram, int done0, double* Tb) {
+    const int lane = threadIdx.x & 63, j = lane & 15;
+    double t[16];
 #pragma unroll
-            for (int i = 0; i < MT; ++i) {
-                if (!whole && !active(i, bb)) continue;
-                if (bb > first(i)) x[i] = load_d4(scr_at(J, i));
-                else x[i] = load16(TX, 16 * i, 16 * J);
-            }
-        };
-        // this wave's first tile after block bb (MT if none)
-        auto next_tile = [&](int bb) { return bb + 1 + ((u - (bb + 1)) % 4 + 4) % 4; };
-        int Jn = next_tile(0);
-        if (Jn < MT) fetch(Jn, 0);
-        for (int b = 0; b < MT && ok; ++b) {
-            if (!wait_geq(&flags[F_LEAF], 4 * (b + 1), a)) break;
-            const double* U = buf0 + (b & 1) * 16 * LDL;
-            double* TbT = TbT0 + (b & 1) * 256;
-            // T_b by the forward recurrence (each 16-lane row of T on its
-            // own), from G and tau read once
-            double gcol[16], tcol[16];
+    for (int l = 0; l < 16; ++l) t[l] = 0.0;
+    for_constants<16>([&](auto cc) {
+        constexpr int C = decltype(cc)::value;
+        while (__builtin_amdgcn_readfirstlane(__hip_atomic_load(
+                   gram.done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) < done0 + C + 1)
+            __builtin_amdgcn_s_sleep(1);
+        asm volatile("" ::: "memory");
+        const double gc = gram.G[16 * C + j], tau = gram.tau[C];
+        double s[2] = {0.0, 0.0};
+        // (entries of t not formed yet are zero)
+        for_constants<(C + 3) / 4>([&](auto lc) {
+            constexpr int L = 4 * decltype(lc)::value;
+            row_dot4<L>(gc, t + L, s);
+        });
+        t[C] = j < C ? -tau * (s[0] + s[1]) : (j == C ? tau : 0.0);
+    });
+    if (lane < 16) {
 #pragma unroll
-            for (int cc = 0; cc < 16; ++cc) {
-                gcol[cc] = Gs[lq + 16 * cc];
-                tcol[cc] = taus[cc];
-            }
-            double til = 0.0;
+        for (int l = 0; l < 16; ++l) Tb[l + 16 * j] = t[l];
+    }
+}
+
+// Matrix results must not be read by a vector instruction within 19 issue
+// slots of the MFMA that writes them; the compiler keeps that distance for
+// its own instructions but does not look into the leaf's assembly, which x
+// reaches here.
+template <int N>
+__device__ __forceinline__ void settle(double (&x)[N]) {
 #pragma unroll
-            for (int cc = 0; cc < 16; ++cc) {
-                const double sm = sum16((lq >= ti && lq < cc) ? til * gcol[cc] : 0.0);
-                const double tic = cc < ti ? 0.0 : (cc == ti ? tcol[cc] : -tcol[cc] * sm);
-                if (lq == cc) til = tic;
-            }
-            TbT[lq + 16 * ti] = til;
-            gstore<CO>(gTt + 256 * b + (tid - 256), til);
-            post(&flags[F_TB]);
-            if (!wait_geq(&flags[F_TB], 4 * (b + 1), a)) break;
+    for (int e = 0; e < N; e += 8)
+        asm volatile("" : "+v"(x[e]), "+v"(x[e + 1]), "+v"(x[e + 2]), "+v"(x[e + 3]), "+v"(x[e + 4]),
+                          "+v"(x[e + 5]), "+v"(x[e + 6]), "+v"(x[e + 7]));
+    asm volatile("s_nop 15\n\ts_nop 7");
+}
+
+// A block U_b in LDS: element (16 i + 4 g + r, c) at 336 i + 84 g + 4 c + r.  A
+// lane's four values of a row tile lie together (16-byte accesses for the
+// leaf's output and for U^T X), and the rows of a column, which the record
+// and U W read, spread over the banks.  T_b (T(i, l) at l + 16 i) follows.
+constexpr int U_TILE = 336, U_G = 84;
+__device__ __forceinline__ int u_at(int row, int col) {
+    return U_TILE * (row >> 4) + U_G * ((row >> 2) & 3) + 4 * col + (row & 3);
+}
+
+// Panel of any kind (pair: TS or TT, tt: TT) and tile size.  For nb <= 128
+// every column tile has its wave.  A 256-wide tile takes two rounds of eight
+// column tiles (a 256 x 16 tile is half of a wave's registers): in the second,
+// the first round's blocks are staged from the record just written, as an
+// update does, and applied first.
+//
+// A wave's work is one sequence: it applies the blocks left of its column
+// tile, factors the tile, and then only takes its share of the outputs.
+// Barrier b of a round follows leaf b, so a block's LDS buffer is rewritten
+// (two blocks later) only after every wave has finished with it.
+//
+// What bounds it: the chain of leaves (leaf_columns) and of the next column
+// tile's applications between them.  Leaves shared by four waves, one column
+// after the other through LDS and a barrier (or a counter), took 2000 cycles
+// a column at nb = 128; one wave alone takes 600 to 800, and the other waves
+// are free for the applications and the outputs.  Unit times in a lightly
+// loaded run, before and after: nb = 32 TTQRT 17 -> 12 us, nb = 64 TSQRT
+// 39 -> 27 us, nb = 128 GEQRT 86 -> 74 and TTQRT 90 -> 65 us, nb = 256 (its
+// trailing tiles used to wait in scratch memory between blocks) GEQRT
+// 390 -> 330 us.
+template <int NB, bool CO>
+__device__ __forceinline__ void panel(const KArgs& a, const DevTask& tk, double* lds, Prev& prev) {
+    using S = Shape<NB>;
+    constexpr int MT = S::MT, BUF = S::UBUF, NW = NT / 64;
+    constexpr int HT = MT < NW ? MT : NW, NH = MT / HT; // column tiles per round, rounds
+    constexpr int CH = MT < 4 ? MT : 4;
+    const bool pair = tk.kind != K_GEQRT, tt = tk.kind == K_TTQRT;
+    const int tid = here(threadIdx.x), lane = tid & 63, j = lane & 15, g = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool own = HT == NW || w < HT;
+
+    const MatDesc md = mat_desc(a, tk.mat);
+    const TileView T1 = view(md, tk, tk.r1, tk.c1, NB);
+    const TileView TX = pair ? view(md, tk, tk.r2, tk.c2, NB) : T1;
+    double* gV = record<NB>(md, tk);
+    double* gTt = gV + NB * NB;
+    double* Ds = lds + 2 * BUF + 272 * (w % HT);        // the wave's diagonal block, column stride 17
+    double* gl = lds + 2 * BUF + 272 * HT;
+    const GramLds gram{gl, gl + 256, (int*)(gl + 272)};
+    if (tid == 0) *gram.done = 0;                       // (barriers follow before the first leaf)
+    lds_barrier();
 
 #pragma unroll 1
-            for (int J = Jn; J < MT; J += 4) {
-                asm volatile("" ::: "memory");
-                const bool whole = J == b + 1;
-                d4 Wk[2] = {R1b, {0.0, 0.0, 0.0, 0.0}};
+    for (int h = 0; h < NH; ++h) {
+        const int ct = HT * h + w;                      // this wave's column tile
+        TileLane l1(T1, 16 * ct, NB), lx(TX, 16 * ct, NB);
+        d4 x[MT], R1n = {0.0, 0.0, 0.0, 0.0};
+        if (own) load_slice<MT>(lx, x);
+        // R1's rows are changed by the block of the same index only: the
+        // diagonal block is read here, the others one block ahead.
+        if (pair && own) {
+            const d4 r = l1.load(16 * ct);
+            if (ct > 0) R1n = l1.load(0);
 #pragma unroll
-                for (int i = 0; i < MT; ++i) {
-                    if (!active(i, b)) continue;
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        Wk[i & 1] = mfma(U[(16 * i + 4 * r + g) + j * LDL], x[i][r], Wk[i & 1]);
-                }
-                const d4 W = Wk[0] + Wk[1];
-                d4 W2 = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                for (int r = 0; r < 4; ++r) W2 = mfma(TbT[j + 16 * (4 * r + g)], W[r], W2);
-                if (PAIR) store16<CO>(T1, 16 * b, 16 * J, R1b - W2);
-#pragma unroll
-                for (int i = 0; i < MT; ++i) {
-                    if (!active(i, b)) continue;
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        x[i] = mfma(-U[(16 * i + j) + (4 * r + g) * LDL], W2[r], x[i]);
-                }
-                if (whole) {
-                    double* Ln = buf0 + ((b + 1) & 1) * 16 * LDL;
-#pragma unroll
-                    for (int i = 0; i < MT; ++i)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) Ln[(16 * i + 4 * r + g) + j * LDL] = x[i][r];
-                    post(&flags[F_TILE]);                           // the next leaf may start
-                } else {
-#pragma unroll
-                    for (int i = 0; i < MT; ++i)
-                        if (active(i, b)) store_d4(scr_at(J, i), x[i]);
-                }
-                // the next tile: this block's, else the next block's first
-                const int Jnext = J + 4 < MT ? J + 4 : next_tile(b + 1);
-                if (Jnext < MT) fetch(Jnext, J + 4 < MT ? b : b + 1);
+            for (int k = 0; k < 4; ++k) Ds[(4 * g + k) + 17 * j] = 4 * g + k <= j ? r[k] : 0.0;
+        }
+        // Zeros below R (GEQRT) or in all of X2 (TS; TT: its triangle).
+        auto clear = [&]() {
+            const int r0 = pair ? 0 : 16 * (ct + 1), r1 = min(tt ? 16 * (ct + 1) : NB, TX.vr);
+            if (TX.rs == 1) {
+                // columns are contiguous: whole lines along them (the slice
+                // layout would write 16 bytes of each line at a time)
+                const int c1 = min(16, TX.vc - 16 * ct), ln = here(lane);
+#pragma unroll 1
+                for (int c = 0; c < c1; ++c)
+#pragma unroll 1
+                    for (int row = r0 + ln; row < r1; row += 64)
+                        gstore<CO>(TX.base + row + (16 * ct + c) * TX.cs, 0.0);
+            } else {
+                const d4 zero = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+                for (int i = r0; i < r1; i += 16) lx.store<CO>(i, zero);
             }
-            Jn = next_tile(b + 1);      // fetched above, after the block's last tile
+        };
+
+        // Q_cb^T on this wave's tile, the block at U: W = R1 + U^T X,
+        // W = T^T W, X -= U W, on the rows U can change.  Row tiles go in
+        // pairs with a sum each, so that consecutive MFMAs are independent.
+        auto apply = [&](int cb, const double* U, auto ahead) {
+            constexpr bool AHEAD = decltype(ahead)::value;
+            const double* Tb = U + MT * U_TILE;
+            const int ln = here(lane), j = ln & 15, g = ln >> 4, pj = perm16(j);
+            l1.renew();
+            lx.renew();
+            const d4 R1b = R1n;
+            if (pair && cb + 1 < ct) R1n = l1.load(16 * (cb + 1));
+            const int plo = pair ? 0 : cb / 2, phi = tt ? cb / 2 + 1 : MT / 2;
+            const double* uw = U + U_G * g + 4 * pj;
+            d4 Wk[2] = {R1b, {0.0, 0.0, 0.0, 0.0}};
+            // AHEAD: operands of the next pair are read while this one's run
+            d2 u[2][2][2];
+            auto read_w = [&](int p) {
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+#pragma unroll
+                    for (int q = 0; q < 2; ++q)
+                        u[p & 1][k][q] = *(const d2*)(uw + U_TILE * (2 * p + k) + 2 * q);
+            };
+            if (AHEAD) read_w(0);
+#pragma unroll
+            for (int p = 0; p < MT / 2; ++p) {
+                if (AHEAD && p + 1 < MT / 2) read_w(p + 1);
+                if (p >= plo && p < phi) {
+                    if (!AHEAD) read_w(p);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+#pragma unroll
+                        for (int k = 0; k < 2; ++k) Wk[k] = mfma(u[p & 1][k][r / 2][r % 2], x[2 * p + k][r], Wk[k]);
+                }
+                SCHED_FENCE();
+            }
+            const double* ux = U + U_G * (j & 3) + 16 * g + (j >> 2);
+            auto read_x = [&](int p) {
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) u[p & 1][k][r / 2][r % 2] = ux[U_TILE * (2 * p + k) + 4 * r];
+            };
+            double tb[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) tb[r] = -Tb[pj + 16 * (4 * g + r)];
+            if (AHEAD) read_x(0);
+            const d4 W = Wk[0] + Wk[1];
+            d4 W2 = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int r = 0; r < 4; ++r) W2 = mfma(tb[r], W[r], W2);
+            if (pair) l1.store<CO>(16 * cb, R1b + W2);
+#pragma unroll
+            for (int p = 0; p < MT / 2; ++p) {
+                if (AHEAD && p + 1 < MT / 2) read_x(p + 1);
+                if (p >= plo && p < phi) {
+                    if (!AHEAD) read_x(p);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+#pragma unroll
+                        for (int k = 0; k < 2; ++k)
+                            x[2 * p + k] = mfma(u[p & 1][k][r / 2][r % 2], W2[r], x[2 * p + k]);
+                }
+                SCHED_FENCE();
+            }
+            if (!pair) {                                // row tile cb is final: rows of R
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+                    if (i == cb) {
+                        lx.store<CO>(16 * i, x[i]);
+                        x[i] = d4{0.0, 0.0, 0.0, 0.0};
+                    }
+            }
+        };
+        // A wave's share of block b's record, the idle waves' in turn.
+        auto write_record = [&](int b) {
+            const double* U = lds + (b & 1) * BUF;
+            const int cb = HT * h + b, n = b + 1 + (NW - HT), k0 = w <= b ? w : w - HT + b + 1;
+            const int ln = here(lane);
+#pragma unroll 1
+            for (int k = k0; k < NB / 4; k += n) {
+                const int e = ln + 64 * k;
+                gstore<CO>(gV + (int64_t)cb * 16 * NB + e, U[u_at(e % NB, e / NB)]);
+            }
+            if (w == b) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    gstore<CO>(gTt + 256 * cb + 64 * k + ln, U[MT * U_TILE + 64 * k + ln]);
+            }
+        };
+        // Before barrier b: the wave two after the leaf's (on another SIMD)
+        // forms T_b.
+        auto meet = [&](int b) {
+            if (w == ((b + 2) & (NW - 1))) form_t(gram, 16 * (HT * h + b), lds + (b & 1) * BUF + MT * U_TILE);
+            lds_barrier();
+        };
+
+        if (h == 0) {
+            retire(a, prev);
+        } else {
+            // the record's first half: every wave's stores done, then stale
+            // lines dropped as at the start of a unit
+            __builtin_amdgcn_s_waitcnt(0);
+            lds_barrier();
+            asm volatile("buffer_inv sc1" ::: "memory");
+            const Rec rec(gV, NB);
+            constexpr int PRE = 16 * NB / NT;
+            double pre[PRE], pt = 0.0;
+            const int tid = here(threadIdx.x);
+            auto fetch = [&](int cb) {
+#pragma unroll
+                for (int k = 0; k < PRE; ++k) pre[k] = rec.ld(8 * (tid + NT * k), 8 * 16 * NB * cb);
+                if (tid < 256) pt = rec.ld(8 * tid, 8 * (NB * NB + 256 * cb));
+            };
+            fetch(0);
+#pragma unroll 1
+            for (int cb = 0; cb < HT; ++cb) {
+                double* U = lds + (cb & 1) * BUF;
+#pragma unroll
+                for (int k = 0; k < PRE; ++k) {
+                    const int e = tid + NT * k;
+                    U[u_at(e % NB, e / NB)] = pre[k];
+                }
+                if (tid < 256) U[MT * U_TILE + tid] = pt;
+                if (cb + 1 < HT) fetch(cb + 1);
+                lds_barrier();
+                // (two waves a SIMD hide each other's operand reads, and the
+                // fetched block takes the registers)
+                apply(cb, U, std::false_type{});
+            }
+            lds_barrier();
+        }
+        // the tile is in registers: its zeros are stored while the first leaf
+        // runs (by wave 0 after its own)
+        if (own && w > 0) {
+            __builtin_amdgcn_s_waitcnt(0);
+            asm volatile("" ::: "memory");
+            clear();
+        }
+
+#pragma unroll 1
+        for (int b = 0; b < HT && b < w; ++b) {
+            if (b + 1 == w) __builtin_amdgcn_s_setprio(3);      // the next leaf
+            meet(b);
+            if (own) apply(HT * h + b, lds + (b & 1) * BUF, std::true_type{});
+            else write_record(b);
+        }
+        if (!own) continue;
+
+        double xs[4 * MT], xd[4] = {0.0, 0.0, 0.0, 0.0}, sc;
+        if (!pair) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+                if (i == ct) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) xd[r] = x[i][r];
+                    x[i] = d4{0.0, 0.0, 0.0, 0.0};
+                }
+        }
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) xs[4 * i + r] = x[i][r];
+        asm volatile("" : "+v"(xd[0]), "+v"(xd[1]), "+v"(xd[2]), "+v"(xd[3]));
+        settle(xs);
+        leaf_columns<MT>(xs, xd, Ds, sc, pair, pair ? 0 : (ct + 1) / CH, tt ? ct / CH + 1 : MT / CH, gram, 16 * ct);
+
+        double* U = lds + (w & 1) * BUF;
+        const int ln = here(lane), j = ln & 15, g = ln >> 4;
+        d4 dt;                                          // the diagonal block in the tile layout
+#pragma unroll
+        for (int r = 0; r < 4; ++r) dt[r] = Ds[(4 * g + r) + 17 * j];
+        double* uw = U + U_G * g + 4 * j;
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+            *(d2*)(uw + U_TILE * i) = d2{xs[4 * i] * sc, xs[4 * i + 1] * sc};
+            *(d2*)(uw + U_TILE * i + 2) = d2{xs[4 * i + 2] * sc, xs[4 * i + 3] * sc};
+        }
+        if (!pair) {                                    // explicit unit lower triangle
+            double v[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int row = 4 * g + r;
+                v[r] = row > j ? dt[r] * sc : (row == j ? 1.0 : 0.0);
+            }
+            *(d2*)(uw + U_TILE * ct) = d2{v[0], v[1]};
+            *(d2*)(uw + U_TILE * ct + 2) = d2{v[2], v[3]};
+        }
+        lds_barrier();
+        __builtin_amdgcn_s_setprio(0);
+        l1.renew();
+        lx.renew();
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            if (4 * g + r > j) dt[r] = 0.0;
+        l1.store<CO>(16 * ct, dt);                   // R (GEQRT) or R1's diagonal block
+        write_record(w);
+        if (w == 0) clear();
+#pragma unroll 1
+        for (int b = w + 1; b < HT; ++b) {
+            meet(b);
+            write_record(b);
         }
     }
     lds_barrier();
-}
-
-template <int NB, int KIND, bool CO>
-__device__ __forceinline__ void panel(const KArgs& a, const DevTask& tk, double* lds, Prev& prev) {
-    if constexpr (NB <= 128) panel_resident<NB, KIND, CO>(a, tk, lds, prev);
-    else panel_split<NB, KIND, CO>(a, tk, lds, prev);
 }
 
 // ---------------------------------------------------------------------------
@@ -1120,7 +1068,7 @@ __device__ __forceinline__ void update(const KArgs& a, const DevTask& tk, int pa
     constexpr int MT = NB / 16;
     constexpr int NS = NB < 128 ? NB : 128;  // strip width: one 16-column slice per wave
     constexpr bool HASC1 = KIND != K_UNMQR;
-    const int tid = threadIdx.x, w = tid >> 6;
+    const int tid = here(threadIdx.x), w = tid >> 6;
     const int c0 = part * NS + 16 * w;
     const MatDesc md = mat_desc(a, tk.mat);
     const TileView T2 = view(md, tk, tk.r2, tk.c2, NB);
@@ -1129,11 +1077,13 @@ __device__ __forceinline__ void update(const KArgs& a, const DevTask& tk, int pa
     const bool active = 16 * w < NS && c0 < T2.vc;
     const Rec rec(record<NB>(md, tk), NB);
 
+    TileLane l1(T1, c0, NB), l2(T2, c0, NB);
     d4 c2[MT];
-    if (active) load_slice<MT>(T2, c0, c2);
-    apply_blocks<NB, MT, KIND, CO, HQ>(rec, T1, c0, active, &c2[0], lds, a, prev);
+    if (active) load_slice<MT>(l2, c2);
+    apply_blocks<NB, MT, KIND, CO, HQ>(rec, l1, active, &c2[0], lds, a, prev);
     if (sch != nullptr) take_next(a, sch);
-    if (active) store_slice<CO, MT>(T2, c0, c2);
+    l2.renew();
+    if (active) store_slice<CO, MT>(l2, c2);
 }
 
 // ---------------------------------------------------------------------------
@@ -1146,47 +1096,14 @@ __device__ __forceinline__ void update(const KArgs& a, const DevTask& tk, int pa
 // FP64 in either case.
 //
 // The FP32 instruction returns element r of lane l at row 4(l/16) + r (the
-// FP64 one at row 4r + l/16).  Slices are therefore held in that layout, and
-// the k-step r of a 16-row block takes the rows {4g + r : g = 0..3}: lane l
-// supplies row 4(l/16) + r of its column, which is its own element r.
+// FP64 one at row 4r + l/16), which is the slices' layout as it is: no row is
+// permuted, and the k-step r of a 16-row block takes the rows
+// {4g + r : g = 0..3}, of which lane l holds its own element r.
 // ---------------------------------------------------------------------------
 typedef float f4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ f4 mfma32(float a, float b, f4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
-template <int MT>
-__device__ __forceinline__ void load_slice_r4(const TileView& t, int c0, d4 (&x)[MT]) {
-    const int lane = threadIdx.x & 63, j = lane & 15, g = lane >> 4;
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) x[i][r] = t.get(16 * i + 4 * g + r, c0 + j);
-}
-
-template <bool CO, int MT>
-__device__ __forceinline__ void store_slice_r4(const TileView& t, int c0, const d4 (&x)[MT]) {
-    const int lane = threadIdx.x & 63, j = lane & 15, g = lane >> 4;
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) t.put<CO>(16 * i + 4 * g + r, c0 + j, x[i][r]);
-}
-
-__device__ __forceinline__ d4 load16_r4(const TileView& t, int r0, int c0) {
-    const int lane = threadIdx.x & 63, j = lane & 15, g = lane >> 4;
-    d4 x;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) x[r] = t.get(r0 + 4 * g + r, c0 + j);
-    return x;
-}
-
-template <bool CO>
-__device__ __forceinline__ void store16_r4(const TileView& t, int r0, int c0, d4 x) {
-    const int lane = threadIdx.x & 63, j = lane & 15, g = lane >> 4;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) t.put<CO>(r0 + 4 * g + r, c0 + j, x[r]);
 }
 
 __device__ __forceinline__ float lo32(double x, float hi) { return (float)(x - (double)hi); }
@@ -1201,7 +1118,7 @@ __device__ __forceinline__ void update32(const KArgs& a, const DevTask& tk, int 
     constexpr int BUF = (SPLIT ? 2 : 1) * PL; // hi plane [, lo plane]
     constexpr int PRE = 16 * NB / NT + 1;
     constexpr bool HASC1 = KIND != K_UNMQR;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, j = lane & 15, g = lane >> 4;
+    const int tid = here(threadIdx.x), lane = tid & 63, w = tid >> 6, j = lane & 15, g = lane >> 4;
     const int c0 = part * NS + 16 * w;
     const MatDesc md = mat_desc(a, tk.mat);
     const TileView T2 = view(md, tk, tk.r2, tk.c2, NB);
@@ -1244,13 +1161,14 @@ __device__ __forceinline__ void update32(const KArgs& a, const DevTask& tk, int 
     };
 
     d4 c2[MT];
-    if (active) load_slice_r4<MT>(T2, c0, c2);
+    TileLane l1(T1, c0, NB), l2(T2, c0, NB);
+    if (active) load_slice<MT>(l2, c2);
     double pre[PRE];
     fetch(0, pre);
     retire(a, prev);
     stage(0, pre);
     d4 C1n = {0.0, 0.0, 0.0, 0.0};
-    if (HASC1 && active) C1n = load16_r4(T1, 0, c0);
+    if (HASC1 && active) C1n = l1.load(0);
     lds_barrier();
 #pragma unroll
     for (int b = 0; b < MT; ++b) {
@@ -1260,7 +1178,7 @@ __device__ __forceinline__ void update32(const KArgs& a, const DevTask& tk, int 
         const float* Tl = Vl + 16 * LDV;
         if (b + 1 < MT) fetch(b + 1, pre);
         const d4 C1b = C1n;
-        if (HASC1 && active && b + 1 < MT) C1n = load16_r4(T1, 16 * (b + 1), c0);
+        if (HASC1 && active && b + 1 < MT) C1n = l1.load(16 * (b + 1));
         if (active) {
             // W = C1_b + V_b^T C2, FP64 across 16-row chunks.
             d4 W = C1b;
@@ -1287,7 +1205,7 @@ __device__ __forceinline__ void update32(const KArgs& a, const DevTask& tk, int 
             d4 W2;
 #pragma unroll
             for (int r = 0; r < 4; ++r) W2[r] = (double)w2[r];
-            if (HASC1) store16_r4<CO>(T1, 16 * b, c0, C1b - W2);
+            if (HASC1) l1.store<CO>(16 * b, C1b - W2);
             // C2 -= V_b W2
 #pragma unroll
             for (int i = 0; i < MT; ++i) {
@@ -1307,7 +1225,8 @@ __device__ __forceinline__ void update32(const KArgs& a, const DevTask& tk, int 
         lds_barrier();
     }
     if (sch != nullptr) take_next(a, sch);
-    if (active) store_slice_r4<CO, MT>(T2, c0, c2);
+    l2.renew();
+    if (active) store_slice<CO, MT>(l2, c2);
 }
 
 // PREC: 0 = FP64 updates, 2 = FP32-MFMA updates, 3 = split-FP32 updates
@@ -1329,9 +1248,9 @@ __device__ __forceinline__ void run_unit(const KArgs& a, int task, int part, dou
         }
     } else {
         switch (tk.kind) {
-        case K_GEQRT: panel<NB, K_GEQRT, CO>(a, tk, lds, prev); break;
-        case K_TSQRT: panel<NB, K_TSQRT, CO>(a, tk, lds, prev); break;
-        case K_TTQRT: panel<NB, K_TTQRT, CO>(a, tk, lds, prev); break;
+        case K_GEQRT:
+        case K_TSQRT:
+        case K_TTQRT: panel<NB, CO>(a, tk, lds, prev); break;
         case K_UNMQR:
             if (PREC == 0) update<NB, K_UNMQR, CO, false>(a, tk, part, lds, prev, sch);
             else update32<NB, K_UNMQR, CO, PREC == 3>(a, tk, part, lds, prev, sch);
@@ -1377,7 +1296,7 @@ constexpr int kernel_lds() { return NB == NB_MIXED ? Shape<128>::LDS : Shape<NB>
 // One launch per topological level: block b runs unit unit_base + b.
 template <int NB, int PREC>
 __global__ __launch_bounds__(NT) void level_kernel(KArgs a, int32_t unit_base) {
-    __shared__ double lds[kernel_lds<NB>()];
+    __shared__ alignas(16) double lds[kernel_lds<NB>()];
     const int2 u = a.units[unit_base + blockIdx.x];
     Prev none{-1, 0, 0, 0, 0};
     run_any<NB, false, PREC>(a, u.x, u.y, lds, none, nullptr);
@@ -1399,7 +1318,7 @@ __global__ __launch_bounds__(NT) void level_kernel(KArgs a, int32_t unit_base) {
 
 template <int NB, int PREC>
 __global__ __launch_bounds__(NT) void persistent_kernel(KArgs a) {
-    __shared__ double lds[kernel_lds<NB>() + SCH_WORDS / 2];
+    __shared__ alignas(16) double lds[kernel_lds<NB>() + SCH_WORDS / 2];
     int* sch = (int*)(lds + kernel_lds<NB>());
     const int tid = threadIdx.x;
     Prev prev{-1, 0, 0, 0, 0};
@@ -1514,6 +1433,11 @@ hipError_t noalloc_scratch(void** ptr, size_t* bytes) {
 
 #endif  // BB_KERNELS_COMMON
 
+// This file is compiled once per (tile size, arithmetic) pair (BB_KERNELS_NB,
+// BB_KERNELS_PREC: that pair's kernels, the translation units built in
+// parallel) and once for the size-independent part (BB_KERNELS_COMMON), which
+// sees the launchers' declarations only and so compiles no kernel twice.
+#if defined(BB_KERNELS_NB) && defined(BB_KERNELS_PREC)
 template <int NB, int PREC>
 hipError_t launch_level_np(const KArgs& a, int32_t unit_base, int32_t count, hipStream_t s) {
     hipLaunchKernelGGL((level_kernel<NB, PREC>), dim3(count), dim3(NT), 0, s, a, unit_base);
@@ -1526,10 +1450,6 @@ hipError_t launch_persistent_np(const KArgs& a, int32_t workgroups, hipStream_t 
     return hipGetLastError();
 }
 
-// This file is compiled once per (tile size, arithmetic) pair (BB_KERNELS_NB,
-// BB_KERNELS_PREC: that pair's kernels, the translation units built in
-// parallel) and once for the size-independent part (BB_KERNELS_COMMON).
-#if defined(BB_KERNELS_NB) && defined(BB_KERNELS_PREC)
 template hipError_t launch_level_np<BB_KERNELS_NB, BB_KERNELS_PREC>(const KArgs&, int32_t, int32_t, hipStream_t);
 template hipError_t launch_persistent_np<BB_KERNELS_NB, BB_KERNELS_PREC>(const KArgs&, int32_t, hipStream_t);
 #endif
