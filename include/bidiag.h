@@ -438,13 +438,14 @@ int bb_choose(int64_t m, int64_t n, int nb, const bb_opts* opts, int* tree, int*
  * bidiagonal form U^T B V (U, V orthogonal, V e1 = e1, neither formed) by
  * two-sided Householder bulge chasing, one row per sweep, the sweeps
  * pipelined over the GPU in one persistent launch (for nb > 64 each sweep
- * is run by a group of workgroups).  Writes the diagonal
+ * is run by a group of workgroups that hold its rows in slices).  Writes the diagonal
  * d[0..n-1] and the superdiagonal e[0..n-2] (device).  The diagonal and
  * superdiagonal are those of the Golub-Kahan bidiagonalization of B started
  * at e1, so they are unique up to signs.
  * ws: device workspace of bb_bnd2bd_workspace bytes (control words, the band
- * with room for the fill, 24 nb n bytes, and a progress counter and a
- * group-barrier counter per sweep), overwritten.  watchdog_s: seconds a sweep may wait for the one
+ * with room for the fill, 24 nb n bytes, a progress counter per sweep and
+ * member of its group, an exchange counter per sweep and the groups' exchange
+ * areas), overwritten.  watchdog_s: seconds a sweep may wait for the one
  * before it (0 = 30); when it fires the launch stops and bb_poll_error(ws)
  * reports BB_ETIMEOUT.  Arguments: B (1), ldb >= max(1, n) (2), n >= 0 (3),
  * 1 <= nb <= 256 (4), d (5), e (6), ws (7), ws_bytes (8, BB_EWORKSPACE when
@@ -453,10 +454,10 @@ int bb_choose(int64_t m, int64_t n, int nb, const bb_opts* opts, int* tree, int*
 int bb_bnd2bd_workspace(int64_t n, int nb, size_t* ws_bytes);
 int bb_bnd2bd(const double* B, int64_t ldb, int64_t n, int nb, double* d, double* e, void* ws,
               size_t ws_bytes, double watchdog_s, void* stream);
-/* bb_bnd2bd_group -- bb_bnd2bd with the number of workgroups that run each
- * sweep for nb > 64 given: group (10) in 1..16, 0 = ceil(nb / 16) as
- * bb_bnd2bd uses (ignored for nb <= 64, where one workgroup runs a sweep).
- * The result does not depend on it.  -10 for group out of range. */
+/* bb_bnd2bd_group -- bb_bnd2bd with a wish for the number of workgroups that
+ * run each sweep: group (10) in 0..16, -10 out of range.  The launch uses the
+ * number its slices need (1 for nb <= 64, ceil(nb / 32) for nb <= 128, else
+ * ceil(nb / 16)) whatever is asked for; the result does not depend on it. */
 int bb_bnd2bd_group(const double* B, int64_t ldb, int64_t n, int nb, double* d, double* e, void* ws,
                     size_t ws_bytes, double watchdog_s, int group, void* stream);
 

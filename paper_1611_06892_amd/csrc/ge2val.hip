@@ -15,22 +15,19 @@
 //   * a reflector from the left clears column c below the diagonal; it is
 //     applied to rows c .. c+nb-1 of columns c+1 .. c+2nb-1.
 // Only the first row or column of a bulge is cleared; the rest is cleared
-// by later sweeps.  Step t of sweep k+1 touches one entry that step t+2 of
-// sweep k also touches (row k+1+(t+1)nb, column k+1+(t+2)nb, the first
-// entry of the row that step clears) and nothing of a later step, so it may
-// start once sweep k has finished step t+1 and has written that entry's
-// final value in step t+2 (its progress counter counts half steps): about
-// two and a half steps separate consecutive sweeps, and about n / (2.5 nb)
-// sweeps run at once.
+// by later sweeps.  Step t of sweep k+1 works one row and one column further
+// down than step t of sweep k, on entries that steps t and t+1 of sweep k
+// write, so it may start once sweep k has finished step t+1: two steps
+// separate consecutive sweeps, and about n / (2 nb) sweeps run at once.
 //
-// One persistent launch: each workgroup takes the next sweep (a ticket from
-// an atomic counter, so a sweep is only ever waited for by a later one that
-// a running workgroup holds: no deadlock for any grid) and runs its steps in
-// order, each after the previous sweep's progress counter allows it.  The
+// One persistent launch: each group of workgroups takes the next sweep
+// (tickets from an atomic counter, so a sweep is only ever waited for by a
+// later one that running workgroups hold: no deadlock for any grid) and runs
+// its steps in order, each after the previous sweep's progress counters allow
+// it.  The
 // band array is written and read with agent-scope stores and loads (past the
 // XCD's L2, at the coherence point), so a counter is published once every
-// wave has waited for its own memory operations and the workgroup has met,
-// with no L2 write-back, and the loads that follow a counter's load see every
+// wave has waited for its own memory operations, with no L2 write-back, and the loads that follow a counter's load see every
 // store performed before it was written, with no L2 invalidation; a
 // wall-clock watchdog bounds every wait.
 //
@@ -53,10 +50,27 @@
 
 namespace bbg {
 
-constexpr int NT = 256;                 // threads of the chase kernel (4 waves)
+constexpr int NT = 512;                 // threads of the chase kernel (8 waves)
 constexpr int NW = NT / 64;
 constexpr int MAX_NB = 256;
+constexpr int GROUP_MAX = 16;
+constexpr int SLICE = 4096;             // entries of a member's slice of one quadrant
 enum : int { G_ERROR = 1, G_HEAD = 32, G_WORDS = 64 };
+
+// Quadrant width the kernel is compiled for (64, 128, 256), rows of a
+// member's slice and workgroups (members) per sweep.
+inline int width_of(int nb) { return nb <= 64 ? 64 : nb <= 128 ? 128 : 256; }
+inline int slice_rows(int nb) { return SLICE / width_of(nb); }
+inline int group_of(int nb) { return (nb + slice_rows(nb) - 1) / slice_rows(nb); }
+
+// Exchange areas: sweeps in progress span at most MAX_WG / group + 2 of them
+// (a sweep cannot finish before the one ahead of it, and every workgroup
+// holds one ticket), so sweep k uses area k % nareas.
+constexpr int MAX_WG = 256;
+inline int nareas_of(int group) { return MAX_WG / group + 2; }
+// doubles of one area: two steps' parity, each the members' partial column
+// products and row 0
+inline int64_t area_doubles(int nb, int group) { return 2 * (int64_t)(group + 1) * 2 * width_of(nb); }
 
 struct ChaseArgs {
     double* W;
@@ -65,18 +79,16 @@ struct ChaseArgs {
     int nb;
     int nsweeps;
     int32_t* ctrl;        // G_* words
-    int32_t* prog;        // steps finished, per sweep
-    int32_t* bar;         // group barrier arrivals, per sweep (nb > LDS_NB)
-    int group;            // workgroups per sweep (nb > LDS_NB; 1 for the LDS steps)
+    int32_t* prog;        // steps finished, per sweep and member
+    int32_t* bar;         // exchange arrivals, per sweep
+    double* xch;          // exchange areas (group > 1)
+    int group;            // workgroups per sweep
+    int nareas;
     int64_t watchdog_ticks;
 };
 
 __host__ __device__ inline int64_t nsteps(int64_t n, int nb, int64_t k) {
     return (n - 1 - k + nb - 1) / nb;
-}
-
-__device__ __forceinline__ double* at(const ChaseArgs& a, int64_t i, int64_t j) {
-    return a.W + (i - j + 2 * a.nb - 1) + j * a.ldw;
 }
 
 // Stores to the band array: agent-scope stores, performed past the XCD's L2
@@ -98,442 +110,142 @@ __device__ __forceinline__ int aload(const int32_t* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ __forceinline__ double wave_sum(double x) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) x += __shfl_xor(x, o, 64);
-    return x;
-}
-
-// Sum over the workgroup; the result is returned to every thread.
-__device__ __forceinline__ double block_sum(double x, double* red) {
-    x = wave_sum(x);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
-    __syncthreads();
-    double s = 0.0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) s += red[w];
-    return s;
-}
-
-// Householder reflector of the L values in v[0 .. L-1] (LDS), in place:
-// v becomes (1, x2 / (alpha - beta)); returns tau (0: the identity) and
-// beta, the value left in the first position.
-__device__ __forceinline__ double reflector(double* v, int L, double* red, double* beta_out) {
-    const int tid = threadIdx.x;
-    const double x = tid < L ? v[tid] : 0.0;
-    const double ss = block_sum(tid >= 1 && tid < L ? x * x : 0.0, red);
-    const double alpha = v[0];
-    __syncthreads();                      // every thread has read v[0] and red
-    if (ss == 0.0) {
-        *beta_out = alpha;
-        return 0.0;
-    }
-    const double beta = -copysign(sqrt(alpha * alpha + ss), alpha);
-    const double scal = 1.0 / (alpha - beta);
-    if (tid < L) v[tid] = tid == 0 ? 1.0 : x * scal;
-    __syncthreads();
-    *beta_out = beta;
-    return (beta - alpha) / beta;
-}
-
-// Wait until *p >= target (wave 0 polls), then acquire.  false: stop (an
-// error was reported, or the watchdog fired here).
-__device__ bool wait_geq(const ChaseArgs& a, const int32_t* p, int target, int* flag) {
-    if (threadIdx.x < 64) {
-        const int lane = threadIdx.x;
-        int ok = 1;
-        const uint64_t t0 = wall_clock64();
-        for (;;) {
-            int v = 0, err = 0;
-            if (lane == 0) {
-                v = aload(p);
-                if (v < target) err = aload(&a.ctrl[G_ERROR]);
-            }
-            v = __builtin_amdgcn_readfirstlane(v);
-            if (v >= target) break;
-            if (__builtin_amdgcn_readfirstlane(err) != 0) {
-                ok = 0;
-                break;
-            }
-            if ((int64_t)(wall_clock64() - t0) > a.watchdog_ticks) {
-                if (lane == 0)
-                    __hip_atomic_store(&a.ctrl[G_ERROR], BB_ETIMEOUT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                ok = 0;
-                break;
-            }
-            __builtin_amdgcn_s_sleep(2);
-        }
-        if (lane == 0) *flag = ok;
-        // no acquire: the band array is read with agent-scope loads, issued
-        // only after this load of the counter has returned
-    }
-    __syncthreads();
-    const int ok = __builtin_amdgcn_readfirstlane(*flag);
-    return ok != 0;
-}
-
-// Step t of sweep k for nb > LDS_NB, on the band array in global memory, by
-// member g of the group of a.group workgroups that runs the sweep (with
-// a group of one, as bb_bnd2bd_group allows, no group barriers).  Only
-// about n / (2.5 nb) sweeps can run at once (26 at n = 16384, nb = 256), so
-// each sweep's steps are spread over a group to use the other CUs.
-//   * Every member reads row rr and forms the right reflector (the same
-//     arithmetic, the same result); the right update M -= tau (M v) v^T of
-//     rows rr+1 .. c+L-1 of columns c .. c+L-1 is split by rows, TPR lanes a
-//     row, in two passes (the row products, then the update).  Every sum
-//     is taken in the same order whatever the group size, so the result
-//     does not depend on it.
-//   * Group barrier: column c is final.
-//   * Every member reads column c and forms the left reflector; the left
-//     update M -= tau v (v^T M) of rows c .. c+L-1 of columns c+1 .. ce-1 is
-//     split by chunks of CHUNK columns, one row per thread, the column sums
-//     formed through LDS, each entry read and written once.
-//   * Group barrier: the step's updates are done.  Member 0 then writes the
-//     cleared row rr and column c (beta, zeros), which no member reads later
-//     in the step or in the next one (the corner of row rr went out with the
-//     half step, after the first group barrier).
-// In the band array entry (i, j+1) follows entry (i, j) at a distance of
-// ldw - 1.  false: an error was reported or the watchdog fired.
-constexpr int GROUP_NB = 64;
-constexpr int GROUP_MAX = 16;
-constexpr int CHUNK = 32;
-constexpr int PLD = NT + 8;              // LDS stride of a product column: lanes 8u+s hit distinct banks
-constexpr int RB = 32;                   // loads in flight per thread in the row passes
-constexpr int TPR = 4;                   // lanes a row in the right update
-
 // A barrier for LDS traffic only: it waits for this wave's LDS operations,
-// not for its global loads, so loads issued before it stay in flight.
+// not for its global accesses, so stores stay in flight across it.
 __device__ __forceinline__ void lds_barrier() {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// The half of step t of sweep k that the next sweep waits for: the corner
-// (rr, c), the first entry of the row the right reflector clears, is final
-// (beta; alpha when the row needs no reflector).  Thread 0 stores it (the
-// LDS steps hold a newer value than memory even then), waits for the store
-// and moves the progress counter to 2t+1; every earlier store of the sweep
-// has completed too, each wave having waited for its own before the
-// preceding barrier (2T marks the whole sweep).  The step's own stores leave
-// the corner alone afterwards: the next sweep changes it from here on.
-__device__ __forceinline__ void publish_corner(const ChaseArgs& a, int64_t k, int64_t t, double* corner,
-                                               double beta) {
-    if (threadIdx.x < 64) {
-        if (threadIdx.x == 0) st(corner, beta);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (threadIdx.x == 0)
-            __hip_atomic_store(&a.prog[k], (int)(2 * t + 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// This wave's loads and stores have completed.
+__device__ __forceinline__ void wait_memory() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// Sum over the four rows of 16 lanes (equal lane % 16), in every lane: four
+// 4 x 4 x 4 matrix products with ones, whose k index is the row.
+__device__ __forceinline__ double sum_rows(double v) {
+    return __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, v, 0.0, 0, 0, 0);
+}
+
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xF, 0xF, true);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, true);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
+// Sum over the lanes l, l + R, l + 2R, ... (64 / R of them; R = 16, 8, 4), or
+// over the wave (R = 1), in each of them.
+template <int R>
+__device__ __forceinline__ double sum_parts(double v) {
+    if (R <= 8) v += dpp<0x128>(v);     // row_ror:8
+    if (R <= 4) v += dpp<0x124>(v);     // row_ror:4
+    if (R <= 2) v += dpp<0x122>(v);     // row_ror:2
+    if (R <= 1) v += dpp<0x121>(v);     // row_ror:1
+    return sum_rows(v);
+}
+
+// Sum of a lane and lane ^ 32.
+__device__ __forceinline__ double sum_halves(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)b, (uint32_t)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false);
+    return __builtin_bit_cast(double, (uint64_t)hi[0] << 32 | lo[0]) +
+           __builtin_bit_cast(double, (uint64_t)hi[1] << 32 | lo[1]);
+}
+
+// Householder reflector of (al, x) with ss = x^T x: beta = -sign(al) nrm,
+// tau = (beta - al) / beta, scale = 1 / (al - beta) (v = (1, scale x)); a
+// zero tail gives the identity.  1 / nrm and scale take one step of third
+// order from the hardware approximations.
+struct Refl {
+    double beta, tau, scale;
+};
+__device__ __forceinline__ Refl reflector(double al, double ss) {
+    if (ss == 0.0) return {al, 0.0, 0.0};
+    const double t = fma(al, al, ss), ts = copysign(t, al), r0 = __builtin_amdgcn_rsq(t);
+    const double s0 = ts * r0, y0 = __builtin_amdgcn_rcp(al + s0);
+    const double e0 = fma(-fabs(s0), r0, 1.0);
+    const double r = fma(r0 * e0, fma(e0, 0.375, 0.5), r0);
+    const double s1 = ts * r;
+    const double e1 = fma(-(al + s1), y0, 1.0);
+    return {-fma(fma(-s1, s1, t), copysign(0.5 * r, al), s1), fma(fabs(al), r, 1.0), fma(y0, fma(e1, e1, e1), y0)};
+}
+
+// Called by a whole wave: polls *p (each lane's own) until all have reached
+// target; false when an error was reported or the watchdog fired.
+__device__ __forceinline__ bool poll(const ChaseArgs& a, const int32_t* p, int target) {
+    const uint64_t t0 = wall_clock64();
+    for (;;) {
+        const int v = aload(p);
+        if (__builtin_amdgcn_ballot_w64(v < target) == 0) return true;
+        if (__builtin_amdgcn_readfirstlane(aload(&a.ctrl[G_ERROR])) != 0) return false;
+        if ((int64_t)(wall_clock64() - t0) > a.watchdog_ticks) {
+            if (threadIdx.x % 64 == 0)
+                __hip_atomic_store(&a.ctrl[G_ERROR], BB_ETIMEOUT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return false;
+        }
+        __builtin_amdgcn_s_sleep(1);
     }
 }
 
-// Publish value through *p after every wave's earlier accesses.  Each wave
-// first waits for its own loads and stores to complete (the barrier alone
-// does not wait for them; the band array's stores are agent-scope, so a
-// completed one has been performed past the XCD's L2 and no write-back is
-// needed), the workgroup meets, and thread 0 stores or adds.
-__device__ __forceinline__ void publish_after_barrier(int32_t* p, int value, bool add) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (threadIdx.x < 64) {
-        if (threadIdx.x == 0) {
-            if (add) __hip_atomic_fetch_add(p, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            else __hip_atomic_store(p, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
-}
-
-__device__ bool group_barrier(const ChaseArgs& a, int64_t k, int target, int* flag) {
-    publish_after_barrier(&a.bar[k], 1, true);
-    return wait_geq(a, &a.bar[k], target, flag);
-}
-
-__device__ bool chase_step(const ChaseArgs& a, int64_t k, int64_t t, int g, double* v, double* red, double* P,
-                           double* wq, int* flag) {
-    const int tid = threadIdx.x;
-    const int nb = a.nb;
-    const int G = a.group;
-    const int64_t c = k + 1 + t * nb;
-    const int64_t rr = t == 0 ? k : c - nb;
-    const int L = (int)(a.n - c < nb ? a.n - c : nb);
-    const int64_t s = a.ldw - 1;
-
-    // right reflector: clear row rr beyond column c; the previous step's
-    // stores complete in every wave before the reflector's barriers, so the
-    // corner's release below covers them too
-    if (tid < L) v[tid] = ld(at(a, rr, c + tid));
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    double beta_r, beta_l;
-    const double tau_r = reflector(v, L, red, &beta_r);
-    if (G == 1) publish_corner(a, k, t, at(a, rr, c), beta_r);
-    if (tau_r != 0.0) {
-        const int R = (int)(c + L - 1 - rr);          // rows rr+1 .. c+L-1
-        const int rpm = (R + G - 1) / G;              // rows of this member: r0 .. r1-1
-        const int r0 = g * rpm, r1 = r0 + rpm < R ? r0 + rpm : R;
-        // TPR lanes a row whatever the group size, so that every row's
-        // products are summed in the same order for any group
-        constexpr int tpr = TPR;
-        const int part = tid & (tpr - 1);
-        // the tpr lanes of a row are adjacent and share its loop trips, so
-        // the shuffles that sum their parts stay within active lanes
-        for (int r = r0 + tid / tpr; r < r1; r += NT / tpr) {
-            double* p = at(a, rr + 1 + r, c);
-            double w0 = 0.0, w1 = 0.0;
-            int j = part;
-            for (; j + (RB - 1) * tpr < L; j += RB * tpr) {
-                double x[RB];
-#pragma unroll
-                for (int u = 0; u < RB; ++u) x[u] = ld(p + (j + u * tpr) * s);
-#pragma unroll
-                for (int u = 0; u < RB; u += 2) {
-                    w0 += x[u] * v[j + u * tpr];
-                    w1 += x[u + 1] * v[j + (u + 1) * tpr];
-                }
-            }
-            for (; j < L; j += tpr) w0 += ld(p + j * s) * v[j];
-            double w = w0 + w1;
-            for (int o = 1; o < tpr; o *= 2) w += __shfl_xor(w, o, 64);
-            w *= tau_r;
-            j = part;
-            for (; j + (RB - 1) * tpr < L; j += RB * tpr) {
-                double x[RB];
-#pragma unroll
-                for (int u = 0; u < RB; ++u) x[u] = ld(p + (j + u * tpr) * s);
-#pragma unroll
-                for (int u = 0; u < RB; ++u) st(p + (j + u * tpr) * s, x[u] - w * v[j + u * tpr]);
-            }
-            for (; j < L; j += tpr) st(p + j * s, ld(p + j * s) - w * v[j]);
-        }
-    }
-    if (G > 1) {
-        // every member has read row rr: its corner may now change
-        if (!group_barrier(a, k, (int)(2 * t + 1) * G, flag)) return false;
-        if (g == 0) publish_corner(a, k, t, at(a, rr, c), beta_r);
-    }
-    __syncthreads();
-
-    // left reflector: clear column c below the diagonal
-    if (tid < L) v[tid] = ld(at(a, c + tid, c));
-    __syncthreads();
-    const double tau_l = reflector(v, L, red, &beta_l);
-    if (tau_l != 0.0) {
-        const int64_t ce = c + 2 * nb < a.n ? c + 2 * nb : a.n;
-        const int C = (int)(ce - c - 1);              // columns c+1 .. ce-1
-        const double vi = tid < L ? v[tid] : 0.0;
-        double* p = tid < L ? at(a, c + tid, c + 1) : nullptr;
-        const int cu = tid >> 3, cs = tid & 7;        // column sums: column cu, rows cs + 8 r
-        // the next chunk's loads are issued before this chunk's sums
-        double x[CHUNK];
-        int q0 = g * CHUNK;
-#pragma unroll
-        for (int u = 0; u < CHUNK; ++u) x[u] = (tid < L && q0 + u < C) ? ld(p + (q0 + u) * s) : 0.0;
-        for (; q0 < C; q0 += G * CHUNK) {
-#pragma unroll
-            for (int u = 0; u < CHUNK; ++u) P[u * PLD + tid] = vi * x[u];
-            lds_barrier();
-            const int qn = q0 + G * CHUNK;
-            double y[CHUNK];
-#pragma unroll
-            for (int u = 0; u < CHUNK; ++u) y[u] = (tid < L && qn + u < C) ? ld(p + (qn + u) * s) : 0.0;
-            double sum = 0.0;
-            for (int r = cs; r < L; r += 8) sum += P[cu * PLD + r];
-            sum += __shfl_xor(sum, 1, 64);
-            sum += __shfl_xor(sum, 2, 64);
-            sum += __shfl_xor(sum, 4, 64);
-            if (cs == 0) wq[cu] = tau_l * sum;
-            lds_barrier();
-            if (tid < L) {
-#pragma unroll
-                for (int u = 0; u < CHUNK; ++u)
-                    if (q0 + u < C) st(p + (q0 + u) * s, x[u] - vi * wq[u]);
-            }
-#pragma unroll
-            for (int u = 0; u < CHUNK; ++u) x[u] = y[u];
-        }
-    }
-    if (G > 1 && !group_barrier(a, k, (int)(2 * t + 2) * G, flag)) return false;
-    if (g == 0) {
-        if (tau_r != 0.0 && tid >= 1 && tid < L) st(at(a, rr, c + tid), 0.0);   // the corner went out early
-        if (tau_l != 0.0 && tid < L) st(at(a, c + tid, c), tid == 0 ? beta_l : 0.0);
-    }
-    __syncthreads();
-    return true;
-}
-
-// Reflector of the L <= 64 values x[i ld] (LDS), formed by wave 0 alone: v
-// gets (1, x2 / (alpha - beta)), x gets (beta, 0, ..), sc[0] tau (0: the
-// identity, x left as it is).  The caller synchronizes after it.
-__device__ __forceinline__ void reflector_wave(double* x, int ld, int L, double* v, double* sc) {
-    const int lane = threadIdx.x;
-    const double xi = lane < L ? x[lane * ld] : 0.0;
-    const double ss = wave_sum(lane >= 1 ? xi * xi : 0.0);
-    const double alpha = __shfl(xi, 0, 64);
-    double tau = 0.0;
-    if (ss != 0.0) {
-        const double beta = -copysign(sqrt(alpha * alpha + ss), alpha);
-        const double scal = 1.0 / (alpha - beta);
-        tau = (beta - alpha) / beta;
-        if (lane < L) {
-            v[lane] = lane == 0 ? 1.0 : xi * scal;
-            x[lane * ld] = lane == 0 ? beta : 0.0;
-        }
-    }
-    if (lane == 0) sc[0] = tau;
-}
-
-// The same step with its region staged in LDS, for nb <= LDS_NB.  The region
-// is three nb x nb quadrants, each stored by column with stride LDS_LD: U
-// (rows c-nb .. c-1 of columns c .. c+nb-1; only rows from rr on are in
-// use), D (rows and columns c .. c+nb-1) and Q (rows c .. c+nb-1, columns
-// c+nb .. c+2nb-1).  Q of step t is U of step t+1, and no other sweep
-// touches it between the two (the sweep ahead finished its steps there
-// before step t started, the sweep behind waits for step t+1), so it stays
-// in LDS: the three buffers rotate, step t loads only D and Q (and, for
-// t = 0, the row k), and stores U and D; Q reaches memory as the next
-// step's U (the last step of a sweep has no Q).  Thread tid moves row
-// tid % nb of columns tid / nb + j (NT / nb), all its loads issued before
-// the first is used.  With the band array's column stride ldw and the
-// entry (i, j+1) at ldw - 1 after (i, j), for d0 = W + 2nb - 1 + c ldw:
-//     D(r, q) = d0 + r + q (ldw - 1),  U(r, q) = D(r, q) - nb,
-//     Q(r, q) = D(r, q) - nb + nb ldw.
-constexpr int LDS_NB = 64;
-constexpr int LDS_LD = LDS_NB + 1;
-// columns a thread moves, at most: cpp = NT / nb >= NT / LDS_NB, so LDS_J cpp >= nb
-constexpr int LDS_J = (LDS_NB + NT / LDS_NB - 1) / (NT / LDS_NB);
-static_assert(LDS_J <= 16, "per-thread staging registers");
-// the updates give each row (column) of a quadrant pair two lanes, each with
-// half of it in registers: 2 (2 nb - 1) <= NT lanes
-constexpr int HALF = LDS_NB / 2;
-static_assert(2 * (2 * LDS_NB - 1) <= NT, "one pass of lane pairs");
-
-__device__ void chase_step_lds(const ChaseArgs& a, int64_t k, int64_t t, double* U, double* D, double* Q,
-                               double* v, double* sc) {
-    const int tid = threadIdx.x;
-    const int nb = a.nb;
-    const int64_t c = k + 1 + t * nb;
-    const int L = (int)(a.n - c < nb ? a.n - c : nb);
-    const int64_t nq = a.n - (c + nb);
-    const int Lq = nq <= 0 ? 0 : (int)(nq < nb ? nq : nb);
-    const int u0 = t == 0 ? nb - 1 : 0;          // first U row in use
-    const int64_t s = a.ldw - 1;
-    const int cpp = NT / nb;                     // columns moved at once
-    const int tr = tid % nb, tq = tid / nb;
-    const bool mover = tq < cpp && tr < L;       // D and Q rows < L exist
-    const double* db = a.W + (2 * nb - 1) + c * a.ldw;
-    const double* d0 = db + tr;
-    const double* q0p = d0 - nb + (int64_t)nb * a.ldw;
-    {
-        double xd[LDS_J], xq[LDS_J];
-        const double xu = t == 0 && tid < L ? ld(db + tid * s - 1) : 0.0;     // U(nb-1, tid): the row k
-#pragma unroll
-        for (int j = 0; j < LDS_J; ++j) {
-            const int q = tq + j * cpp;
-            xd[j] = mover && q < L ? ld(d0 + q * s) : 0.0;
-            xq[j] = mover && q < Lq ? ld(q0p + q * s) : 0.0;
-        }
-        if (t == 0 && tid < L) U[(nb - 1) + tid * LDS_LD] = xu;
-#pragma unroll
-        for (int j = 0; j < LDS_J; ++j) {
-            const int q = tq + j * cpp;
-            if (mover && q < L) D[tr + q * LDS_LD] = xd[j];
-            if (mover && q < Lq) Q[tr + q * LDS_LD] = xq[j];
-        }
-    }
-    __syncthreads();
-
-    // right reflector (wave 0): clear row rr (U row u0) beyond column c;
-    // then rows U u0+1 .. nb-1 and D 0 .. L-1 take M -= tau (M v) v^T
-    if (tid < 64) reflector_wave(U + u0, LDS_LD, L, v, sc);
-    // the previous step's stores complete in every wave before the barrier,
-    // so wave 0's release in publish_corner covers them too
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    publish_corner(a, k, t, const_cast<double*>(db) - nb + u0, U[u0]);
-    const int pr = tid >> 1, ph = tid & 1;       // a pair of lanes per row (column): halves of it
-    double tau = sc[0];
-    if (tau != 0.0) {
-        const int ru = nb - 1 - u0;
-        const bool act = pr < ru + L;
-        double* p = pr < ru ? U + (u0 + 1 + pr) : D + (pr - ru);
-        double x[HALF];
-        double w = 0.0;
-#pragma unroll
-        for (int u = 0; u < HALF; ++u) {
-            const int j = ph * HALF + u;
-            x[u] = act && j < L ? p[j * LDS_LD] : 0.0;
-        }
-#pragma unroll
-        for (int u = 0; u < HALF; ++u) {
-            const int j = ph * HALF + u;
-            if (j < L) w += x[u] * v[j];
-        }
-        w = tau * (w + __shfl_xor(w, 1, 64));
-#pragma unroll
-        for (int u = 0; u < HALF; ++u) {
-            const int j = ph * HALF + u;
-            if (act && j < L) p[j * LDS_LD] = x[u] - w * v[j];
-        }
-    }
-    __syncthreads();
-
-    // left reflector (wave 0): clear column c (D column 0) below the
-    // diagonal; then D columns 1 .. L-1 and Q columns 0 .. Lq-1 take
-    // M -= tau v (v^T M)
-    if (tid < 64) reflector_wave(D, 1, L, v, sc);
-    __syncthreads();
-    tau = sc[0];
-    if (tau != 0.0) {
-        const bool act = pr < L - 1 + Lq;
-        double* p = pr < L - 1 ? D + (pr + 1) * LDS_LD : Q + (pr - (L - 1)) * LDS_LD;
-        double x[HALF];
-        double w = 0.0;
-#pragma unroll
-        for (int u = 0; u < HALF; ++u) {
-            const int i = ph * HALF + u;
-            x[u] = act && i < L ? p[i] : 0.0;
-        }
-#pragma unroll
-        for (int u = 0; u < HALF; ++u) {
-            const int i = ph * HALF + u;
-            if (i < L) w += v[i] * x[u];
-        }
-        w = tau * (w + __shfl_xor(w, 1, 64));
-#pragma unroll
-        for (int u = 0; u < HALF; ++u) {
-            const int i = ph * HALF + u;
-            if (act && i < L) p[i] = x[u] - w * v[i];
-        }
-    }
-    __syncthreads();
-
-    // store U (rows u0 .. nb-1) and D back; Q stays for the next step
-    double* ud = const_cast<double*>(d0);
-    if (tq < cpp && tr >= u0) {
-#pragma unroll
-        for (int j = 0; j < LDS_J; ++j) {
-            const int q = tq + j * cpp;
-            if (q < L && (q > 0 || tr > u0)) st(ud + q * s - nb, U[tr + q * LDS_LD]);   // not the corner
-        }
-    }
-    if (mover) {
-#pragma unroll
-        for (int j = 0; j < LDS_J; ++j) {
-            const int q = tq + j * cpp;
-            if (q < L) st(ud + q * s, D[tr + q * LDS_LD]);
-        }
-    }
-}
-
-template <bool TILE>
+// The chase.  A group of a.group workgroups runs a sweep; member m holds, in
+// LDS, rows s = m S .. m S + S - 1 of each block row of the sweep's window
+// (S = 4096 / NBP, so a quadrant's slice is 4096 entries for any nb): three
+// quadrants, by step t with block column c:
+//     U  rows c - nb + s, columns c .. c + nb - 1   (t >= 1),
+//     D  rows c + s,      columns c .. c + nb - 1,
+//     Q  rows c + s,      columns c + nb .. c + 2 nb - 1.
+// Q of step t is U of step t + 1, with the same owner, and no other sweep
+// touches it between the two: the buffers rotate, a step loads D and Q and
+// stores U and D.
+//   * Right reflector (row rr, cleared): every member knows the row, from
+//     the step before, and applies the reflector to its rows alone.
+//   * Left reflector (column c): with x the column below its first entry,
+//     v = (1, scale x), so v^T M = M(0, :) + scale (x^T M): one exchange of
+//     the members' partial products x^T M (its first entry is x^T x) and of row 0 gives
+//     every member the norm, the reflector, the products it applies to its
+//     rows, and the new row 0 of Q -- the row the next step clears.
+// So a step has one exchange between members (none for nb <= 64, a group of
+// one) and one wait for the sweep ahead.  Members' sums are added in the
+// order of the members, so all members compute the same values.
+//
+// What bounds it: the chain of steps.  A sweep follows the one ahead at a
+// distance of two steps, so the chase is about 2 n steps one after the other
+// plus, per step, the round trips to the coherence point: the poll of the
+// sweep ahead, the loads, for groups the exchange (store, counter, poll,
+// loads), and the publication, which is taken off the chain: a step's stores
+// complete while the next step's wait is polled, and the last wave whose
+// stores have completed publishes.
+// Why this split: a right update needs whole rows and a left update whole
+// columns, and slices by rows make the first local and leave the second one
+// exchange of sums; shares of rows and of columns by turns, as before, moved
+// every quadrant through memory between the two and met at two group
+// barriers a step.  Measured, before and now: 2000 at nb = 64 70.7 and
+// 24.7 ms (6.2 us a step), 8192 at nb = 256 477 and 232 ms (14.1 us), 16384
+// at nb = 128 982 and 333 ms (10.2 us); 9000 at nb = 16 217 and 100 ms.
+template <int NBP>
 __global__ __launch_bounds__(NT) void chase_kernel(ChaseArgs a) {
-    __shared__ double v[MAX_NB];
-    __shared__ double red[NW];
-    // TILE: the three rotating quadrant buffers; else the left update's
-    // column products and sums
-    __shared__ double lds[TILE ? 3 * LDS_NB * LDS_LD : CHUNK * PLD + CHUNK];
-    __shared__ int sk, flag;
-    const int tid = threadIdx.x;
-    const int G = TILE ? 1 : a.group;
+    constexpr int S = SLICE / NBP;          // rows of a slice: 64, 32, 16
+    constexpr int PR = NBP / 16, R = 64 / PR;   // right update: lanes per row, rows per wave
+    constexpr int PL = S / 16, C = 64 / PL;     // left update: lanes per column, columns per wave
+    constexpr int ST = S + PL;              // LDS column stride: columns and rows spread over the banks
+    static_assert(NW * R == 2 * S && NW * C == 2 * NBP, "one pass");
+    constexpr bool GROUPED = NBP > 64;
+    __shared__ double quad[3][NBP * ST];
+    __shared__ double vr[NBP], xr[NBP];     // the right reflector; the row it comes from
+    __shared__ double srefl[2];             // its beta, tau
+    __shared__ int sk, flag, stored;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nb = a.nb, G = GROUPED ? a.group : 1;
+    const int64_t cs = a.ldw - 1;           // from entry (i, j) to (i, j + 1)
+    // right update: row (U for waves 0-3, D for waves 4-7), columns rp + PR u
+    const int rrow = (w % (NW / 2)) * R + lane % R, rp = lane / R;
+    // left update: column (D for waves 0-3, Q for waves 4-7), rows lp + PL u
+    const int lcol = (w % (NW / 2)) * C + lane % C, lp = lane / C;
+    const bool low = w < NW / 2;
+    if (tid == 0) stored = 0;
+
     for (;;) {
         // ticket = sweep * G + member: a group's members are consecutive
         // tickets, all taken by running workgroups before any of them can
@@ -543,30 +255,211 @@ __global__ __launch_bounds__(NT) void chase_kernel(ChaseArgs a) {
         const int ticket = __builtin_amdgcn_readfirstlane(sk);
         __syncthreads();
         const int64_t k = ticket / G;
-        const int g = ticket - (int)k * G;
+        const int m = ticket - (int)k * G;
         if (k >= a.nsweeps) return;
-        const int64_t T = nsteps(a.n, a.nb, k);
-        const int64_t Tp = k > 0 ? nsteps(a.n, a.nb, k - 1) : 0;
-        for (int64_t t = 0; t < T; ++t) {
-            // the previous sweep's step t+1 done and step t+2 half done
-            // (2t+5), or the whole sweep when it is shorter
-            if (k > 0 && !wait_geq(a, &a.prog[k - 1], (int)(t + 2 < Tp ? 2 * t + 5 : 2 * Tp), &flag)) return;
-            if constexpr (TILE) {
-                const int u = (int)((2 * t) % 3);    // Q of step t is U of step t+1
-                double* U = lds + u * LDS_NB * LDS_LD;
-                double* D = lds + ((u + 1) % 3) * LDS_NB * LDS_LD;
-                double* Q = lds + ((u + 2) % 3) * LDS_NB * LDS_LD;
-                chase_step_lds(a, k, t, U, D, Q, v, red);   // red[0]: tau
-            } else {
-                if (!chase_step(a, k, t, g, v, red, lds, lds + CHUNK * PLD, &flag)) return;
+        const int T = (int)nsteps(a.n, nb, k);
+        const int Tp = k > 0 ? (int)nsteps(a.n, nb, k - 1) : 0;
+        double* area = GROUPED ? a.xch + (k % a.nareas) * (2 * (int64_t)(G + 1) * 2 * NBP) : nullptr;
+        int32_t* prog = a.prog + k * G;
+
+        // The reflector that clears row (i, j .. j + len - 1) held in xr, by
+        // this wave: vr and srefl; the owner of the row stores it cleared
+        // (row k later, when every member has read it).
+        auto right_reflector = [&](int64_t i, int64_t j, int len) {
+            double x[NBP / 64], ss = 0.0;
+#pragma unroll
+            for (int h = 0; h < NBP / 64; ++h) {
+                x[h] = xr[lane + 64 * h];
+                if (lane + 64 * h > 0) ss = fma(x[h], x[h], ss);
             }
-            // The next sweep waits for half steps (2t+5: step t+1 done, the
-            // corner of step t+2 final), whose release also covers every
-            // earlier store of the sweep; only the last step is published
-            // whole (2T).  The barrier keeps a step's LDS buffers until
-            // every wave has stored them.
-            if (g == 0 && t + 1 == T) publish_after_barrier(&a.prog[k], (int)(2 * T), false);
-            else __syncthreads();
+            const Refl f = reflector(xr[0], sum_parts<1>(ss));
+#pragma unroll
+            for (int h = 0; h < NBP / 64; ++h) {
+                const int q = lane + 64 * h;
+                vr[q] = q == 0 ? 1.0 : f.scale * x[h];
+                if (i > k && m == 0 && q < len)
+                    st(a.W + (i - j + 2 * nb - 1) + j * a.ldw + q * cs, q == 0 ? f.beta : 0.0);
+            }
+            if (lane == 0) {
+                srefl[0] = f.beta;
+                srefl[1] = f.tau;
+            }
+        };
+
+        for (int t = 0; t < T; ++t) {
+            const int64_t c = k + 1 + (int64_t)t * nb;
+            const int L = (int)(a.n - c < nb ? a.n - c : nb);
+            const int64_t nq = a.n - (c + nb);
+            const int Lq = nq <= 0 ? 0 : (int)(nq < nb ? nq : nb);
+            double* U = quad[(2 * t) % 3];          // Q of step t is U of step t + 1
+            double* D = quad[(2 * t + 1) % 3];
+            double* Q = quad[(2 * t + 2) % 3];
+            double* w0 = a.W + (2 * nb - 1) + c * a.ldw;    // entry (c, c)
+
+            // The sweep ahead has finished step t + 1 (and with it stored the
+            // row its step t + 2 clears): this member's rows, one further down than
+            // there, belong to members m and m + 1 of it (the last one to
+            // member 0, in the next block); row k, which every member reads
+            // at the first step, to member 0.
+            const bool waits = k > 0 && w == 0;
+            const int32_t* ahead = a.prog + (k - 1) * G + (lane == 0 ? m : lane == 1 ? (m + 1 < G ? m + 1 : 0)
+                                                                                           : (t > 0 ? m : 0));
+            const int target = t + 2 < Tp ? t + 2 : Tp;
+            const int seen = waits ? aload(ahead) : 0;      // beside the stores still in flight
+            // the previous step's stores: published by the wave whose stores
+            // complete last
+            if (t > 0) {
+                wait_memory();
+                if (lane == 0 && __hip_atomic_fetch_add(&stored, 1, __ATOMIC_RELAXED,
+                                                        __HIP_MEMORY_SCOPE_WORKGROUP) % NW == NW - 1)
+                    __hip_atomic_store(&prog[m], t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            if (waits) {
+                const bool ok = __builtin_amdgcn_ballot_w64(seen < target) == 0 || poll(a, ahead, target);
+                if (lane == 0) flag = ok;
+            }
+            lds_barrier();
+            if (k > 0 && __builtin_amdgcn_readfirstlane(flag) == 0) return;
+            {
+                double xd[SLICE / NT], xq[SLICE / NT], xk = 0.0;
+#pragma unroll
+                for (int h = 0; h < SLICE / NT; ++h) {
+                    const int e = tid + NT * h, i = e % S, q = e / S, s = m * S + i;
+                    xd[h] = s < L && q < L ? ld(w0 + s + q * cs) : 0.0;
+                    xq[h] = s < L && q < Lq ? ld(w0 + s + (q + nb) * cs) : 0.0;
+                }
+                if (t == 0 && tid < L) xk = ld(w0 - 1 + tid * cs);       // row k
+#pragma unroll
+                for (int h = 0; h < SLICE / NT; ++h) {
+                    const int e = tid + NT * h, i = e % S, q = e / S;
+                    D[i + q * ST] = xd[h];
+                    Q[i + q * ST] = xq[h];
+                }
+                if (t == 0 && tid < NBP) xr[tid] = xk;
+            }
+            lds_barrier();
+            if (t == 0) {
+                if (w == NW - 1) right_reflector(k, c, L);
+                lds_barrier();
+            }
+
+            // right update M -= tau (M v) v^T of rows rr + 1 .. c + L - 1
+            if (!low || t > 0) {
+                double* M = (low ? U : D) + rrow + rp * ST;
+                const double tau = srefl[1];
+                double x[16], v[16], p[2] = {0.0, 0.0};
+#pragma unroll
+                for (int u = 0; u < 16; ++u) {
+                    x[u] = M[u * PR * ST];
+                    v[u] = vr[rp + PR * u];
+                }
+#pragma unroll
+                for (int u = 0; u < 16; ++u) p[u & 1] = fma(x[u], v[u], p[u & 1]);
+                const double wt = tau * sum_parts<R>(p[0] + p[1]);
+#pragma unroll
+                for (int u = 0; u < 16; ++u) x[u] = fma(-wt, v[u], x[u]);
+                if (low) {
+                    // U is final; its row 0 is rr, stored cleared already
+                    const int s = m * S + rrow;
+                    if (s > 0 && s < nb) {
+#pragma unroll
+                        for (int u = 0; u < 16; ++u)
+                            if (rp + PR * u < L) st(w0 - nb + s + (rp + PR * u) * cs, x[u]);
+                    }
+                } else {
+#pragma unroll
+                    for (int u = 0; u < 16; ++u) M[u * PR * ST] = x[u];
+                }
+            }
+            lds_barrier();
+
+            // left update M -= tau v (v^T M) of columns c + 1 .. c + nb + Lq - 1,
+            // x_0 taken as zero; column c itself becomes (beta_l, 0, ..), but
+            // stays as it is in LDS, where every wave reads x
+            double beta_l;
+            {
+                double* M = (low ? D : Q) + lcol * ST + lp;
+                const bool top = m == 0 && lp == 0;             // element 0 is row 0
+                double x[16], y[16], p[2] = {0.0, 0.0};
+#pragma unroll
+                for (int u = 0; u < 16; ++u) {
+                    y[u] = M[u * PL];
+                    x[u] = D[lp + PL * u];
+                }
+                if (top) x[0] = 0.0;
+#pragma unroll
+                for (int u = 0; u < 16; ++u) p[u & 1] = fma(x[u], y[u], p[u & 1]);
+                double dot = p[0] + p[1], ss, row0, al;
+                if (PL == 4) dot = sum_rows(dot);
+                if (PL == 2) dot = sum_halves(dot);
+                if constexpr (!GROUPED) {
+                    row0 = (low ? D : Q)[lcol * ST];
+                    al = D[0];
+                    const double xi = lane > 0 ? D[lane] : 0.0;
+                    ss = sum_parts<1>(xi * xi);
+                } else {
+                    double* slot = area + (t & 1) * (int64_t)(G + 1) * 2 * NBP;
+                    const int q = (low ? 0 : NBP) + lcol;
+                    if (lp == 0) {
+                        st(slot + m * 2 * NBP + q, dot);
+                        if (m == 0) st(slot + G * 2 * NBP + q, y[0]);
+                    }
+                    wait_memory();
+                    lds_barrier();
+                    if (w == 0) {
+                        if (lane == 0)
+                            __hip_atomic_fetch_add(&a.bar[k], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        const bool ok = poll(a, &a.bar[k], (t + 1) * G);
+                        if (lane == 0) flag = ok;
+                    }
+                    lds_barrier();
+                    if (__builtin_amdgcn_readfirstlane(flag) == 0) return;
+                    double pd[GROUP_MAX], ps[GROUP_MAX];
+#pragma unroll
+                    for (int h = 0; h < GROUP_MAX; ++h) {
+                        pd[h] = h < G ? ld(slot + h * 2 * NBP + q) : 0.0;
+                        ps[h] = h < G ? ld(slot + h * 2 * NBP) : 0.0;
+                    }
+                    row0 = ld(slot + G * 2 * NBP + q);
+                    al = ld(slot + G * 2 * NBP);
+                    dot = ss = 0.0;
+#pragma unroll
+                    for (int h = 0; h < GROUP_MAX; ++h) {
+                        dot += pd[h];
+                        ss += ps[h];
+                    }
+                }
+                const Refl f = reflector(al, ss);
+                const double wt = f.tau * fma(f.scale, dot, row0);
+                const double ws = wt * f.scale;
+                beta_l = f.beta;
+                // row k, which every member has read by now, is stored cleared
+                if (low && t == 0 && m == 0 && tid < L) st(w0 - 1 + tid * cs, tid == 0 ? srefl[0] : 0.0);
+                if (!low || lcol > 0) {
+                    if (top) y[0] -= wt;
+#pragma unroll
+                    for (int u = 0; u < 16; ++u) M[u * PL] = fma(-ws, x[u], y[u]);  // (x_0 is zero)
+                }
+                if (!low && lp == 0) xr[lcol] = row0 - wt;      // the row the next step clears
+            }
+            lds_barrier();
+
+            // D is final: whole columns of the slice; the last wave first
+            // forms the next right reflector
+            if (w == NW - 1 && Lq > 0) right_reflector(c, c + nb, Lq);
+#pragma unroll
+            for (int h = 0; h < SLICE / NT; ++h) {
+                const int e = tid + NT * h, i = e % S, q = e / S, s = m * S + i;
+                const double v = q > 0 ? D[i + q * ST] : s == 0 ? beta_l : 0.0;
+                if (s < L && q < L) st(w0 + s + q * cs, v);
+            }
+        }
+        // the whole sweep
+        wait_memory();
+        __syncthreads();
+        if (tid == 0) {
+            stored = 0;
+            __hip_atomic_store(&prog[m], T, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
 }
@@ -578,14 +471,12 @@ __global__ __launch_bounds__(NT) void chase_kernel(ChaseArgs a) {
 // the band is B[i rs + j cs]: rs = 1, cs = ldb for an upper band stored as
 // is, rs = ldb, cs = 1 for the transpose of a lower band.
 __global__ void pack_kernel(const double* B, int64_t rs, int64_t cs, int64_t n, int nb, double* W, int64_t ldw,
-                            int32_t* ctrl, int32_t* prog, int32_t* bar, int nsweeps, int keep_error) {
+                            int32_t* ctrl, int32_t* prog, int32_t* bar, int nsweeps, int group, int keep_error) {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     if (g < G_WORDS && !(keep_error && g == G_ERROR)) ctrl[g] = 0;
-    for (int64_t s = g; s < nsweeps; s += stride) {
-        prog[s] = 0;
-        bar[s] = 0;
-    }
+    for (int64_t s = g; s < (int64_t)nsweeps * group; s += stride) prog[s] = 0;
+    for (int64_t s = g; s < nsweeps; s += stride) bar[s] = 0;
     const int64_t total = ldw * n;
     for (int64_t x = g; x < total; x += stride) {
         const int64_t j = x / ldw;
@@ -672,13 +563,24 @@ __global__ void bisect_kernel(const double* d, const double* e, int64_t n, doubl
 }
 
 // workspace: control words (256 B), the band array (3 nb n doubles), the
-// progress counters and the group barrier counters (one int32 per sweep each)
-inline int64_t ws_prog_off(int64_t n, int nb) { return 256 + (int64_t)3 * nb * n * 8; }
+// members' progress counters and the exchange counters (int32 per sweep and
+// member, and per sweep), the exchange areas
+inline int64_t round256(int64_t b) { return (b + 255) / 256 * 256; }
 
 inline int nsweeps_of(int64_t n, int nb) { return nb <= 1 || n <= 2 ? 0 : (int)(n - 2); }
 
+inline int64_t ws_prog_off(int64_t n, int nb) { return round256(256 + (int64_t)3 * nb * n * 8); }
+inline int64_t ws_bar_off(int64_t n, int nb) {
+    return ws_prog_off(n, nb) + round256((int64_t)nsweeps_of(n, nb) * group_of(nb) * 4);
+}
+inline int64_t ws_xch_off(int64_t n, int nb) {
+    return ws_bar_off(n, nb) + round256((int64_t)nsweeps_of(n, nb) * 4);
+}
+
 inline size_t ws_bytes(int64_t n, int nb) {
-    return (size_t)(ws_prog_off(n, nb) + 2 * (((int64_t)nsweeps_of(n, nb) * 4 + 255) / 256 * 256));
+    const int g = group_of(nb);
+    const int64_t xch = g > 1 && nsweeps_of(n, nb) > 0 ? 8 * nareas_of(g) * area_doubles(nb, g) : 0;
+    return (size_t)(ws_xch_off(n, nb) + xch);
 }
 
 int device_attr(hipDeviceAttribute_t attr, int fallback) {
@@ -705,7 +607,7 @@ namespace bbg {
 
 // The chase after argument checks: band entry (i, j) at B[i rs + j cs].
 int bnd2bd_launch(const double* B, int64_t rs, int64_t cs, int64_t n, int nb, double* d, double* e, void* ws,
-                  double watchdog_s, int group, bool keep_error, void* stream);
+                  double watchdog_s, bool keep_error, void* stream);
 
 }  // namespace bbg
 
@@ -723,13 +625,13 @@ int bb_bnd2bd_group(const double* B, int64_t ldb, int64_t n, int nb, double* d, 
     if (!ws && n > 0) return -7;
     if (ws_bytes < bbg::ws_bytes(n, nb)) return BB_EWORKSPACE;
     if (n == 0) return BB_OK;
-    return bbg::bnd2bd_launch(B, 1, ldb, n, nb, d, e, ws, watchdog_s, group, false, stream);
+    return bbg::bnd2bd_launch(B, 1, ldb, n, nb, d, e, ws, watchdog_s, false, stream);
 }
 
 }  // extern "C"
 
 int bbg::bnd2bd_launch(const double* B, int64_t rs, int64_t cs, int64_t n, int nb, double* d, double* e,
-                       void* ws, double watchdog_s, int group, bool keep_error, void* stream) {
+                       void* ws, double watchdog_s, bool keep_error, void* stream) {
     hipStream_t s = (hipStream_t)stream;
     const int nsw = bbg::nsweeps_of(n, nb);
     bbg::ChaseArgs a;
@@ -740,33 +642,29 @@ int bbg::bnd2bd_launch(const double* B, int64_t rs, int64_t cs, int64_t n, int n
     a.nsweeps = nsw;
     a.ctrl = (int32_t*)ws;
     a.prog = (int32_t*)((char*)ws + bbg::ws_prog_off(n, nb));
-    a.bar = a.prog + ((int64_t)nsw * 4 + 255) / 256 * 64;
+    a.bar = (int32_t*)((char*)ws + bbg::ws_bar_off(n, nb));
+    a.xch = (double*)((char*)ws + bbg::ws_xch_off(n, nb));
+    a.group = bbg::group_of(nb);
+    a.nareas = bbg::nareas_of(a.group);
     const double khz = (double)bbg::device_attr(hipDeviceAttributeWallClockRate, 100000);
     a.watchdog_ticks = (int64_t)((watchdog_s > 0 ? watchdog_s : 30.0) * khz * 1000.0);
     const int cus = bbg::device_attr(hipDeviceAttributeMultiprocessorCount, 256);
     const int64_t total = a.ldw * n;
     int blocks = (int)std::min<int64_t>((total + 255) / 256, 8 * (int64_t)cus);
     hipLaunchKernelGGL(bbg::pack_kernel, dim3(blocks < 1 ? 1 : blocks), dim3(256), 0, s, B, rs, cs, n, nb, a.W,
-                       a.ldw, a.ctrl, a.prog, a.bar, nsw, keep_error ? 1 : 0);
+                       a.ldw, a.ctrl, a.prog, a.bar, nsw, a.group, keep_error ? 1 : 0);
     if (hipGetLastError() != hipSuccess) return BB_EHIP;
-    // nb > GROUP_NB: a group of ceil(nb / 16) workgroups a sweep, so that a
-    // member takes about 32 rows of the right update and one 32-column chunk
-    // of the left one (measured at n = 16384: nb = 256 1.35 s with 16
-    // workgroups a sweep, 1.60 s with 8, 2.64 s with 4; nb = 128 1.01 s with
-    // 8, 1.06 s with 4, 1.58 s with 12); the grid holds whole groups, at
-    // least one
-    a.group = 1;
-    if (nb > bbg::GROUP_NB) {
-        a.group = std::min(std::min((nb + 15) / 16, bbg::GROUP_MAX), cus);
-        if (group > 0) a.group = std::min(group, cus);
-    }
     if (nsw > 0) {
-        const int grid = nb <= bbg::LDS_NB ? std::min(nsw, cus)
-                                           : (int)std::min<int64_t>((int64_t)nsw * a.group, cus / a.group * a.group);
-        if (nb <= bbg::LDS_NB)
-            hipLaunchKernelGGL(bbg::chase_kernel<true>, dim3(grid), dim3(bbg::NT), 0, s, a);
-        else
-            hipLaunchKernelGGL(bbg::chase_kernel<false>, dim3(grid), dim3(bbg::NT), 0, s, a);
+        // whole groups, at least one, one workgroup a CU (MAX_WG at most: the
+        // exchange areas are counted for that)
+        const int wg = std::min(cus, bbg::MAX_WG);
+        if (wg < a.group) return BB_ENOTSUP;
+        const dim3 grid((unsigned)std::min<int64_t>((int64_t)nsw * a.group, wg / a.group * a.group));
+        switch (bbg::width_of(nb)) {
+            case 64: hipLaunchKernelGGL(bbg::chase_kernel<64>, grid, dim3(bbg::NT), 0, s, a); break;
+            case 128: hipLaunchKernelGGL(bbg::chase_kernel<128>, grid, dim3(bbg::NT), 0, s, a); break;
+            default: hipLaunchKernelGGL(bbg::chase_kernel<256>, grid, dim3(bbg::NT), 0, s, a); break;
+        }
         if (hipGetLastError() != hipSuccess) return BB_EHIP;
     }
     hipLaunchKernelGGL(bbg::extract_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a.W, a.ldw, n,
@@ -838,8 +736,8 @@ int bb_ge2val(void* A, int64_t m, int64_t n, int64_t lda, int nb, int tree, int 
     // m >= n: upper band in the leading n x n part; m < n: lower band in the
     // leading m x m part, chased as its transpose
     const double* B = (const double*)A;
-    rc = m >= n ? bbg::bnd2bd_launch(B, 1, lda, k, nb, d, e, ws, opts ? opts->watchdog_s : 0.0, 0, true, stream)
-                : bbg::bnd2bd_launch(B, lda, 1, k, nb, d, e, ws, opts ? opts->watchdog_s : 0.0, 0, true, stream);
+    rc = m >= n ? bbg::bnd2bd_launch(B, 1, lda, k, nb, d, e, ws, opts ? opts->watchdog_s : 0.0, true, stream)
+                : bbg::bnd2bd_launch(B, lda, 1, k, nb, d, e, ws, opts ? opts->watchdog_s : 0.0, true, stream);
     if (rc != BB_OK) return rc;
     return bb_bd2val(d, e, k, sigma, stream);
 }

@@ -198,6 +198,22 @@ def test_bnd2bd_result_does_not_depend_on_group_size(bb, n, nb):
     assert np.max(np.abs(np.abs(res[0][1].cpu().numpy()) - np.abs(eo))) <= tol
 
 
+@pytest.mark.parametrize("n,nb", [(3, 64), (65, 64), (67, 33), (130, 128), (194, 97), (260, 129), (273, 255),
+                                  (514, 256)])
+def test_chase_slices_at_their_edges(bb, n, nb):
+    """Quadrants of 64, 128 and 256 columns, one to sixteen members: bandwidths
+    one below, at and one above a slice or a width, last blocks of one row, of
+    one entry and of less than a slice."""
+    print("case chase edges", n, nb, flush=True)
+    A = band_input("square", n, nb, 7500 + n + nb)
+    S, ld = colmajor(A)
+    d, e = bb.bnd2bd(S, ld, n, nb, watchdog_s=20.0)
+    do, eo = og.bnd2bd(A, nb)
+    tol = 50 * n * EPS * np.linalg.norm(og.upper_band(A, n, nb))
+    assert np.max(np.abs(np.abs(d.cpu().numpy()) - np.abs(do))) <= tol
+    assert np.max(np.abs(np.abs(e.cpu().numpy()) - np.abs(eo))) <= tol
+
+
 def test_bnd2bd_group_out_of_range(bb):
     S = torch.zeros(10, 10, dtype=torch.float64, device="cuda")
     with pytest.raises(bb.BidiagError):
