@@ -33,9 +33,9 @@
 //
 // BD2VAL.  The singular values of the bidiagonal (d, e) are the positive
 // eigenvalues of the 2n x 2n Golub-Kahan matrix, symmetric tridiagonal with
-// a zero diagonal and off-diagonal d1, e1, d2, ..., dn.  A Sturm count (the
-// signs of the pivots of T - x I, safeguarded against zero pivots) gives the
-// number of singular values below x; a group of lanes narrows the interval
+// a zero diagonal and off-diagonal d1, e1, d2, ..., dn; its pivots in pairs
+// are those of B^T B - x^2 I.  A Sturm count (their signs, by a recurrence
+// without divisions) gives the number of singular values below x; a group of lanes narrows the interval
 // of one singular value by multisection, so all n are found at once (the
 // bisection method of the paper's list of BD2VAL methods, chosen over the
 // serial bidiagonal QR for its parallelism).
@@ -52,6 +52,8 @@ namespace bbg {
 
 constexpr int NT = 512;                 // threads of the chase kernel (8 waves)
 constexpr int NW = NT / 64;
+constexpr int BT = 256;                 // threads of a bisection workgroup
+constexpr int MS_LANES = 1 << 16;       // lanes of the bisection: one wave a SIMD
 constexpr int MAX_NB = 256;
 constexpr int GROUP_MAX = 16;
 constexpr int SLICE = 4096;             // entries of a member's slice of one quadrant
@@ -492,62 +494,130 @@ __global__ void extract_kernel(const double* W, int64_t ldw, int64_t n, int nb, 
     if (i + 1 < n) e[i] = W[(2 * nb - 2) + (i + 1) * ldw];
 }
 
-// Number of singular values of (d, e) below x > 0: the negative pivots of
-// T_GK - x I, less the n eigenvalues -sigma_i that are always below x.
-__device__ __forceinline__ int64_t sturm_below(const double* d, const double* e, int64_t n, double x,
-                                               double pivmin) {
-    double q = -x;                   // the first pivot
-    if (fabs(q) < pivmin) q = -pivmin;
-    int64_t cnt = 1;
-    for (int64_t i = 0; i < n; ++i) {
-        const double di = d[i];
-        q = -x - (di * di) / q;
-        if (fabs(q) < pivmin) q = -pivmin;
-        cnt += q < 0.0;
-        if (i + 1 < n) {
-            const double ei = e[i];
-            q = -x - (ei * ei) / q;
-            if (fabs(q) < pivmin) q = -pivmin;
-            cnt += q < 0.0;
-        }
-    }
-    return cnt - n;
+// Largest of v over the workgroup, in every thread; red holds a value a wave.
+__device__ __forceinline__ double block_max(double v, double* red) {
+#pragma unroll
+    for (int o = 1; o < 64; o *= 2) v = fmax(v, __shfl_xor(v, o, 64));
+    __syncthreads();
+    if (threadIdx.x % 64 == 0) red[threadIdx.x / 64] = v;
+    __syncthreads();
+    v = red[0];
+#pragma unroll
+    for (int w = 1; w < BT / 64; ++w) v = fmax(v, red[w]);
+    return v;
+}
+
+// One pivot of B^T B - x^2 I as the quotient of successive M: with
+// t = N / M the pivot is d^2 + t and the next t is e^2 t / pivot - x^2, so
+//     M' = d^2 M + N,   N' = e^2 N - x^2 M'
+// with no division; the pivot's sign is the change of M's.
+__device__ __forceinline__ void sturm_step(double2 de, double x2, double& M, double& N, uint32_t& signs) {
+    const double Mn = fma(de.x, M, N);
+    N = fma(-x2, Mn, de.y * N);
+    M = Mn;
+    signs = __builtin_amdgcn_alignbit(signs, (uint32_t)(__builtin_bit_cast(uint64_t, Mn) >> 32), 31);
+}
+
+// M and N by the power of two that brings the larger to [1, 2).
+__device__ __forceinline__ void sturm_scale(double& M, double& N) {
+    const uint32_t hm = (uint32_t)(__builtin_bit_cast(uint64_t, M) >> 32) & 0x7FFFFFFFu;
+    const uint32_t hn = (uint32_t)(__builtin_bit_cast(uint64_t, N) >> 32) & 0x7FFFFFFFu;
+    const uint32_t h = (hm > hn ? hm : hn) & 0x7FF00000u;
+    const double f = __builtin_bit_cast(double, (uint64_t)((2046u << 20) - h) << 32);
+    M *= f;
+    N *= f;
 }
 
 // MS lanes per singular value (multisection): each round, lane l counts
 // below x_l = lo + (l+1)(hi-lo)/(MS+1), and the interval shrinks to the
 // one between the largest x with at most s values below it and the
 // smallest x with more, a factor MS+1 a round (13 rounds to full precision
-// at MS = 16, against 53 for bisection), with MS times the lanes.  The host
-// picks MS so that about MS_LANES lanes run (measured: n = 16384 76 ms at
-// MS = 8, 92 ms at 4 and 16; n = 4096 13 ms at 16 or 32, 23 ms at 4).
-constexpr int MS_LANES = 1 << 17;
+// at MS = 16, against 53 for bisection), with MS times the lanes.
+//
+// The entries are scaled by a power of two to at most one and squared once
+// per staging, in LDS, where every lane reads the same pair; squares below
+// 2^-124 are raised to it (entries by 2^-62 of the largest at most, a
+// thousandth of the bisection's own 2^-52), so the map of (M, N) a step makes
+// (determinant d^2 e^2) takes neither both to zero nor, in the four steps
+// between scalings, to underflow.  Every rounding is a relative change of one
+// d^2, e^2 or x^2, as in the recurrence with divisions.
+//
+// What bounds it: a round is a chain of n steps of two dependent FMAs, and
+// the lanes of all values fill the chip at one wave a SIMD; a step issues
+// about 28 cycles (three FP64 operations, the sign, a quarter of a scaling;
+// measured 39 at n = 16384, with the staging).  Against two divisions a pair
+// of pivots on twice the lanes: n = 2000 5.6 -> 0.43 ms, 8192 29.5 -> 2.4 ms,
+// 16384 75.9 -> 6.1 ms, 33000 255 -> 28 ms.
+constexpr int STAGE = 4096;             // pairs staged at a time (64 KiB, two workgroups a CU)
 
 template <int MS>
-__global__ void bisect_kernel(const double* d, const double* e, int64_t n, double* sigma) {
+__global__ __launch_bounds__(BT) void bisect_kernel(const double* d, const double* e, int64_t n, double* sigma) {
     static_assert(64 % MS == 0, "a value's lanes lie in one wave");
-    const int64_t gt = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ double2 pair[STAGE];
+    __shared__ double red[BT / 64];
+    const int64_t gt = (int64_t)blockIdx.x * BT + threadIdx.x;
     const int64_t j = gt / MS;
     const int lane = (int)(gt % MS);
-    if (j >= n) return;                 // whole groups leave together (n MS threads are a multiple of MS)
-    // Gershgorin bound of T_GK and the pivot floor
-    double amax = 0.0, bound = 0.0, prev = 0.0;
-    for (int64_t i = 0; i < n; ++i) {
+    // largest entry and half the Gershgorin bound of the Golub-Kahan matrix
+    double amax = 0.0, half = 0.0, bad = 0.0;
+    for (int64_t i = threadIdx.x; i < n; i += BT) {
         const double di = fabs(d[i]);
-        const double ei = i + 1 < n ? fabs(e[i]) : 0.0;
-        bound = fmax(bound, fmax(prev + di, di + ei));
+        const double ei = i + 1 < n ? fabs(e[i]) : 0.0, ep = i > 0 ? fabs(e[i - 1]) : 0.0;
+        if (di != di || ei != ei) bad = 1.0;
+        half = fmax(half, 0.5 * di + 0.5 * fmax(ei, ep));
         amax = fmax(amax, fmax(di, ei));
-        prev = ei;
     }
-    const double pivmin = DBL_MIN * fmax(1.0, amax * amax);
-    const int64_t s = n - 1 - j;     // sigma[j] is the s-th smallest (decreasing order)
-    double lo = 0.0, hi = bound * (1.0 + 4.0 * DBL_EPSILON) + pivmin;
+    amax = block_max(amax, red);
+    half = block_max(half, red);
+    bad = block_max(bad, red);
+    if (bad != 0.0 || amax == 0.0 || amax > DBL_MAX) {      // NaN, zero or infinity throughout
+        if (lane == 0 && j < n) sigma[j] = bad != 0.0 ? __builtin_nan("") : amax;
+        return;
+    }
+    int ex;
+    (void)frexp(amax, &ex);             // entries times 2^-ex are at most one
+    const double bound = ldexp(half, 1 - ex);
     const double abstol = DBL_EPSILON * bound;
+    double lo = 0.0, hi = bound * (1.0 + 4.0 * DBL_EPSILON);
+    const int64_t s = n - 1 - j;        // sigma[j] is the s-th smallest (decreasing order)
+    bool active = j < n;
     for (int it = 0; it < 128; ++it) {
-        if (hi - lo <= fmax(abstol, 2.0 * DBL_EPSILON * hi)) break;
+        active = active && hi - lo > fmax(abstol, 2.0 * DBL_EPSILON * hi);
+        if (!__syncthreads_or(active)) break;
         const double x = lo + (hi - lo) * (double)(lane + 1) / (double)(MS + 1);
+        const double x2 = x * x;
+        const bool any = __builtin_amdgcn_ballot_w64(active) != 0;
+        double M = 1.0, N = -x2;
+        uint32_t signs = 0;             // the latest signs of M, the newest lowest
+        int cnt = 0;
+        for (int64_t c = 0; c < n; c += STAGE) {
+            const int len = (int)(n - c < STAGE ? n - c : STAGE);
+            if (it == 0 || n > STAGE) {
+                __syncthreads();
+                for (int i = threadIdx.x; i < len; i += BT) {
+                    const double di = ldexp(d[c + i], -ex), ei = c + i + 1 < n ? ldexp(e[c + i], -ex) : 0.0;
+                    pair[i] = {fmax(di * di, 0x1p-124), fmax(ei * ei, 0x1p-124)};
+                }
+                __syncthreads();
+            }
+            if (!any) continue;
+            int i = 0;
+            for (; i + 16 <= len; i += 16) {
+#pragma unroll
+                for (int u = 0; u < 16; ++u) {
+                    sturm_step(pair[i + u], x2, M, N, signs);
+                    if (u % 4 == 3) sturm_scale(M, N);
+                }
+                cnt += __builtin_popcount((signs ^ signs >> 1) & 0xFFFFu);
+            }
+            for (; i < len; ++i) {
+                sturm_step(pair[i], x2, M, N, signs);
+                sturm_scale(M, N);
+                cnt += (signs ^ signs >> 1) & 1u;
+            }
+        }
         const bool inside = x > lo && x < hi;
-        const bool below = inside && sturm_below(d, e, n, x, pivmin) <= s;   // x <= sigma_j
+        const bool below = inside && cnt <= s;                  // x <= sigma_j
         double nlo = below ? x : lo;
         double nhi = inside && !below ? x : hi;
 #pragma unroll
@@ -555,11 +625,13 @@ __global__ void bisect_kernel(const double* d, const double* e, int64_t n, doubl
             nlo = fmax(nlo, __shfl_xor(nlo, o, 64));
             nhi = fmin(nhi, __shfl_xor(nhi, o, 64));
         }
-        if (nlo >= nhi || (nlo == lo && nhi == hi)) break;   // counts out of order, or no progress
-        lo = nlo;
-        hi = nhi;
+        if (nlo >= nhi || (nlo == lo && nhi == hi)) active = false;     // counts out of order, or no progress
+        if (active) {
+            lo = nlo;
+            hi = nhi;
+        }
     }
-    if (lane == 0) sigma[j] = 0.5 * (lo + hi);
+    if (lane == 0 && j < n) sigma[j] = ldexp(0.5 * (lo + hi), ex);
 }
 
 // workspace: control words (256 B), the band array (3 nb n doubles), the
@@ -685,15 +757,21 @@ int bb_bd2val(const double* d, const double* e, int64_t n, double* sigma, void* 
     if (!e && n > 1) return -2;
     if (!sigma && n > 0) return -4;
     if (n == 0) return BB_OK;
-    int ms = 4;
-    while (ms < 32 && n * ms < bbg::MS_LANES) ms *= 2;
-    const dim3 grid((unsigned)((n * ms + 255) / 256));
+    // as many lanes a value as leave one wave a SIMD (rounds go with
+    // 1 / log2(ms + 1), a second wave on a SIMD doubles their time: n = 9000
+    // takes 3.4 ms at 4, where half the SIMDs idle, 16385 8.6 ms at 2)
+    int ms = 1;
+    while (ms < 64 && n * 2 * ms <= bbg::MS_LANES) ms *= 2;
+    const dim3 grid((unsigned)((n * ms + bbg::BT - 1) / bbg::BT)), block(bbg::BT);
     hipStream_t s = (hipStream_t)stream;
     switch (ms) {
-        case 4: hipLaunchKernelGGL(bbg::bisect_kernel<4>, grid, dim3(256), 0, s, d, e, n, sigma); break;
-        case 8: hipLaunchKernelGGL(bbg::bisect_kernel<8>, grid, dim3(256), 0, s, d, e, n, sigma); break;
-        case 16: hipLaunchKernelGGL(bbg::bisect_kernel<16>, grid, dim3(256), 0, s, d, e, n, sigma); break;
-        default: hipLaunchKernelGGL(bbg::bisect_kernel<32>, grid, dim3(256), 0, s, d, e, n, sigma); break;
+        case 1: hipLaunchKernelGGL(bbg::bisect_kernel<1>, grid, block, 0, s, d, e, n, sigma); break;
+        case 2: hipLaunchKernelGGL(bbg::bisect_kernel<2>, grid, block, 0, s, d, e, n, sigma); break;
+        case 4: hipLaunchKernelGGL(bbg::bisect_kernel<4>, grid, block, 0, s, d, e, n, sigma); break;
+        case 8: hipLaunchKernelGGL(bbg::bisect_kernel<8>, grid, block, 0, s, d, e, n, sigma); break;
+        case 16: hipLaunchKernelGGL(bbg::bisect_kernel<16>, grid, block, 0, s, d, e, n, sigma); break;
+        case 32: hipLaunchKernelGGL(bbg::bisect_kernel<32>, grid, block, 0, s, d, e, n, sigma); break;
+        default: hipLaunchKernelGGL(bbg::bisect_kernel<64>, grid, block, 0, s, d, e, n, sigma); break;
     }
     return hipGetLastError() == hipSuccess ? BB_OK : BB_EHIP;
 }

@@ -214,6 +214,50 @@ def test_chase_slices_at_their_edges(bb, n, nb):
     assert np.max(np.abs(np.abs(e.cpu().numpy()) - np.abs(eo))) <= tol
 
 
+@pytest.mark.parametrize("n", [1, 3, 15, 16, 17, 1024, 1025, 4096, 4097, 4113])
+@pytest.mark.parametrize("scale", [1.0, 1e200, 1e-200])
+def test_bd2val_counts_at_their_edges(bb, n, scale):
+    """Lane groups of 64 down to 8, blocks of 16 steps with and without a rest,
+    one and two stagings; zeros in d and e, equal and graded entries, squares
+    beyond the exponent range: with e = 0 the values are |d|, within the
+    interval the bisection stops at (eps (|d| + max |d|), halved) and the floor of the
+    squares; with e, the norm and the values of the first 400 rows."""
+    print("case bd2val counts", n, scale, flush=True)
+    rng = np.random.default_rng(7700 + n)
+    d = rng.standard_normal(n) * 10.0 ** rng.uniform(-14, 0, n)
+    d[::5] = 0.0
+    d[1::7] = 0.25
+    d[-1] = 1.0
+    e = np.zeros(max(n - 1, 1))
+    gpu = lambda a: torch.from_numpy(a * scale).cuda()    # noqa: E731
+    s = bb.bd2val(gpu(d), gpu(e)[:n - 1]).cpu().numpy() / scale
+    assert np.max(np.abs(s - np.sort(np.abs(d))[::-1])) <= 4 * EPS
+    m = min(n, 400)
+    e = rng.standard_normal(max(n - 1, 1)) * 10.0 ** rng.uniform(-14, 0, max(n - 1, 1))
+    e[::6] = 0.0
+    B = np.diag(d[:m]) + np.diag(e[:m - 1], 1)
+    s = bb.bd2val(gpu(d[:m]), gpu(e)[:m - 1]).cpu().numpy() / scale
+    ref = np.linalg.svd(B, compute_uv=False)
+    assert np.max(np.abs(s - ref)) <= 50 * m * EPS * ref[0]
+    s = bb.bd2val(gpu(d), gpu(e)[:n - 1]).cpu().numpy() / scale
+    fro = np.sum(d * d) + np.sum(e[:n - 1] ** 2)
+    assert np.all(s[:-1] >= s[1:] - 4 * EPS * s[0])
+    assert abs(np.sum(s * s) - fro) <= 50 * n * EPS * fro
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan"), 0.0])
+def test_bd2val_of_no_finite_bound(bb, value):
+    """All zero gives zeros; an infinity or a NaN anywhere shows in every value."""
+    d, e = torch.ones(70, dtype=torch.float64, device="cuda"), torch.ones(69, dtype=torch.float64, device="cuda")
+    if value == 0.0:
+        d, e = 0 * d, 0 * e
+    else:
+        e[68] = value
+    s = bb.bd2val(d, e)
+    assert torch.equal(torch.nan_to_num(s, nan=-1.0, posinf=-2.0),
+                       torch.full_like(s, {0.0: 0.0}.get(value, -2.0 if value == float("inf") else -1.0)))
+
+
 def test_bnd2bd_group_out_of_range(bb):
     S = torch.zeros(10, 10, dtype=torch.float64, device="cuda")
     with pytest.raises(bb.BidiagError):
