@@ -269,7 +269,7 @@ def ge2val_stage(bb, torch, np, S, m, n, nb, s_ref, e2bnd_ms):
             "sigma_max_rel_err": err, "tol": 50 * n * np.finfo(np.float64).eps,
             "bnd2bd_roofline": {"bound": "hbm", "achieved": round(gbs, 2), "peak": 8000.0, "unit": "GB/s",
                                 "frac": round(gbs / 8000.0, 5), "traffic": chase_traffic(n, nb),
-                                "kernel": "chase_kernel<%d>" % (64 if nb <= 64 else 128 if nb <= 128 else 256),
+                                "kernel": "hold_kernel",
                                 "algorithmic_bytes": nbytes}}
 
 

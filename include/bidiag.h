@@ -437,16 +437,20 @@ int bb_choose(int64_t m, int64_t n, int nb, const bb_opts* opts, int* tree, int*
  * only entries with 0 <= j - i <= nb are read, B is not written) to upper
  * bidiagonal form U^T B V (U, V orthogonal, V e1 = e1, neither formed) by
  * two-sided Householder bulge chasing, one row per sweep, the sweeps
- * pipelined over the GPU in one persistent launch (for nb > 64 each sweep
- * is run by a group of workgroups that hold its rows in slices).  Writes the diagonal
+ * pipelined over the GPU in one persistent launch.  Up to n = 768 nb (nb <=
+ * 32), 512 nb (64), 256 nb (128), 64 nb (256) and while that many workgroups
+ * find room within 2 ms, workgroups hold the band's blocks in registers and
+ * the sweeps pass through them; else groups of workgroups run the sweeps over
+ * a band array.  The two differ in rounding.  Writes the diagonal
  * d[0..n-1] and the superdiagonal e[0..n-2] (device).  The diagonal and
  * superdiagonal are those of the Golub-Kahan bidiagonalization of B started
  * at e1, so they are unique up to signs.
- * ws: device workspace of bb_bnd2bd_workspace bytes (control words, the band
+ * ws: device workspace of bb_bnd2bd_workspace bytes (control words, the
+ * held blocks' messages, and for the other way the band
  * with room for the fill, 24 nb n bytes, a progress counter per sweep and
  * member of its group, an exchange counter per sweep and the groups' exchange
- * areas), overwritten.  watchdog_s: seconds a sweep may wait for the one
- * before it (0 = 30); when it fires the launch stops and bb_poll_error(ws)
+ * areas), overwritten.  watchdog_s: seconds a sweep (or a
+ * held block) may wait for the one before it (0 = 30); when it fires the launch stops and bb_poll_error(ws)
  * reports BB_ETIMEOUT.  Arguments: B (1), ldb >= max(1, n) (2), n >= 0 (3),
  * 1 <= nb <= 256 (4), d (5), e (6), ws (7), ws_bytes (8, BB_EWORKSPACE when
  * too small), watchdog_s (9), stream (10).  Asynchronous.
@@ -456,8 +460,7 @@ int bb_bnd2bd(const double* B, int64_t ldb, int64_t n, int nb, double* d, double
               size_t ws_bytes, double watchdog_s, void* stream);
 /* bb_bnd2bd_group -- bb_bnd2bd with a wish for the number of workgroups that
  * run each sweep: group (10) in 0..16, -10 out of range.  The launch uses the
- * number its slices need (1 for nb <= 64, ceil(nb / 32) for nb <= 128, else
- * ceil(nb / 16)) whatever is asked for; the result does not depend on it. */
+ * number it needs whatever is asked for; the result does not depend on it. */
 int bb_bnd2bd_group(const double* B, int64_t ldb, int64_t n, int nb, double* d, double* e, void* ws,
                     size_t ws_bytes, double watchdog_s, int group, void* stream);
 

@@ -2,10 +2,7 @@
 // and 6.2): BND2BD, band to bidiagonal by bulge chasing, and BD2VAL,
 // singular values of the bidiagonal, on gfx950.
 //
-// BND2BD.  The n x n upper band of bandwidth nb is copied into a band work
-// array with room for the fill of the chase (nb - 1 diagonals below the
-// main one, 2 nb - 1 above), column-major by diagonal offset:
-//     W[(i - j + 2 nb - 1) + j * 3 nb]  holds entry (i, j).
+// BND2BD.  An n x n upper band of bandwidth nb.
 // Sweep k clears row k beyond its superdiagonal and chases the bulge this
 // makes down the band, one block of nb columns per step.  Step t of sweep k
 // works at column c = k + 1 + t nb:
@@ -20,6 +17,14 @@
 // write, so it may start once sweep k has finished step t+1: two steps
 // separate consecutive sweeps, and about n / (2 nb) sweeps run at once.
 //
+// Where the band fits in the registers of the chip, it is held there and the
+// sweeps pass through it (hold_kernel); else, and when the compute units are
+// not free for that, the sweeps pass over the band array (chase_kernel):
+//
+// the band is copied into a band work array with room for the fill of the
+// chase (nb - 1 diagonals below the main one, 2 nb - 1 above), column-major by
+// diagonal offset:
+//     W[(i - j + 2 nb - 1) + j * 3 nb]  holds entry (i, j).
 // One persistent launch: each group of workgroups takes the next sweep
 // (tickets from an atomic counter, so a sweep is only ever waited for by a
 // later one that running workgroups hold: no deadlock for any grid) and runs
@@ -57,7 +62,7 @@ constexpr int MS_LANES = 1 << 16;       // lanes of the bisection: one wave a SI
 constexpr int MAX_NB = 256;
 constexpr int GROUP_MAX = 16;
 constexpr int SLICE = 4096;             // entries of a member's slice of one quadrant
-enum : int { G_ERROR = 1, G_HEAD = 32, G_WORDS = 64 };
+enum : int { G_ERROR = 1, G_MET = 2, G_RUNNING = 3, G_HEAD = 32, G_WORDS = 64 };
 
 // Quadrant width the kernel is compiled for (64, 128, 256), rows of a
 // member's slice and workgroups (members) per sweep.
@@ -87,6 +92,7 @@ struct ChaseArgs {
     int group;            // workgroups per sweep
     int nareas;
     int64_t watchdog_ticks;
+    const int32_t* met;   // the meeting of hold_kernel before this launch, or null
 };
 
 __host__ __device__ inline int64_t nsteps(int64_t n, int nb, int64_t k) {
@@ -111,6 +117,8 @@ __device__ __forceinline__ double ld(const double* p) {
 __device__ __forceinline__ int aload(const int32_t* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+
+enum : int { MET_GO = 1, MET_GIVE_UP = 2 };     // the word G_MET
 
 // A barrier for LDS traffic only: it waits for this wave's LDS operations,
 // not for its global accesses, so stores stay in flight across it.
@@ -247,6 +255,7 @@ __global__ __launch_bounds__(NT) void chase_kernel(ChaseArgs a) {
     const int lcol = (w % (NW / 2)) * C + lane % C, lp = lane / C;
     const bool low = w < NW / 2;
     if (tid == 0) stored = 0;
+    if (a.met && aload(a.met) == MET_GO) return;
 
     for (;;) {
         // ticket = sweep * G + member: a group's members are consecutive
@@ -466,6 +475,474 @@ __global__ __launch_bounds__(NT) void chase_kernel(ChaseArgs a) {
     }
 }
 
+// ---- the chase with the band held in registers -----------------------------
+//
+// When every block row of the window has workgroups of its own, nothing of
+// the band has to move: block b keeps, through all sweeps, the nb rows below
+// row c = k + 1 + b nb and in them the columns c .. c + nb - 1 (D) and
+// c + nb .. c + 2 nb - 1 (Q), in registers, and sweeps pass through the
+// blocks.  In sweep k block b
+//   * receives from block b - 1 the row that the right reflector clears
+//     (its columns are D's), forms the reflector and applies it to D;
+//   * forms the left reflector of D's first column and applies it to D and Q;
+//   * sends the new first row of Q to block b + 1, as the row to be cleared
+//     there, and applies its reflector to its own other rows of Q;
+//   * moves its window one row and one column on: its first row, finished for
+//     this block, goes to block b - 1 as that one's new last row (from block
+//     0 it is the row the next sweep clears), the last row comes from b + 1.
+// Rows and columns are held in rings of nb: row or column c + i of sweep k,
+// of D and of Q, is in slot (k + i) mod nb, so the window moves without moving
+// anything but one column of Q, which becomes D's in the same lanes, and the
+// messages, indexed by slot, need no rotation.  Rows and columns past the
+// matrix are zeros and stay zeros; a zero column or row gives the identity.
+//
+// Lane l holds the columns of slots l + 64 h, wave w and register i row slot
+// 8 i + w (+ 8 RW m for member m of a group, nb > 128).  Row sums go over the
+// lanes of a wave; column sums over a wave's registers, then the waves (LDS)
+// and, in a group, the members.
+//
+// A message is its values: an inbox word holds MARK, a NaN no arithmetic
+// gives (and senders replace), until the value comes; the receiver polls the
+// words it needs and sets them back.  Two inboxes by parity are enough: what
+// a receiver reads in sweep k is set back before it leaves sweep k + 1, and
+// no value of sweep k + 2 can be sent to it before that.
+//
+// What bounds it: the chain of 2 n steps, a message (about 1.3 us from the
+// store to the polling load that sees it) and the step's own chain (reflector,
+// row sums, column sums over the waves, reflector) each; the rest of a step's
+// work falls into the time the block waits anyway, as a block works in every
+// other step only.  A step takes 1.8 us (nb = 32), 2.1 (64), 2.9 (128) and 4.6
+// (256, with the exchange between four members).  Against the chase by sweeps
+// below: 2000 at nb = 64 24.7 -> 8.0 ms, 8192 at nb = 256 232 -> 76.5 ms, 16384
+// at nb = 128 333 -> 96.4 ms, 9000 at nb = 16 99 -> 40 ms.
+//
+// All workgroups have to run at once, so they meet first; if they have not
+// met within MEET_SECONDS (other work holds compute units) the launch ends
+// without having done anything, and the chase by sweeps, which needs no more
+// than one running group, does the work.
+constexpr uint64_t MARK = 0x7FF4B1D1A60CA11Eull;
+constexpr double MEET_SECONDS = 2e-3;
+
+struct HoldArgs {
+    const double* B;
+    int64_t rs, cs, n;
+    int nb;
+    int group;            // workgroups per block
+    int32_t* ctrl;
+    double* box;          // inboxes, per workgroup
+    double* d;
+    double* e;
+    int64_t watchdog_ticks, meet_ticks;
+};
+
+// An inbox: two rows to clear, two last rows (and a diagonal entry behind
+// each), for groups two sets of the members' column sums and of row 0.
+constexpr int box_row(int ch) { return 64 * ch; }
+constexpr int box_last(int ch) { return 64 * ch + 8; }
+constexpr int box_sums(int ch, int group) { return ch <= 2 ? 0 : (group + 1) * 128 * ch; }
+constexpr int box_doubles(int ch, int group) { return 2 * (box_row(ch) + box_last(ch) + box_sums(ch, group)); }
+
+__device__ __forceinline__ bool marked(double v) { return __builtin_bit_cast(uint64_t, v) == MARK; }
+__device__ __forceinline__ void send(double* p, double v) {
+    st(p, v != v ? __builtin_bit_cast(double, 0x7FF8000000000000ull) : v);
+}
+__device__ __forceinline__ void set_back(double* p) { st(p, __builtin_bit_cast(double, MARK)); }
+
+// Called by a whole wave: v[h] = p[h * stride] where use, once none of them
+// is MARK; false when an error was reported or the watchdog fired.
+template <int N>
+__device__ __forceinline__ bool await(const HoldArgs& a, const double* p, int stride, const bool (&use)[N],
+                                      double (&v)[N]) {
+    uint64_t t0 = 0;
+    for (int tries = 0;; ++tries) {
+        bool missing = false;
+#pragma unroll
+        for (int h = 0; h < N; ++h) {
+            v[h] = use[h] ? ld(p + h * stride) : 0.0;
+        }
+#pragma unroll
+        for (int h = 0; h < N; ++h) missing = missing || marked(v[h]);
+        if (__builtin_amdgcn_ballot_w64(missing) == 0) return true;
+        if (tries % 32 == 0) {
+            const uint64_t now = wall_clock64();
+            if (tries == 0) t0 = now;
+            if (tries > 0 && __builtin_amdgcn_readfirstlane(aload(&a.ctrl[G_ERROR])) != 0) return false;
+            if ((int64_t)(now - t0) >= a.watchdog_ticks) {
+                if (threadIdx.x % 64 == 0)
+                    __hip_atomic_store(&a.ctrl[G_ERROR], BB_ETIMEOUT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                return false;
+            }
+        }
+    }
+}
+
+// One thread of each workgroup: whether all of them are running.
+__device__ __forceinline__ bool meet(const HoldArgs& a) {
+    const uint64_t t0 = wall_clock64();
+    int none = 0;
+    if (__hip_atomic_fetch_add(&a.ctrl[G_RUNNING], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+        (int)gridDim.x - 1)
+        __hip_atomic_compare_exchange_strong(&a.ctrl[G_MET], &none, (int)MET_GO, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+    for (;;) {
+        const int met = aload(&a.ctrl[G_MET]);
+        if (met != 0) return met == MET_GO;
+        if ((int64_t)(wall_clock64() - t0) > a.meet_ticks) {
+            none = 0;
+            __hip_atomic_compare_exchange_strong(&a.ctrl[G_MET], &none, (int)MET_GIVE_UP, __ATOMIC_RELAXED,
+                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __builtin_amdgcn_s_sleep(4);
+    }
+}
+
+__device__ __forceinline__ double lane_value(double v, int lane) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_readlane((uint32_t)b, lane);
+    const uint32_t hi = __builtin_amdgcn_readlane((uint32_t)(b >> 32), lane);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
+// Lanes < 32: a summed over l, l ^ 32, the others b (WIDE); by rows of 16
+// lanes: even a, odd b, summed over l, l ^ 16.
+template <bool WIDE>
+__device__ __forceinline__ double fold(double a, double b) {
+    const uint64_t x = __builtin_bit_cast(uint64_t, a), y = __builtin_bit_cast(uint64_t, b);
+    uint64_t p, q;
+    if constexpr (WIDE) {
+        const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)x, (uint32_t)y, false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+        p = (uint64_t)hi[0] << 32 | lo[0], q = (uint64_t)hi[1] << 32 | lo[1];
+    } else {
+        const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)x, (uint32_t)y, false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(x >> 32), (uint32_t)(y >> 32), false, false);
+        p = (uint64_t)hi[0] << 32 | lo[0], q = (uint64_t)hi[1] << 32 | lo[1];
+    }
+    return __builtin_bit_cast(double, p) + __builtin_bit_cast(double, q);
+}
+
+// Sums over the wave of RW = 4, 8 or 16 values a lane, each made uniform:
+// values are paired off while lanes are folded, so half as many are left at
+// each of the first levels.
+template <int RW>
+__device__ __forceinline__ void wave_sums(double (&p)[RW]) {
+    const int lane = threadIdx.x & 63;
+    double q[RW / 4];
+#pragma unroll
+    for (int i = 0; i < RW / 4; ++i)
+        q[i] = fold<false>(fold<true>(p[i], p[i + RW / 2]), fold<true>(p[i + RW / 4], p[i + 3 * RW / 4]));
+    if constexpr (RW == 16) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const bool up = lane & 8;
+            q[i] = (up ? q[i + 2] : q[i]) + dpp<0x128>(up ? q[i] : q[i + 2]);   // row_ror:8
+        }
+        const bool up = lane & 4;
+        q[0] = (up ? q[1] : q[0]) + dpp<0x141>(up ? q[0] : q[1]);               // row_half_mirror
+    } else if constexpr (RW == 8) {
+        const bool up = lane & 8;
+        q[0] = (up ? q[1] : q[0]) + dpp<0x128>(up ? q[0] : q[1]);
+        q[0] += dpp<0x141>(q[0]);
+    } else {
+        q[0] += dpp<0x128>(q[0]);
+        q[0] += dpp<0x141>(q[0]);
+    }
+    q[0] += dpp<0x4E>(q[0]);            // quad_perm:[2,3,0,1]
+    q[0] += dpp<0xB1>(q[0]);            // quad_perm:[1,0,3,2]
+#pragma unroll
+    for (int i = 0; i < RW; ++i) {
+        const int half = i / (RW / 2), r = i % (RW / 2), row = r / (RW / 4), s = r % (RW / 4);
+        const int lane_of = 32 * half + 16 * row + (RW == 16 ? 8 * (s / 2) + 4 * (s % 2) : RW == 8 ? 8 * s : 0);
+        p[i] = lane_value(q[0], lane_of);
+    }
+}
+
+template <int CH, int RW>
+__global__ __launch_bounds__(NT) void hold_kernel(HoldArgs a) {
+    constexpr int NBP = 64 * CH;
+    constexpr int PARTS = NW * CH / 4;          // waves' sums a lane adds: 2, 4, 8
+    constexpr bool GROUPED = CH == 4;
+    __shared__ double part[NW][2 * NBP];        // column sums of each wave
+    __shared__ double total[2 * NBP];           // of the block
+    __shared__ double row0[2][2 * NBP];         // the first row, by parity of the sweep
+    __shared__ int fail[2], go;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (tid == 0) {
+        fail[0] = fail[1] = 0;
+        go = meet(a);
+    }
+    __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(go) == 0) return;
+    const int nb = a.nb, G = GROUPED ? a.group : 1;
+    const int b = (int)blockIdx.x / G, m = (int)blockIdx.x % G;
+    const int size = box_doubles(CH, G);
+    double* box = a.box + (int64_t)blockIdx.x * size;
+    double* box_l = box + 2 * box_row(CH);
+    double* box_x = box_l + 2 * box_last(CH);
+    const int64_t K = a.n - 1 - (int64_t)b * nb, Kn = K - nb;   // sweeps of this block, of the next
+    bool use[CH];
+    double D[RW][CH], Q[RW][CH];
+#pragma unroll
+    for (int h = 0; h < CH; ++h) {
+        use[h] = lane + 64 * h < nb;
+#pragma unroll
+        for (int i = 0; i < RW; ++i) {
+            const int r = 8 * (RW * m + i) + w, q = lane + 64 * h;
+            const int64_t row = 1 + (int64_t)b * nb + r, col = 1 + (int64_t)b * nb + q;
+            const bool in = r < nb && use[h] && row < a.n;
+            D[i][h] = in && col >= row && col < a.n ? a.B[row * a.rs + col * a.cs] : 0.0;
+            Q[i][h] = in && col <= row && col + nb < a.n ? a.B[row * a.rs + (col + nb) * a.cs] : 0.0;
+        }
+    }
+    if (blockIdx.x == 0 && tid == 0) a.d[0] = a.B[0];
+
+    int i0 = 0, ip = 0;                         // slots of the first row and column: of this sweep, of the last
+    for (int64_t k = 0; k < K; ++k) {
+        const int par = (int)(k & 1);
+        bool ok = true;
+        // the last row, which was the first one of the next block
+        const bool takes = k > 0 && k <= Kn && w == ip % 8 && (!GROUPED || m == ip / (8 * RW));
+        if (takes) {
+            double x[CH], diag[1];
+            const bool one[1] = {true};
+            ok = await(a, box_l + (par ^ 1) * box_last(CH) + lane, 64, use, x);
+            ok = ok && await(a, box_l + (par ^ 1) * box_last(CH) + NBP, 0, one, diag);
+            const int reg = ip / 8 % RW;
+#pragma unroll
+            for (int i = 0; i < RW; ++i)
+                if (i == reg) {
+#pragma unroll
+                    for (int h = 0; h < CH; ++h) {
+                        D[i][h] = lane + 64 * h == ip ? diag[0] : 0.0;
+                        Q[i][h] = x[h];
+                        asm volatile("" : "+v"(D[i][h]), "+v"(Q[i][h]));
+                    }
+                }
+        }
+        // the row to clear, its reflector and D (I - tau v v^T)
+        const int l0 = i0 % 64, h0 = i0 / 64;
+        double v[CH];
+        if (b > 0 || k > 0) {
+            ok = await(a, box + par * box_row(CH) + lane, 64, use, v) && ok;
+        } else {
+#pragma unroll
+            for (int h = 0; h < CH; ++h) {
+                const int64_t col = 1 + lane + 64 * h;
+                v[h] = use[h] && col < a.n ? a.B[col * a.cs] : 0.0;
+            }
+        }
+        auto first = [&](const double (&x)[CH]) {       // entry of slot i0, uniform
+            double y = x[0];
+#pragma unroll
+            for (int h = 1; h < CH; ++h) {
+                double z = x[h];
+                asm("" : "+v"(z));              // a value, not an address to choose
+                y = h == h0 ? z : y;
+            }
+            return lane_value(y, l0);
+        };
+        auto clear = [&](double (&x)[CH]) {             // row x becomes the reflector's v
+            double ss = 0.0;
+#pragma unroll
+            for (int h = 0; h < CH; ++h) {
+                const double y = lane + 64 * h == i0 ? 0.0 : x[h];
+                ss = fma(y, y, ss);
+            }
+            const Refl f = reflector(first(x), sum_parts<1>(ss));
+#pragma unroll
+            for (int h = 0; h < CH; ++h) x[h] = lane + 64 * h == i0 ? 1.0 : f.scale * x[h];
+            return f;
+        };
+        auto from_right = [&](double (&M)[RW][CH], const double (&x)[CH], double tau) {
+            double p[RW];
+#pragma unroll
+            for (int i = 0; i < RW; ++i) {
+                p[i] = M[i][0] * x[0];
+#pragma unroll
+                for (int h = 1; h < CH; ++h) p[i] = fma(M[i][h], x[h], p[i]);
+            }
+            wave_sums<RW>(p);
+            double tx[CH];
+#pragma unroll
+            for (int h = 0; h < CH; ++h) tx[h] = -tau * x[h];
+#pragma unroll
+            for (int i = 0; i < RW; ++i)
+#pragma unroll
+                for (int h = 0; h < CH; ++h) M[i][h] = fma(p[i], tx[h], M[i][h]);
+        };
+        const Refl fr = clear(v);
+        from_right(D, v, fr.tau);
+        if (b == 0 && m == 0 && tid == 0) a.e[k] = fr.beta;
+
+        // the first row leaves the registers
+        const bool gives = w == i0 % 8 && (!GROUPED || m == i0 / (8 * RW));
+        if (gives) {
+            const int reg = i0 / 8 % RW;
+#pragma unroll
+            for (int i = 0; i < RW; ++i)
+                if (i == reg) {
+#pragma unroll
+                    for (int h = 0; h < CH; ++h) {
+                        row0[par][lane + 64 * h] = D[i][h];
+                        row0[par][NBP + lane + 64 * h] = Q[i][h];
+                        D[i][h] = Q[i][h] = 0.0;
+                        asm volatile("" : "+v"(D[i][h]), "+v"(Q[i][h]));
+                    }
+                }
+        }
+        // column sums x^T (D, Q), x the first column below the first row
+        double x[RW];
+        {
+            double pd[CH], pq[CH];
+#pragma unroll
+            for (int i = 0; i < RW; ++i) x[i] = first(D[i]);
+#pragma unroll
+            for (int h = 0; h < CH; ++h) {
+                pd[h] = pq[h] = 0.0;
+#pragma unroll
+                for (int i = 0; i < RW; ++i) {
+                    pd[h] = fma(x[i], D[i][h], pd[h]);
+                    pq[h] = fma(x[i], Q[i][h], pq[h]);
+                }
+                part[w][lane + 64 * h] = pd[h];
+                part[w][NBP + lane + 64 * h] = pq[h];
+            }
+        }
+        if (!ok) fail[par] = 1;
+        wait_memory();                          // inbox words set back in the last sweep
+        lds_barrier();
+        if (__builtin_amdgcn_readfirstlane(fail[par]) != 0) return;
+        {
+            const int col = w * 16 * CH + lane % (16 * CH), sub = lane / (16 * CH);
+            double s = 0.0;
+#pragma unroll
+            for (int h = 0; h < PARTS; ++h) s += part[sub * PARTS + h][col];
+            if constexpr (CH == 1) s = sum_rows(s);
+            if constexpr (CH == 2) s = sum_halves(s);
+            if constexpr (GROUPED) {
+                // the members' sums and, from the one that has it, row 0
+                const int64_t slot = par * (int64_t)box_sums(CH, G);
+                const int holder = i0 / (8 * RW);
+                const double r0 = row0[par][col];
+                for (int o = 1; o < G; ++o) {
+                    const int to = m + o < G ? m + o : m + o - G;
+                    double* other = box_x + (int64_t)(to - m) * size + slot;
+                    send(other + m * 2 * NBP + col, s);
+                    if (m == holder) send(other + G * 2 * NBP + col, r0);
+                }
+                bool from[5];
+                double y[5];
+#pragma unroll
+                for (int h = 0; h < 4; ++h) from[h] = h < G && h != m;
+                from[4] = m != holder;
+                // four members at most, row 0 behind them
+                bool ok2 = true;
+                {
+                    const bool f4[4] = {from[0], from[1], from[2], from[3]};
+                    double y4[4], y1[1];
+                    const bool f1[1] = {from[4]};
+                    ok2 = await(a, box_x + slot + col, 2 * NBP, f4, y4);
+                    ok2 = await(a, box_x + slot + G * 2 * NBP + col, 0, f1, y1) && ok2;
+#pragma unroll
+                    for (int h = 0; h < 4; ++h) y[h] = h == m ? s : y4[h];
+                    y[4] = y1[0];
+                }
+#pragma unroll
+                for (int h = 0; h < 4; ++h)
+                    if (from[h]) set_back(box_x + slot + h * 2 * NBP + col);
+                if (from[4]) set_back(box_x + slot + G * 2 * NBP + col);
+                s = ((y[0] + y[1]) + (y[2] + y[3]));
+                if (from[4]) row0[par][col] = y[4];
+                if (!ok2) fail[par] = 1;
+            }
+            if (sub == 0) total[col] = s;
+        }
+        lds_barrier();
+        if (GROUPED && __builtin_amdgcn_readfirstlane(fail[par]) != 0) return;
+
+        // left reflector; the new first row
+        const Refl fl = reflector(row0[par][i0], total[i0]);
+        double td[CH], tq[CH], g[CH], last[CH];
+#pragma unroll
+        for (int h = 0; h < CH; ++h) {
+            const double rd = row0[par][lane + 64 * h], rq = row0[par][NBP + lane + 64 * h];
+            td[h] = fl.tau * fma(fl.scale, total[lane + 64 * h], rd);
+            tq[h] = fl.tau * fma(fl.scale, total[NBP + lane + 64 * h], rq);
+            last[h] = rd - td[h];
+            g[h] = rq - tq[h];
+            td[h] *= -fl.scale;
+            tq[h] *= -fl.scale;
+        }
+        if (w == 0 && k < Kn) {
+            double* to = box + (int64_t)G * size + par * box_row(CH) + lane;
+#pragma unroll
+            for (int h = 0; h < CH; ++h)
+                if (use[h]) send(to + 64 * h, g[h]);
+        }
+        const Refl fg = clear(g);
+        if (w == 1) {
+            if (b > 0) {
+                if (!GROUPED || m == i0 / (8 * RW)) {
+                    double* to = box_l - (int64_t)G * size + par * box_last(CH);
+#pragma unroll
+                    for (int h = 0; h < CH; ++h)
+                        if (use[h]) send(to + lane + 64 * h, lane + 64 * h == i0 ? fg.beta : last[h]);
+                    if (lane == 0) send(to + NBP, fl.beta);
+                }
+            } else {
+                if (k + 1 < K) {
+                    double* to = box + (par ^ 1) * box_row(CH) + lane;
+#pragma unroll
+                    for (int h = 0; h < CH; ++h)
+                        if (use[h]) send(to + 64 * h, lane + 64 * h == i0 ? fg.beta : last[h]);
+                }
+                if (m == 0 && lane == 0) a.d[k + 1] = fl.beta;
+            }
+        }
+        // words read in this sweep are set back
+        if (w == NW - 1 && (b > 0 || k > 0)) {
+#pragma unroll
+            for (int h = 0; h < CH; ++h)
+                if (use[h]) set_back(box + par * box_row(CH) + lane + 64 * h);
+        }
+        if (takes) {
+#pragma unroll
+            for (int h = 0; h < CH; ++h)
+                if (use[h]) set_back(box_l + (par ^ 1) * box_last(CH) + lane + 64 * h);
+            if (lane == 0) set_back(box_l + (par ^ 1) * box_last(CH) + NBP);
+        }
+        // the other rows: from the left, then Q from the right
+#pragma unroll
+        for (int i = 0; i < RW; ++i)
+#pragma unroll
+            for (int h = 0; h < CH; ++h) {
+                D[i][h] = fma(x[i], td[h], D[i][h]);
+                Q[i][h] = fma(x[i], tq[h], Q[i][h]);
+            }
+        from_right(Q, g, fg.tau);
+        // Q's first column becomes D's last
+#pragma unroll
+        for (int h = 0; h < CH; ++h) {
+            const bool moves = lane + 64 * h == i0;
+#pragma unroll
+            for (int i = 0; i < RW; ++i) {
+                D[i][h] = moves ? Q[i][h] : D[i][h];
+                Q[i][h] = moves ? 0.0 : Q[i][h];
+            }
+        }
+        ip = i0;
+        i0 = i0 + 1 < nb ? i0 + 1 : 0;
+    }
+}
+
+// Control words and inboxes before hold_kernel.
+__global__ void hold_init_kernel(int32_t* ctrl, double* box, int64_t words, int keep_error) {
+    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (g < G_WORDS && !(keep_error && g == G_ERROR)) ctrl[g] = 0;
+    for (int64_t i = g; i < words; i += (int64_t)gridDim.x * blockDim.x) box[i] = __builtin_bit_cast(double, MARK);
+}
+
 // Copy the upper band of B into W (zero elsewhere), clear the control words
 // (the error word too unless keep_error: then a status already there, such as
 // the band reduction's in the one-shot pipeline, stops the chase at its
@@ -473,10 +950,12 @@ __global__ __launch_bounds__(NT) void chase_kernel(ChaseArgs a) {
 // the band is B[i rs + j cs]: rs = 1, cs = ldb for an upper band stored as
 // is, rs = ldb, cs = 1 for the transpose of a lower band.
 __global__ void pack_kernel(const double* B, int64_t rs, int64_t cs, int64_t n, int nb, double* W, int64_t ldw,
-                            int32_t* ctrl, int32_t* prog, int32_t* bar, int nsweeps, int group, int keep_error) {
+                            int32_t* ctrl, int32_t* prog, int32_t* bar, int nsweeps, int group, int keep_error,
+                            const int32_t* met) {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    if (g < G_WORDS && !(keep_error && g == G_ERROR)) ctrl[g] = 0;
+    if (met && aload(met) == MET_GO) return;
+    if (g < G_WORDS && g != G_MET && !(keep_error && g == G_ERROR)) ctrl[g] = 0;
     for (int64_t s = g; s < (int64_t)nsweeps * group; s += stride) prog[s] = 0;
     for (int64_t s = g; s < nsweeps; s += stride) bar[s] = 0;
     const int64_t total = ldw * n;
@@ -487,9 +966,10 @@ __global__ void pack_kernel(const double* B, int64_t rs, int64_t cs, int64_t n, 
     }
 }
 
-__global__ void extract_kernel(const double* W, int64_t ldw, int64_t n, int nb, double* d, double* e) {
+__global__ void extract_kernel(const double* W, int64_t ldw, int64_t n, int nb, double* d, double* e,
+                               const int32_t* met) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
+    if (i >= n || (met && aload(met) == MET_GO)) return;
     d[i] = W[(2 * nb - 1) + i * ldw];
     if (i + 1 < n) e[i] = W[(2 * nb - 2) + (i + 1) * ldw];
 }
@@ -649,10 +1129,29 @@ inline int64_t ws_xch_off(int64_t n, int nb) {
     return ws_bar_off(n, nb) + round256((int64_t)nsweeps_of(n, nb) * 4);
 }
 
-inline size_t ws_bytes(int64_t n, int nb) {
+inline int64_t ws_sweep_bytes(int64_t n, int nb) {
     const int g = group_of(nb);
     const int64_t xch = g > 1 && nsweeps_of(n, nb) > 0 ? 8 * nareas_of(g) * area_doubles(nb, g) : 0;
-    return (size_t)(ws_xch_off(n, nb) + xch);
+    return round256(ws_xch_off(n, nb) + xch);
+}
+
+// Workgroups of a block and all inboxes of hold_kernel; none (0) where the
+// blocks do not fit on the chip at once, or nothing is chased.  Workgroups a
+// compute unit: what the registers of the instance allow (72, 88, 200, 224 of
+// 512 a lane and SIMD, two waves a workgroup and SIMD).
+inline int hold_ch(int nb) { return width_of(nb) / 64; }
+inline int hold_group(int nb) { return nb <= 128 ? 1 : (nb + 63) / 64; }
+inline int hold_per_cu(int nb) { return nb <= 32 ? 3 : nb <= 64 ? 2 : 1; }
+inline int64_t hold_workgroups(int64_t n, int nb) {
+    const int64_t wg = (n - 1 + nb - 1) / nb * hold_group(nb);
+    return nsweeps_of(n, nb) > 0 && wg <= MAX_WG * hold_per_cu(nb) ? wg : 0;
+}
+inline int64_t hold_words(int64_t n, int nb) {
+    return hold_workgroups(n, nb) * box_doubles(hold_ch(nb), hold_group(nb));
+}
+
+inline size_t ws_bytes(int64_t n, int nb) {
+    return (size_t)(ws_sweep_bytes(n, nb) + 8 * hold_words(n, nb));
 }
 
 int device_attr(hipDeviceAttribute_t attr, int fallback) {
@@ -721,10 +1220,44 @@ int bbg::bnd2bd_launch(const double* B, int64_t rs, int64_t cs, int64_t n, int n
     const double khz = (double)bbg::device_attr(hipDeviceAttributeWallClockRate, 100000);
     a.watchdog_ticks = (int64_t)((watchdog_s > 0 ? watchdog_s : 30.0) * khz * 1000.0);
     const int cus = bbg::device_attr(hipDeviceAttributeMultiprocessorCount, 256);
+    const int64_t wgs = bbg::hold_workgroups(n, nb);
+    a.met = nullptr;
+    if (wgs > 0 && wgs <= (int64_t)cus * bbg::hold_per_cu(nb)) {
+        bbg::HoldArgs h;
+        h.B = B;
+        h.rs = rs;
+        h.cs = cs;
+        h.n = n;
+        h.nb = nb;
+        h.group = bbg::hold_group(nb);
+        h.ctrl = a.ctrl;
+        h.box = (double*)((char*)ws + bbg::ws_sweep_bytes(n, nb));
+        h.d = d;
+        h.e = e;
+        h.watchdog_ticks = a.watchdog_ticks;
+        h.meet_ticks = (int64_t)(bbg::MEET_SECONDS * khz * 1000.0);
+        const int64_t words = bbg::hold_words(n, nb);
+        hipLaunchKernelGGL(bbg::hold_init_kernel, dim3((unsigned)std::min<int64_t>((words + 255) / 256, cus)),
+                           dim3(256), 0, s, a.ctrl, h.box, words, keep_error ? 1 : 0);
+        if (hipGetLastError() != hipSuccess) return BB_EHIP;
+        const dim3 grid((unsigned)wgs), block(bbg::NT);
+        if (nb <= 32)
+            hipLaunchKernelGGL((bbg::hold_kernel<1, 4>), grid, block, 0, s, h);
+        else if (nb <= 64)
+            hipLaunchKernelGGL((bbg::hold_kernel<1, 8>), grid, block, 0, s, h);
+        else if (nb <= 128)
+            hipLaunchKernelGGL((bbg::hold_kernel<2, 16>), grid, block, 0, s, h);
+        else
+            hipLaunchKernelGGL((bbg::hold_kernel<4, 8>), grid, block, 0, s, h);
+        if (hipGetLastError() != hipSuccess) return BB_EHIP;
+        a.met = &a.ctrl[bbg::G_MET];
+        keep_error = true;
+    }
+    // the chase by sweeps; after a launch above that held the band, these end at once
     const int64_t total = a.ldw * n;
     int blocks = (int)std::min<int64_t>((total + 255) / 256, 8 * (int64_t)cus);
     hipLaunchKernelGGL(bbg::pack_kernel, dim3(blocks < 1 ? 1 : blocks), dim3(256), 0, s, B, rs, cs, n, nb, a.W,
-                       a.ldw, a.ctrl, a.prog, a.bar, nsw, a.group, keep_error ? 1 : 0);
+                       a.ldw, a.ctrl, a.prog, a.bar, nsw, a.group, keep_error ? 1 : 0, a.met);
     if (hipGetLastError() != hipSuccess) return BB_EHIP;
     if (nsw > 0) {
         // whole groups, at least one, one workgroup a CU (MAX_WG at most: the
@@ -740,7 +1273,7 @@ int bbg::bnd2bd_launch(const double* B, int64_t rs, int64_t cs, int64_t n, int n
         if (hipGetLastError() != hipSuccess) return BB_EHIP;
     }
     hipLaunchKernelGGL(bbg::extract_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a.W, a.ldw, n,
-                       nb, d, e);
+                       nb, d, e, a.met);
     return hipGetLastError() == hipSuccess ? BB_OK : BB_EHIP;
 }
 

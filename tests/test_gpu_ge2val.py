@@ -199,11 +199,12 @@ def test_bnd2bd_result_does_not_depend_on_group_size(bb, n, nb):
 
 
 @pytest.mark.parametrize("n,nb", [(3, 64), (65, 64), (67, 33), (130, 128), (194, 97), (260, 129), (273, 255),
-                                  (514, 256)])
+                                  (514, 256), (389, 193), (1541, 2), (1537, 2)])
 def test_chase_slices_at_their_edges(bb, n, nb):
-    """Quadrants of 64, 128 and 256 columns, one to sixteen members: bandwidths
-    one below, at and one above a slice or a width, last blocks of one row, of
-    one entry and of less than a slice."""
+    """Blocks of 64, 128 and 256 columns, one to four members: bandwidths one
+    below, at and one above a width or a member's rows, last blocks of one row,
+    of one entry and of less than a member's rows; and one block more than
+    there is room for, and no more."""
     print("case chase edges", n, nb, flush=True)
     A = band_input("square", n, nb, 7500 + n + nb)
     S, ld = colmajor(A)
@@ -212,6 +213,67 @@ def test_chase_slices_at_their_edges(bb, n, nb):
     tol = 50 * n * EPS * np.linalg.norm(og.upper_band(A, n, nb))
     assert np.max(np.abs(np.abs(d.cpu().numpy()) - np.abs(do))) <= tol
     assert np.max(np.abs(np.abs(e.cpu().numpy()) - np.abs(eo))) <= tol
+
+
+@pytest.mark.parametrize("n,nb", [(900, 64), (1500, 128), (1000, 256)])
+def test_chase_by_sweeps_beside_work_that_holds_the_chip(bb, n, nb):
+    """The blocks of a band are held in registers when all of them can run at
+    once; beside another chase that leaves a few compute units only (246
+    workgroups of one a unit, about 0.1 s) the sweeps run over the band array.
+    Both match the oracle, both times."""
+    print("case chase beside", n, nb, flush=True)
+    big, bnb = 16000, 65
+    Z = torch.zeros(big, big, dtype=torch.float64, device="cuda")
+    for k in range(bnb + 1):
+        Z.diagonal(-k).fill_(1.0 / (1 + k))
+    A = band_input("tall", n, nb, 7800 + n)
+    S, ld = colmajor(A)
+    do, eo = og.bnd2bd(A, nb)
+    tol = 50 * n * EPS * np.linalg.norm(og.upper_band(A, n, nb))
+    alone = bb.bnd2bd(Z, big, big, bnb, watchdog_s=20.0)
+    wsz = torch.empty(bb.bnd2bd_workspace(big, bnb), dtype=torch.uint8, device="cuda")
+    ws = torch.empty(bb.bnd2bd_workspace(n, nb), dtype=torch.uint8, device="cuda")
+    one, two = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(one):
+        beside = bb.bnd2bd(Z, big, big, bnb, ws=wsz, watchdog_s=20.0, check=False)
+    with torch.cuda.stream(two):
+        d, e = bb.bnd2bd(S, ld, n, nb, ws=ws, watchdog_s=20.0)
+    torch.cuda.synchronize()
+    print("the smaller one's meeting (1 met, 2 given up):", int(ws[8:12].view(torch.int32)[0]), flush=True)
+    assert bb.poll_error(wsz) == 0
+    for got in ((d, e), bb.bnd2bd(S, ld, n, nb, watchdog_s=20.0)):
+        assert np.max(np.abs(np.abs(got[0].cpu().numpy()) - np.abs(do))) <= tol
+        assert np.max(np.abs(np.abs(got[1].cpu().numpy()) - np.abs(eo))) <= tol
+    sa, sb = bb.bd2val(*alone), bb.bd2val(*beside)
+    assert float((sa - sb).abs().max()) <= 50 * big * EPS * float(sa[0])
+
+
+@pytest.mark.parametrize("n,nb", [(40, 8), (300, 64), (300, 128), (600, 256)])
+def test_chase_in_a_graph(bb, n, nb):
+    """Captured and replayed on new values, with eager calls between the
+    replays: every replay gives the eager result bit by bit."""
+    print("case chase graph", n, nb, flush=True)
+    rng = np.random.default_rng(7900 + n)
+    S = torch.zeros(n, n, dtype=torch.float64, device="cuda")
+    ws = torch.empty(bb.bnd2bd_workspace(n, nb), dtype=torch.uint8, device="cuda")
+    inputs = []
+    for _ in range(4):
+        B = np.triu(np.tril(rng.standard_normal((n, n)), nb))
+        inputs.append(torch.from_numpy(np.ascontiguousarray(B.T)).cuda())
+    bb.bnd2bd(inputs[0], n, n, nb, ws=ws)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        d, e = bb.bnd2bd(S, n, n, nb, ws=ws, check=False)
+    for B in inputs:
+        S.copy_(B)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        got = d.clone(), e.clone()
+        want = bb.bnd2bd(B, n, n, nb)
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
 
 
 @pytest.mark.parametrize("n", [1, 3, 15, 16, 17, 1024, 1025, 4096, 4097, 4113])
