@@ -207,17 +207,9 @@ int build_schedule(bb_plan& P) {
     // one strip per update below nb = 128 (every task of a mixed launch)
     P.ns = P.nb == bbk::NB_MIXED ? 128 : bbk::strip_width(P.nb);
     const int nb = P.nb == bbk::NB_MIXED ? 128 : P.nb;
-    P.nparts.assign(nt, 1);
-    for (int t = 0; t < nt; ++t)
-        if (!bb::is_panel(g.tasks[t].kind)) P.nparts[t] = (nb + P.ns - 1) / P.ns;
-    P.ndeps.assign(nt, 0);
     std::vector<int32_t> cnt(nt + 1, 0);
-    for (int t = 0; t < nt; ++t) {
-        for (int32_t pr : g.pred[t]) {
-            P.ndeps[t] += P.nparts[pr];
-            cnt[pr + 1]++;
-        }
-    }
+    for (int t = 0; t < nt; ++t)
+        for (int32_t pr : g.pred[t]) cnt[pr + 1]++;
     P.succ_off.assign(nt + 1, 0);
     for (int t = 0; t < nt; ++t) P.succ_off[t + 1] = P.succ_off[t] + cnt[t + 1];
     P.succ_idx.assign(P.succ_off[nt], 0);
@@ -233,6 +225,43 @@ int build_schedule(bb_plan& P) {
         for (int s = P.succ_off[t]; s < P.succ_off[t + 1]; ++s) b = std::max(b, blevel[P.succ_idx[s]]);
         blevel[t] = b + task_cost(P, t);
     }
+    // Parts: an update's strips side by side.  Applying Q or P is a chain of
+    // updates, and a strip of 64 columns (one wave a SIMD) takes 0.65 of the
+    // time of one of 128 (two), so where workgroups are idle anyway the strips
+    // are narrow: all of them while the work is at most 0.35 of what the
+    // workgroups could do along the critical path (0.75 for nb = 256), and up
+    // to 0.55 those of the tasks on paths of at least 0.95 of it.  Measured,
+    // 128 and 64 columns: P of 6000 x 1500 to 1500 columns, nb = 128 (0.13)
+    // 1.65 and 1.27 ms; Q of the same (0.50) 3.97 ms, all narrow 3.73, the
+    // critical ones 3.45; Q of 8192 x 1024 (0.60) 2.13 and 2.16 ms; Q of 4096^2
+    // to 4096 columns (0.73) 7.1 and 7.9 ms; nb = 256: Q of 4000 x 2000 to 4000
+    // columns (0.58) 5.2 and 3.5 ms, of 8192^2 to 1024 (0.19) 15.7 and 9.9 ms.
+    // Reductions keep whole strips: panels make their chains.
+    P.nparts.assign(nt, 1);
+    for (int t = 0; t < nt; ++t)
+        if (!bb::is_panel(g.tasks[t].kind)) P.nparts[t] = (nb + P.ns - 1) / P.ns;
+    std::vector<char> narrow(nt, 0);
+    if (P.apply_graph && P.ns == 128) {
+        double work = 0.0, cp = 0.0;
+        for (int t = 0; t < nt; ++t) {
+            work += task_cost(P, t) * P.nparts[t];
+            cp = std::max(cp, blevel[t]);
+        }
+        work /= std::max(1, P.opts.workgroups);
+        if (work <= (nb == 256 ? 0.75 : 0.55) * cp) {
+            std::vector<double> tlevel(nt, 0.0);
+            for (int t = 0; t < nt; ++t) {
+                for (int32_t pr : g.pred[t]) tlevel[t] = std::max(tlevel[t], tlevel[pr] + task_cost(P, pr));
+                if (nb == 256 || work <= 0.35 * cp || tlevel[t] + blevel[t] >= 0.95 * cp) {
+                    narrow[t] = 1;
+                    P.nparts[t] *= 2;
+                }
+            }
+        }
+    }
+    P.ndeps.assign(nt, 0);
+    for (int t = 0; t < nt; ++t)
+        for (int32_t pr : g.pred[t]) P.ndeps[t] += P.nparts[pr];
     // Plain bottom levels for both variants: ranking R-BiDiag's second phase
     // above QR(p,q) measured slightly slower for tall and square inputs.
     const std::vector<double>& prio = blevel;
@@ -263,8 +292,8 @@ int build_schedule(bb_plan& P) {
             ready.pop();
             int t = std::get<1>(r);
             P.units_ticket.push_back(t);
-            P.units_ticket.push_back(std::get<2>(r));
-            running.emplace(now + task_cost(P, t), t);
+            P.units_ticket.push_back(std::get<2>(r) | (narrow[t] ? bbk::PART_NARROW : 0));
+            running.emplace(now + task_cost(P, t) * (narrow[t] ? 0.65 : 1.0), t);
             busy++;
         }
         if (running.empty()) break;

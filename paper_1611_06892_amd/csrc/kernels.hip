@@ -1058,7 +1058,7 @@ __device__ __forceinline__ void panel(const KArgs& a, const DevTask& tk, double*
 // ---------------------------------------------------------------------------
 // Update kernels: UNMQR, TSMQR, TTMQR (Table 1) on a strip of the trailing
 // tile (or tile pair): the whole tile for nb <= 128, a 128-column half for
-// nb = 256.  Wave w owns the 16 logical columns c0 = part * NS + 16 w ..
+// nb = 256, or (PART_NARROW, applications only) 64 columns.  Wave w owns the 16 logical columns c0 = part * NS + 16 w ..
 // c0 + 15 of C2 (and C1); waves past the tile's width only stage and
 // synchronize.  All nb/16 blocks of the record are applied (apply_blocks).
 // ---------------------------------------------------------------------------
@@ -1066,15 +1066,17 @@ template <int NB, int KIND, bool CO, bool HQ>
 __device__ __forceinline__ void update(const KArgs& a, const DevTask& tk, int part, double* lds, Prev& prev,
                                        int* sch) {
     constexpr int MT = NB / 16;
-    constexpr int NS = NB < 128 ? NB : 128;  // strip width: one 16-column slice per wave
     constexpr bool HASC1 = KIND != K_UNMQR;
+    // strip width: one 16-column slice per wave at most
+    const int ns = NB < 128 ? NB : part & PART_NARROW ? 64 : 128;
+    if (NB >= 128) part &= PART_NARROW - 1;
     const int tid = here(threadIdx.x), w = tid >> 6;
-    const int c0 = part * NS + 16 * w;
+    const int c0 = part * ns + 16 * w;
     const MatDesc md = mat_desc(a, tk.mat);
     const TileView T2 = view(md, tk, tk.r2, tk.c2, NB);
     const TileView T1 = HASC1 ? view(md, tk, tk.r1, tk.c1, NB) : T2;
     // Waves without columns still take part in staging and barriers.
-    const bool active = 16 * w < NS && c0 < T2.vc;
+    const bool active = 16 * w < ns && c0 < T2.vc;
     const Rec rec(record<NB>(md, tk), NB);
 
     TileLane l1(T1, c0, NB), l2(T2, c0, NB);

@@ -45,6 +45,8 @@ struct KArgs {
 // 16-column slice per wave of the 512-thread workgroup, so the whole tile up
 // to nb = 128 and a 128-column half at nb = 256.
 inline int strip_width(int nb) { return nb < 128 ? nb : 128; }
+// Flag in a unit's part: a strip of 64 columns instead of 128 (nb >= 128).
+constexpr int PART_NARROW = 1 << 16;
 
 // One V/T record: V (nb x nb) and nb/16 blocks T_b^T (16 x 16).
 inline int64_t record_doubles(int nb) { return 1LL * nb * nb + 16LL * nb; }

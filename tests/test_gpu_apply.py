@@ -161,3 +161,25 @@ def test_full_size_probe_vectors(bb):
     err = torch.linalg.norm(Ad @ X - SW.t(), dim=0) / (torch.linalg.norm(Ad) * torch.linalg.norm(X, dim=0))
     print("probe residuals", err.cpu().numpy(), flush=True)
     assert float(err.max()) <= 50 * n * EPS
+
+
+@pytest.mark.parametrize("m,n,nb", [(1024, 256, 128), (900, 300, 128), (1024, 512, 256)])
+@pytest.mark.parametrize("transpose", [False, True])
+def test_strips_of_64_and_128_columns_give_the_same_bits(bb, m, n, nb, transpose):
+    """Applied to a few columns, Q and P are chains of 64-column strips; to
+    24000 columns, the strips are 128 wide.  Every 16-column slice is the same
+    arithmetic, so the columns agree bit by bit, also those of a last tile that
+    ends inside a strip."""
+    print("case strips", m, n, nb, transpose, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    S = torch.randn(n, m, generator=g, device="cuda", dtype=torch.float64)
+    plan = bb.Plan(m, n, nb, "greedy", "bidiag")
+    vt, ws = plan.alloc()
+    plan.execute(S, m, vt, ws)
+    for rows, run in ((m, plan.apply_q), (n, plan.apply_p)):
+        C = torch.randn(24000, rows, generator=g, device="cuda", dtype=torch.float64)
+        few = C[-331:].clone()
+        run(C, rows, 24000, vt, transpose=transpose)
+        # the last 331 columns start inside a tile of the wide C
+        run(few, rows, 331, vt, transpose=transpose)
+        assert torch.equal(C[-331:], few)
