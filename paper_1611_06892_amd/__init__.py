@@ -11,8 +11,10 @@ FlatTT, Greedy or Auto reduction trees.
 """
 from __future__ import annotations
 
+import collections
 import ctypes
 import os
+import threading
 
 import numpy as np
 
@@ -190,8 +192,40 @@ def choose(m, n, nb, **opts):
 
 
 def cache_clear():
-    """Drop the plans the one-shot entry points cache."""
+    """Drop the plans the one-shot entry points and band_autograd cache."""
     lib().bb_cache_clear()
+    with _plans_lock:
+        dropped = list(_plans.values())
+        _plans.clear()
+    del dropped                     # destroyed outside the lock
+
+
+# Plans of band_autograd, least recently used first: as many as the library
+# keeps for the one-shot entry points.  A plan holds no state of a run (its
+# buffers belong to the caller), so threads and streams may share one; a plan
+# in use stays alive with its user.  Building the three graphs of a pass takes
+# the host 4 ms at 8192 x 1024, nb = 128 (a third of the pass).
+_PLANS_MAX = 16
+_plans = collections.OrderedDict()
+_plans_lock = threading.Lock()
+
+
+def _shared_plan(m, n, nb, tree, variant, device):
+    key = (m, n, nb, tree, variant, device)
+    with _plans_lock:
+        plan = _plans.get(key)
+        if plan is not None:
+            _plans.move_to_end(key)
+            return plan
+    plan = Plan(m, n, nb, tree, variant)
+    dropped = []
+    with _plans_lock:
+        plan = _plans.setdefault(key, plan)
+        _plans.move_to_end(key)
+        while len(_plans) > _PLANS_MAX:
+            dropped.append(_plans.popitem(last=False))
+    del dropped                     # destroyed outside the lock
+    return plan
 
 
 def strerror(code: int) -> str:
@@ -646,7 +680,7 @@ def _band_function():
         @staticmethod
         def forward(ctx, A, nb, tree, variant):
             m, n = A.shape
-            plan = Plan(m, n, nb, tree, variant)
+            plan = _shared_plan(m, n, int(nb), tree, variant, torch.cuda.current_device())
             S = to_colmajor(A.detach())
             vt, ws = plan.alloc(S.device)
             plan.execute(S, m, vt, ws)

@@ -409,3 +409,35 @@ def test_choose_picks_by_shape():
     t2, v2, e2 = bb.choose(4096, 2 * 4096, 128)     # wide: the transpose's choice
     t3, v3, e3 = bb.choose(2 * 4096, 4096, 128)
     assert (t2, v2, e2) == (t3, v3, e3)
+
+
+def test_autograd_plans_are_shared_bounded_and_dropped():
+    """band_autograd's plans: one per shape, whatever thread asks; the least
+    recently used ones go beyond the bound; cache_clear drops all, and a plan
+    that is still held stays usable."""
+    import threading
+    import paper_1611_06892_amd as mod
+    bb.cache_clear()
+    got = []
+
+    def ask():
+        for m in (70, 80, 90):
+            got.append((m, mod._shared_plan(m, 40, 32, "greedy", "rbidiag", 0)))
+
+    threads = [threading.Thread(target=ask) for _ in range(6)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for m in (70, 80, 90):
+        assert len({id(p) for k, p in got if k == m}) == 1
+    held = got[0][1]
+    for n in range(1, 3 * mod._PLANS_MAX):
+        mod._shared_plan(200, n, 32, "greedy", "rbidiag", 0)
+        assert len(mod._plans) <= mod._PLANS_MAX
+    assert held.stats()["ntasks"] > 0
+    assert mod._shared_plan(70, 40, 32, "greedy", "rbidiag", 0) is not held
+    assert mod._shared_plan(70, 40, 32, "greedy", "rbidiag", 1) is not mod._shared_plan(70, 40, 32, "greedy",
+                                                                                           "rbidiag", 0)
+    bb.cache_clear()
+    assert not mod._plans and held.stats()["ntasks"] > 0
