@@ -38,6 +38,7 @@ constexpr int NT = 512;          // threads per workgroup
 typedef double d4 __attribute__((ext_vector_type(4)));
 typedef double d2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u2 __attribute__((ext_vector_type(2)));
 
 enum : int { K_GEQRT = 0, K_TSQRT = 1, K_TTQRT = 2, K_UNMQR = 3, K_TSMQR = 4, K_TTMQR = 5, K_HQ = 3 };
 
@@ -107,26 +108,37 @@ struct TileView {
 
 // One lane's part of the 16 columns from c0: column c0 + lane % 16, rows
 // 16 i + 4 (lane / 16) .. + 3 of row tile i, read and written four at a time.
-// Whole tiles whose columns are contiguous and 16-byte aligned (QR steps)
-// take 16-byte buffer accesses: one byte offset per lane, the row in the
-// instruction.  Everything else (LQ steps, ragged or unaligned tiles) is
-// addressed by element; in a ragged tile a load of a missing element reads
-// the tile's first one instead and yields zero, so that no load is behind a
-// branch.
+// Tiles whose columns are contiguous (QR steps) take buffer accesses: one
+// byte offset per lane, the row in the instruction, 16 bytes at a time (the
+// accesses need 4-byte alignment only, so any leading dimension does for nb <= 128), by
+// element in the row tile in which a ragged tile ends; what does not exist has
+// an offset past the buffer's end, where loads give zero and stores do
+// nothing.  Everything else (LQ steps) is addressed by element; in a ragged
+// tile a load of a missing element reads the tile's first one instead and
+// yields zero, so that no load is behind a branch.
+// ENDS: ragged tiles go through the buffer too.  In panels, whose chain they
+// lengthen (1 % at nb = 64), and at nb = 256, where the branches cost 400
+// spills, they go by element.
+template <int NB, bool ENDS = NB <= 128>
 struct TileLane {
+    static constexpr int PAST = (int)0xC0000000u;
     __amdgpu_buffer_rsrc_t rsrc;
-    int voff;
+    int voff, vr;
     bool vec, whole;
     gdouble *p, *first;
     int64_t rs;
     int rlim;                       // rows r0 + r < rlim exist (r0 a multiple of 16, r < 4)
-    __device__ __forceinline__ TileLane(const TileView& t, int c0, int nb) {
+    __device__ __forceinline__ TileLane(const TileView& t, int c0) {
         const int lane = here(threadIdx.x) & 63, c = c0 + (lane & 15), r = 4 * (lane >> 4);
-        // whole, contiguous columns, aligned, within a buffer's 32-bit offsets
-        whole = t.vr == nb && t.vc == nb;
-        vec = whole && t.rs == 1 && ((uint64_t)t.base & 15) == 0 && (t.cs & 1) == 0 && t.cs * nb < (1 << 27);
+        whole = t.vr == NB && t.vc == NB;
+        // contiguous columns within a buffer's 32-bit offsets (nb = 256: aligned
+        // too; without that condition, or with it a value of its own, the
+        // compiler spills 445 registers, not 401, and 16384^2 takes 360 ms, not 352)
+        vec = (ENDS || whole) && t.rs == 1 &&
+              (NB <= 128 || (((uint64_t)t.base & 15) == 0 && (t.cs & 1) == 0)) && t.cs * NB < (1 << 27);
+        vr = t.vr;
         rsrc = __builtin_amdgcn_make_buffer_rsrc((void*)t.base, (short)0, 0x7fffffff, 0x00020000);
-        voff = 8 * (r + c * (int)t.cs);
+        voff = !ENDS || c < t.vc ? 8 * (r + c * (int)t.cs) : PAST;
         first = gptr(t.base);
         p = first + r * t.rs + c * t.cs;
         rs = t.rs;
@@ -135,15 +147,27 @@ struct TileLane {
     // Keeps addresses formed from this lane's offsets from being hoisted
     // above this point.
     __device__ __forceinline__ void renew() { asm volatile("" : "+v"(p), "+v"(voff)); }
+    // The lane's offset where it has row `row` + 4 (lane / 16) of the tile.
+    __device__ __forceinline__ int element(int row) const {
+        return row + 4 * ((threadIdx.x & 63) >> 4) < vr ? voff : PAST;
+    }
     template <int MT>
     __device__ __forceinline__ void load(int r0, d4 (&x)[MT]) const {
         if (vec) {
 #pragma unroll
             for (int i = 0; i < MT; ++i) {
-                const u4 lo = __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, 8 * (r0 + 16 * i), 0);
-                const u4 hi = __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff + 16, 8 * (r0 + 16 * i), 0);
-                const d2 l = __builtin_bit_cast(d2, lo), h = __builtin_bit_cast(d2, hi);
-                x[i] = d4{l[0], l[1], h[0], h[1]};
+                const int row = r0 + 16 * i;
+                if (!ENDS || row + 16 <= vr) {
+                    const u4 lo = __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, 8 * row, 0);
+                    const u4 hi = __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff + 16, 8 * row, 0);
+                    const d2 l = __builtin_bit_cast(d2, lo), h = __builtin_bit_cast(d2, hi);
+                    x[i] = d4{l[0], l[1], h[0], h[1]};
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        x[i][r] = __builtin_bit_cast(
+                            double, __builtin_amdgcn_raw_buffer_load_b64(rsrc, element(row + r), 8 * (row + r), 0));
+                }
             }
         } else if (whole) {
             gdouble* q = p + r0 * rs;
@@ -176,15 +200,44 @@ struct TileLane {
         load<1>(r0, x);
         return x[0];
     }
-    template <bool CO>
+    // LINES: the stores of a row tile take 64 bytes of each column; without,
+    // 16 of each 32 (panels, which wait for nothing but their own chain, and
+    // nb = 256, where the exchange costs registers: 16384^2 352 and 356 ms).
+    // Together with 16-byte accesses at any leading dimension and in ragged
+    // tiles, nb = 128 updates of uneven matrices (4096 of 64 to 1024 rows in
+    // a batch): TSMQR 62.7 -> 49.3, UNMQR 36.6 -> 32.8 us.
+    template <bool CO, bool LINES = NB <= 128>
     __device__ __forceinline__ void store(int r0, d4 x) const {
-        if (vec) {
-            // cache policy 16 (sc1): performed at the agent's coherence point,
-            // as gstore's agent-scope stores
+        if (ENDS && vec && r0 + 16 > vr) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const double v = x[r];          // (a bit cast of the vector's element takes element 0)
+                __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), rsrc, element(r0 + r), 8 * (r0 + r),
+                                                      CO ? 16 : 0);
+            }
+        } else if (vec && !LINES) {
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, d2{x[0], x[1]}), rsrc, voff, 8 * r0,
                                                    CO ? 16 : 0);
             __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, d2{x[2], x[3]}), rsrc, voff + 16, 8 * r0,
                                                    CO ? 16 : 0);
+        } else if (vec) {
+            // Each store takes 64 contiguous bytes of every column: lane g of
+            // a column has rows 2 g, 2 g + 1 of the tile's first eight for the
+            // one, of its last eight for the other.
+            u4 lo = __builtin_bit_cast(u4, d2{x[0], x[1]}), hi = __builtin_bit_cast(u4, d2{x[2], x[3]});
+            u4 a, b;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const auto p = __builtin_amdgcn_permlane16_swap(lo[k], hi[k], false, false);
+                const auto q = __builtin_amdgcn_permlane32_swap(p[0], p[1], false, false);
+                a[k] = q[0];
+                b[k] = q[1];
+            }
+            // cache policy 16 (sc1): performed at the agent's coherence point,
+            // as gstore's agent-scope stores
+            const int v = voff - 16 * ((threadIdx.x & 63) >> 4);
+            __builtin_amdgcn_raw_buffer_store_b128(a, rsrc, v, 8 * r0, CO ? 16 : 0);
+            __builtin_amdgcn_raw_buffer_store_b128(b, rsrc, v + 64, 8 * r0, CO ? 16 : 0);
         } else if (whole) {
             gdouble* q = p + r0 * rs;
 #pragma unroll
@@ -260,15 +313,15 @@ __device__ __forceinline__ TileView view(const MatDesc& d, const DevTask& tk, in
 // data movement.
 __device__ __forceinline__ int perm16(int m) { return 4 * (m & 3) + (m >> 2); }
 
-template <int MT>
-__device__ __forceinline__ void load_slice(const TileLane& t, d4 (&x)[MT]) {
-    t.load<MT>(0, x);
+template <int MT, class Lane>
+__device__ __forceinline__ void load_slice(const Lane& t, d4 (&x)[MT]) {
+    t.template load<MT>(0, x);
 }
 
 template <bool CO, int MT>
-__device__ __forceinline__ void store_slice(const TileLane& t, const d4 (&x)[MT]) {
+__device__ __forceinline__ void store_slice(const TileLane<16 * MT>& t, const d4 (&x)[MT]) {
 #pragma unroll
-    for (int i = 0; i < MT; ++i) t.store<CO>(16 * i, x[i]);
+    for (int i = 0; i < MT; ++i) t.template store<CO>(16 * i, x[i]);
 }
 
 // Reads of one V/T record through a buffer descriptor: every load of a
@@ -406,7 +459,7 @@ __device__ __forceinline__ void retire(const KArgs& a, Prev& p) {
 // record block's loads are issued.
 // ---------------------------------------------------------------------------
 template <int NB, int NBLK, int KIND, bool CO, bool HQ>
-__device__ __forceinline__ void apply_blocks(const Rec& rec, const TileLane& T1, bool active, d4* c2,
+__device__ __forceinline__ void apply_blocks(const Rec& rec, const TileLane<NB>& T1, bool active, d4* c2,
                                              double* lds, const KArgs& a, Prev& prev) {
     constexpr int MT = NB / 16;
     constexpr int LDV = Shape<NB>::LDV;
@@ -471,7 +524,7 @@ __device__ __forceinline__ void apply_blocks(const Rec& rec, const TileLane& T1,
                 W2 = mfma(-(HQ ? Ts[(4 * g + r) + 16 * pj] : Ts[pj + 16 * (4 * g + r)]), W[r], W2);
             // W2 holds -T_b^T W: negating the 4 T operands spares negating
             // the V operands of the update below.
-            if (HASC1) T1.store<CO>(16 * b, C1b + W2);
+            if (HASC1) T1.template store<CO>(16 * b, C1b + W2);
 #pragma unroll
             for (int i = 0; i < MT; ++i) {
                 if (KIND == K_UNMQR && i < b) continue;
@@ -818,7 +871,7 @@ __device__ __forceinline__ void panel(const KArgs& a, const DevTask& tk, double*
 #pragma unroll 1
     for (int h = 0; h < NH; ++h) {
         const int ct = HT * h + w;                      // this wave's column tile
-        TileLane l1(T1, 16 * ct, NB), lx(TX, 16 * ct, NB);
+        TileLane<NB, false> l1(T1, 16 * ct), lx(TX, 16 * ct);
         d4 x[MT], R1n = {0.0, 0.0, 0.0, 0.0};
         if (own) load_slice<MT>(lx, x);
         // R1's rows are changed by the block of the same index only: the
@@ -844,7 +897,7 @@ __device__ __forceinline__ void panel(const KArgs& a, const DevTask& tk, double*
             } else {
                 const d4 zero = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 1
-                for (int i = r0; i < r1; i += 16) lx.store<CO>(i, zero);
+                for (int i = r0; i < r1; i += 16) lx.template store<CO, false>(i, zero);
             }
         };
 
@@ -899,7 +952,7 @@ __device__ __forceinline__ void panel(const KArgs& a, const DevTask& tk, double*
             d4 W2 = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
             for (int r = 0; r < 4; ++r) W2 = mfma(tb[r], W[r], W2);
-            if (pair) l1.store<CO>(16 * cb, R1b + W2);
+            if (pair) l1.template store<CO, false>(16 * cb, R1b + W2);
 #pragma unroll
             for (int p = 0; p < MT / 2; ++p) {
                 if (AHEAD && p + 1 < MT / 2) read_x(p + 1);
@@ -917,7 +970,7 @@ __device__ __forceinline__ void panel(const KArgs& a, const DevTask& tk, double*
 #pragma unroll
                 for (int i = 0; i < MT; ++i)
                     if (i == cb) {
-                        lx.store<CO>(16 * i, x[i]);
+                        lx.template store<CO, false>(16 * i, x[i]);
                         x[i] = d4{0.0, 0.0, 0.0, 0.0};
                     }
             }
@@ -1043,7 +1096,7 @@ __device__ __forceinline__ void panel(const KArgs& a, const DevTask& tk, double*
 #pragma unroll
         for (int r = 0; r < 4; ++r)
             if (4 * g + r > j) dt[r] = 0.0;
-        l1.store<CO>(16 * ct, dt);                   // R (GEQRT) or R1's diagonal block
+        l1.template store<CO, false>(16 * ct, dt);                   // R (GEQRT) or R1's diagonal block
         write_record(w);
         if (w == 0) clear();
 #pragma unroll 1
@@ -1079,7 +1132,7 @@ __device__ __forceinline__ void update(const KArgs& a, const DevTask& tk, int pa
     const bool active = 16 * w < ns && c0 < T2.vc;
     const Rec rec(record<NB>(md, tk), NB);
 
-    TileLane l1(T1, c0, NB), l2(T2, c0, NB);
+    TileLane<NB> l1(T1, c0), l2(T2, c0);
     d4 c2[MT];
     if (active) load_slice<MT>(l2, c2);
     apply_blocks<NB, MT, KIND, CO, HQ>(rec, l1, active, &c2[0], lds, a, prev);
@@ -1163,7 +1216,7 @@ __device__ __forceinline__ void update32(const KArgs& a, const DevTask& tk, int 
     };
 
     d4 c2[MT];
-    TileLane l1(T1, c0, NB), l2(T2, c0, NB);
+    TileLane<NB> l1(T1, c0), l2(T2, c0);
     if (active) load_slice<MT>(l2, c2);
     double pre[PRE];
     fetch(0, pre);
@@ -1207,7 +1260,7 @@ __device__ __forceinline__ void update32(const KArgs& a, const DevTask& tk, int 
             d4 W2;
 #pragma unroll
             for (int r = 0; r < 4; ++r) W2[r] = (double)w2[r];
-            if (HASC1) l1.store<CO>(16 * b, C1b - W2);
+            if (HASC1) l1.template store<CO>(16 * b, C1b - W2);
             // C2 -= V_b W2
 #pragma unroll
             for (int i = 0; i < MT; ++i) {

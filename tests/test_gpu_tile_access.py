@@ -75,3 +75,20 @@ def test_zero_columns_and_scaled_columns(bb, nb):
     assert np.isfinite(B).all()
     assert oracle.band_violation(B, nb) == 0.0
     assert abs(np.linalg.norm(B) / np.linalg.norm(A) - 1) <= 50 * n * EPS
+
+
+@pytest.mark.parametrize("nb", [32, 64, 128])
+@pytest.mark.parametrize("rest", [1, 3, 4, 15, 16, 17])
+def test_last_tiles_of_any_height_and_width(bb, nb, rest):
+    """Last row and column tiles that end inside a lane's four rows, at and one
+    past a row tile: the band form against the oracle's, rows below the matrix
+    untouched, tall and (transposed) wide."""
+    m, n = 2 * nb + rest, nb + rest
+    for rows, cols in ((m, n), (n, m)):
+        A = workloads.gaussian(rows, cols, seed=10 * nb + rest)
+        plan = bb.Plan(rows, cols, nb, "flatts", "bidiag")
+        B, _ = reduce_at(bb, A, plan, rows + 3, 1)
+        Bt, At = (B, A) if rows >= cols else (B.T, A.T)
+        Bo, _ = oracle.band_reduce(np.ascontiguousarray(At), nb)
+        d = np.linalg.norm(oracle.sign_normalize(np.ascontiguousarray(Bt), nb) - oracle.sign_normalize(Bo, nb))
+        assert d <= 50 * n * EPS * np.linalg.norm(A), d
