@@ -263,13 +263,14 @@ def ge2val_stage(bb, torch, np, S, m, n, nb, s_ref, e2bnd_ms):
         ref = np.sort(np.asarray(s_ref))[::-1]
         err = float(np.max(np.abs(sig.cpu().numpy() - ref))) / float(ref[0])
     nbytes = chase_bytes(n, nb)
-    gbs = nbytes / (chase_ms * 1e-3) / 1e9
+    flops = 8.0 * n * n * nb          # two reflectors per nb columns of each of n sweeps
+    tflops = flops / (chase_ms * 1e-3) / 1e12
     return {"nb": nb, "ge2bnd_ms": round(e2bnd_ms, 3), "bnd2bd_ms": round(chase_ms, 3),
             "bd2val_ms": round(bd_ms, 3), "total_ms": round(e2bnd_ms + chase_ms + bd_ms, 3),
             "sigma_max_rel_err": err, "tol": 50 * n * np.finfo(np.float64).eps,
-            "bnd2bd_roofline": {"bound": "hbm", "achieved": round(gbs, 2), "peak": 8000.0, "unit": "GB/s",
-                                "frac": round(gbs / 8000.0, 5), "traffic": chase_traffic(n, nb),
-                                "kernel": "hold_kernel",
+            "bnd2bd_roofline": {"bound": "mfma", "achieved": round(tflops, 3), "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
+                                "frac": round(tflops / FP64_PEAK_TFLOPS, 5), "traffic": chase_traffic(n, nb),
+                                "kernel": "hold_kernel", "algorithmic_flops": flops,
                                 "algorithmic_bytes": nbytes}}
 
 
