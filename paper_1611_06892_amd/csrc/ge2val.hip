@@ -670,7 +670,7 @@ __global__ __launch_bounds__(NT) void hold_kernel(HoldArgs a) {
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (tid == 0) {
         fail[0] = fail[1] = 0;
-        go = meet(a);
+        go = meet(a) && aload(&a.ctrl[G_ERROR]) == 0;   // (an error reported before stops the chase)
     }
     __syncthreads();
     if (__builtin_amdgcn_readfirstlane(go) == 0) return;
