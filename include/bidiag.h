@@ -440,16 +440,16 @@ int bb_choose(int64_t m, int64_t n, int nb, const bb_opts* opts, int* tree, int*
  * pipelined over the GPU in one persistent launch.  Up to n = 768 nb (nb <=
  * 32), 512 nb (64), 256 nb (128), 64 nb (256) and while that many workgroups
  * find room within 2 ms, workgroups hold the band's blocks in registers and
- * the sweeps pass through them; else groups of workgroups run the sweeps over
- * a band array.  The two differ in rounding.  Writes the diagonal
+ * the sweeps pass through them; else workgroups run the sweeps over a band
+ * array.  Both do the same arithmetic in the same order: the result is the same,
+ * bit by bit.  Writes the diagonal
  * d[0..n-1] and the superdiagonal e[0..n-2] (device).  The diagonal and
  * superdiagonal are those of the Golub-Kahan bidiagonalization of B started
  * at e1, so they are unique up to signs.
- * ws: device workspace of bb_bnd2bd_workspace bytes (control words, the
- * held blocks' messages, and for the other way the band
+ * ws: device workspace of bb_bnd2bd_workspace bytes (control words, the band
  * with room for the fill, 24 nb n bytes, a progress counter per sweep and
- * member of its group, an exchange counter per sweep and the groups' exchange
- * areas), overwritten.  watchdog_s: seconds a sweep (or a
+ * member of its group, the groups' exchange areas and the held blocks'
+ * messages), overwritten.  watchdog_s: seconds a sweep (or a
  * held block) may wait for the one before it (0 = 30); when it fires the launch stops and bb_poll_error(ws)
  * reports BB_ETIMEOUT.  Arguments: B (1), ldb >= max(1, n) (2), n >= 0 (3),
  * 1 <= nb <= 256 (4), d (5), e (6), ws (7), ws_bytes (8, BB_EWORKSPACE when
@@ -458,9 +458,11 @@ int bb_choose(int64_t m, int64_t n, int nb, const bb_opts* opts, int* tree, int*
 int bb_bnd2bd_workspace(int64_t n, int nb, size_t* ws_bytes);
 int bb_bnd2bd(const double* B, int64_t ldb, int64_t n, int nb, double* d, double* e, void* ws,
               size_t ws_bytes, double watchdog_s, void* stream);
-/* bb_bnd2bd_group -- bb_bnd2bd with a wish for the number of workgroups that
- * run each sweep: group (10) in 0..16, -10 out of range.  The launch uses the
- * number it needs whatever is asked for; the result does not depend on it. */
+/* bb_bnd2bd_group -- bb_bnd2bd with group (10) in 0..16, -10 out of range: 0 as
+ * bb_bnd2bd, any other value runs the sweeps over the band array whatever the
+ * size, which needs no more than four free compute units (one for nb <= 128).
+ * A sweep takes ceil(nb / 64) workgroups for nb > 128, else one, for every
+ * group; the result does not depend on it. */
 int bb_bnd2bd_group(const double* B, int64_t ldb, int64_t n, int nb, double* d, double* e, void* ws,
                     size_t ws_bytes, double watchdog_s, int group, void* stream);
 

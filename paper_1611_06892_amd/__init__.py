@@ -477,10 +477,11 @@ def bnd2bd_workspace(n, nb) -> int:
 
 
 def bnd2bd(S, ldb, n, nb, ws=None, watchdog_s=0.0, stream=None, check=True, group=0):
-    """Band to bidiagonal (bb_bnd2bd; group: 0 to 16, a wish for the workgroups
-    per sweep that the result does not depend on).  S: CUDA FP64 storage of a column-major
-    matrix whose leading n x n part holds the upper band of bandwidth nb
-    (leading dimension ldb), e.g. the storage tensor a Plan reduced.
+    """Band to bidiagonal (bb_bnd2bd_group: group 0, or 1 to 16 to run the sweeps
+    over a band array even where the band could be held in registers, with the
+    same bits).  S: CUDA FP64 storage of a column-major matrix whose leading
+    n x n part holds the upper band of bandwidth nb (leading dimension ldb), e.g.
+    the storage tensor a Plan reduced.
     Returns (d, e) as CUDA tensors; S is not modified."""
     import torch
     dev = S.device

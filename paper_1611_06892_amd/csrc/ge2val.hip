@@ -17,24 +17,18 @@
 // write, so it may start once sweep k has finished step t+1: two steps
 // separate consecutive sweeps, and about n / (2 nb) sweeps run at once.
 //
-// Where the band fits in the registers of the chip, it is held there and the
-// sweeps pass through it (hold_kernel); else, and when the compute units are
-// not free for that, the sweeps pass over the band array (chase_kernel):
-//
-// the band is copied into a band work array with room for the fill of the
-// chase (nb - 1 diagonals below the main one, 2 nb - 1 above), column-major by
-// diagonal offset:
-//     W[(i - j + 2 nb - 1) + j * 3 nb]  holds entry (i, j).
-// One persistent launch: each group of workgroups takes the next sweep
-// (tickets from an atomic counter, so a sweep is only ever waited for by a
-// later one that running workgroups hold: no deadlock for any grid) and runs
-// its steps in order, each after the previous sweep's progress counters allow
-// it.  The
-// band array is written and read with agent-scope stores and loads (past the
-// XCD's L2, at the coherence point), so a counter is published once every
-// wave has waited for its own memory operations, with no L2 write-back, and the loads that follow a counter's load see every
-// store performed before it was written, with no L2 invalidation; a
-// wall-clock watchdog bounds every wait.
+// Blocks: block b of sweep k is the nb rows from c = k + 1 + b nb on, with the
+// columns c .. c + 2 nb - 1.  One block of one sweep (block_step) is the unit
+// of work, and there are two ways to bring the blocks to it:
+//   * where all blocks' workgroups find room on the chip at once, they hold
+//     the blocks in registers and the sweeps pass through them (hold_kernel);
+//   * else, for larger matrices or beside work that holds compute units, each
+//     sweep is run by workgroups of its own over the band in memory
+//     (sweep_kernel), any number of them.
+// Both run the same block_step on the same values in the same lanes, so the
+// result does not depend on the way, bit by bit.  Multiply-adds are written
+// out and contraction is off, so that the compiler cannot round the two
+// copies of the step differently.
 //
 // BD2VAL.  The singular values of the bidiagonal (d, e) are the positive
 // eigenvalues of the 2n x 2n Golub-Kahan matrix, symmetric tridiagonal with
@@ -53,46 +47,23 @@
 
 #include "bidiag.h"
 
+#pragma clang fp contract(off)
+
 namespace bbg {
 
-constexpr int NT = 512;                 // threads of the chase kernel (8 waves)
+constexpr int NT = 512;                 // threads of the chase kernels (8 waves)
 constexpr int NW = NT / 64;
 constexpr int BT = 256;                 // threads of a bisection workgroup
 constexpr int MS_LANES = 1 << 16;       // lanes of the bisection: one wave a SIMD
 constexpr int MAX_NB = 256;
-constexpr int GROUP_MAX = 16;
-constexpr int SLICE = 4096;             // entries of a member's slice of one quadrant
+constexpr int GROUP_MAX = 16;           // of bb_bnd2bd_group's argument
+constexpr int MAX_WG = 256;             // compute units
 enum : int { G_ERROR = 1, G_MET = 2, G_RUNNING = 3, G_HEAD = 32, G_WORDS = 64 };
 
-// Quadrant width the kernel is compiled for (64, 128, 256), rows of a
-// member's slice and workgroups (members) per sweep.
-inline int width_of(int nb) { return nb <= 64 ? 64 : nb <= 128 ? 128 : 256; }
-inline int slice_rows(int nb) { return SLICE / width_of(nb); }
-inline int group_of(int nb) { return (nb + slice_rows(nb) - 1) / slice_rows(nb); }
-
-// Exchange areas: sweeps in progress span at most MAX_WG / group + 2 of them
-// (a sweep cannot finish before the one ahead of it, and every workgroup
-// holds one ticket), so sweep k uses area k % nareas.
-constexpr int MAX_WG = 256;
-inline int nareas_of(int group) { return MAX_WG / group + 2; }
-// doubles of one area: two steps' parity, each the members' partial column
-// products and row 0
-inline int64_t area_doubles(int nb, int group) { return 2 * (int64_t)(group + 1) * 2 * width_of(nb); }
-
-struct ChaseArgs {
-    double* W;
-    int64_t ldw;          // 3 nb
-    int64_t n;
-    int nb;
-    int nsweeps;
-    int32_t* ctrl;        // G_* words
-    int32_t* prog;        // steps finished, per sweep and member
-    int32_t* bar;         // exchange arrivals, per sweep
-    double* xch;          // exchange areas (group > 1)
-    int group;            // workgroups per sweep
-    int nareas;
+// What a wait needs: the control words and the watchdog.
+struct Waits {
+    int32_t* ctrl;
     int64_t watchdog_ticks;
-    const int32_t* met;   // the meeting of hold_kernel before this launch, or null
 };
 
 __host__ __device__ inline int64_t nsteps(int64_t n, int nb, int64_t k) {
@@ -117,8 +88,6 @@ __device__ __forceinline__ double ld(const double* p) {
 __device__ __forceinline__ int aload(const int32_t* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-
-enum : int { MET_GO = 1, MET_GIVE_UP = 2 };     // the word G_MET
 
 // A barrier for LDS traffic only: it waits for this wave's LDS operations,
 // not for its global accesses, so stores stay in flight across it.
@@ -173,17 +142,17 @@ struct Refl {
 __device__ __forceinline__ Refl reflector(double al, double ss) {
     if (ss == 0.0) return {al, 0.0, 0.0};
     const double t = fma(al, al, ss), ts = copysign(t, al), r0 = __builtin_amdgcn_rsq(t);
-    const double s0 = ts * r0, y0 = __builtin_amdgcn_rcp(al + s0);
+    const double s0 = ts * r0, y0 = __builtin_amdgcn_rcp(fma(ts, r0, al));
     const double e0 = fma(-fabs(s0), r0, 1.0);
     const double r = fma(r0 * e0, fma(e0, 0.375, 0.5), r0);
     const double s1 = ts * r;
-    const double e1 = fma(-(al + s1), y0, 1.0);
+    const double e1 = fma(-fma(ts, r, al), y0, 1.0);
     return {-fma(fma(-s1, s1, t), copysign(0.5 * r, al), s1), fma(fabs(al), r, 1.0), fma(y0, fma(e1, e1, e1), y0)};
 }
 
 // Called by a whole wave: polls *p (each lane's own) until all have reached
 // target; false when an error was reported or the watchdog fired.
-__device__ __forceinline__ bool poll(const ChaseArgs& a, const int32_t* p, int target) {
+__device__ __forceinline__ bool poll(const Waits& a, const int32_t* p, int target) {
     const uint64_t t0 = wall_clock64();
     for (;;) {
         const int v = aload(p);
@@ -198,349 +167,36 @@ __device__ __forceinline__ bool poll(const ChaseArgs& a, const int32_t* p, int t
     }
 }
 
-// The chase.  A group of a.group workgroups runs a sweep; member m holds, in
-// LDS, rows s = m S .. m S + S - 1 of each block row of the sweep's window
-// (S = 4096 / NBP, so a quadrant's slice is 4096 entries for any nb): three
-// quadrants, by step t with block column c:
-//     U  rows c - nb + s, columns c .. c + nb - 1   (t >= 1),
-//     D  rows c + s,      columns c .. c + nb - 1,
-//     Q  rows c + s,      columns c + nb .. c + 2 nb - 1.
-// Q of step t is U of step t + 1, with the same owner, and no other sweep
-// touches it between the two: the buffers rotate, a step loads D and Q and
-// stores U and D.
-//   * Right reflector (row rr, cleared): every member knows the row, from
-//     the step before, and applies the reflector to its rows alone.
-//   * Left reflector (column c): with x the column below its first entry,
-//     v = (1, scale x), so v^T M = M(0, :) + scale (x^T M): one exchange of
-//     the members' partial products x^T M (its first entry is x^T x) and of row 0 gives
-//     every member the norm, the reflector, the products it applies to its
-//     rows, and the new row 0 of Q -- the row the next step clears.
-// So a step has one exchange between members (none for nb <= 64, a group of
-// one) and one wait for the sweep ahead.  Members' sums are added in the
-// order of the members, so all members compute the same values.
+// ---- one block of one sweep -------------------------------------------------
 //
-// What bounds it: the chain of steps.  A sweep follows the one ahead at a
-// distance of two steps, so the chase is about 2 n steps one after the other
-// plus, per step, the round trips to the coherence point: the poll of the
-// sweep ahead, the loads, for groups the exchange (store, counter, poll,
-// loads), and the publication, which is taken off the chain: a step's stores
-// complete while the next step's wait is polled, and the last wave whose
-// stores have completed publishes.
-// Why this split: a right update needs whole rows and a left update whole
-// columns, and slices by rows make the first local and leave the second one
-// exchange of sums; shares of rows and of columns by turns, as before, moved
-// every quadrant through memory between the two and met at two group
-// barriers a step.  Measured, before and now: 2000 at nb = 64 70.7 and
-// 24.7 ms (6.2 us a step), 8192 at nb = 256 477 and 232 ms (14.1 us), 16384
-// at nb = 128 982 and 333 ms (10.2 us); 9000 at nb = 16 217 and 100 ms.
-template <int NBP>
-__global__ __launch_bounds__(NT) void chase_kernel(ChaseArgs a) {
-    constexpr int S = SLICE / NBP;          // rows of a slice: 64, 32, 16
-    constexpr int PR = NBP / 16, R = 64 / PR;   // right update: lanes per row, rows per wave
-    constexpr int PL = S / 16, C = 64 / PL;     // left update: lanes per column, columns per wave
-    constexpr int ST = S + PL;              // LDS column stride: columns and rows spread over the banks
-    static_assert(NW * R == 2 * S && NW * C == 2 * NBP, "one pass");
-    constexpr bool GROUPED = NBP > 64;
-    __shared__ double quad[3][NBP * ST];
-    __shared__ double vr[NBP], xr[NBP];     // the right reflector; the row it comes from
-    __shared__ double srefl[2];             // its beta, tau
-    __shared__ int sk, flag, stored;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nb = a.nb, G = GROUPED ? a.group : 1;
-    const int64_t cs = a.ldw - 1;           // from entry (i, j) to (i, j + 1)
-    // right update: row (U for waves 0-3, D for waves 4-7), columns rp + PR u
-    const int rrow = (w % (NW / 2)) * R + lane % R, rp = lane / R;
-    // left update: column (D for waves 0-3, Q for waves 4-7), rows lp + PL u
-    const int lcol = (w % (NW / 2)) * C + lane % C, lp = lane / C;
-    const bool low = w < NW / 2;
-    if (tid == 0) stored = 0;
-    if (a.met && aload(a.met) == MET_GO) return;
-
-    for (;;) {
-        // ticket = sweep * G + member: a group's members are consecutive
-        // tickets, all taken by running workgroups before any of them can
-        // be needed by a later sweep (grid >= G)
-        if (tid == 0) sk = __hip_atomic_fetch_add(&a.ctrl[G_HEAD], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __syncthreads();
-        const int ticket = __builtin_amdgcn_readfirstlane(sk);
-        __syncthreads();
-        const int64_t k = ticket / G;
-        const int m = ticket - (int)k * G;
-        if (k >= a.nsweeps) return;
-        const int T = (int)nsteps(a.n, nb, k);
-        const int Tp = k > 0 ? (int)nsteps(a.n, nb, k - 1) : 0;
-        double* area = GROUPED ? a.xch + (k % a.nareas) * (2 * (int64_t)(G + 1) * 2 * NBP) : nullptr;
-        int32_t* prog = a.prog + k * G;
-
-        // The reflector that clears row (i, j .. j + len - 1) held in xr, by
-        // this wave: vr and srefl; the owner of the row stores it cleared
-        // (row k later, when every member has read it).
-        auto right_reflector = [&](int64_t i, int64_t j, int len) {
-            double x[NBP / 64], ss = 0.0;
-#pragma unroll
-            for (int h = 0; h < NBP / 64; ++h) {
-                x[h] = xr[lane + 64 * h];
-                if (lane + 64 * h > 0) ss = fma(x[h], x[h], ss);
-            }
-            const Refl f = reflector(xr[0], sum_parts<1>(ss));
-#pragma unroll
-            for (int h = 0; h < NBP / 64; ++h) {
-                const int q = lane + 64 * h;
-                vr[q] = q == 0 ? 1.0 : f.scale * x[h];
-                if (i > k && m == 0 && q < len)
-                    st(a.W + (i - j + 2 * nb - 1) + j * a.ldw + q * cs, q == 0 ? f.beta : 0.0);
-            }
-            if (lane == 0) {
-                srefl[0] = f.beta;
-                srefl[1] = f.tau;
-            }
-        };
-
-        for (int t = 0; t < T; ++t) {
-            const int64_t c = k + 1 + (int64_t)t * nb;
-            const int L = (int)(a.n - c < nb ? a.n - c : nb);
-            const int64_t nq = a.n - (c + nb);
-            const int Lq = nq <= 0 ? 0 : (int)(nq < nb ? nq : nb);
-            double* U = quad[(2 * t) % 3];          // Q of step t is U of step t + 1
-            double* D = quad[(2 * t + 1) % 3];
-            double* Q = quad[(2 * t + 2) % 3];
-            double* w0 = a.W + (2 * nb - 1) + c * a.ldw;    // entry (c, c)
-
-            // The sweep ahead has finished step t + 1 (and with it stored the
-            // row its step t + 2 clears): this member's rows, one further down than
-            // there, belong to members m and m + 1 of it (the last one to
-            // member 0, in the next block); row k, which every member reads
-            // at the first step, to member 0.
-            const bool waits = k > 0 && w == 0;
-            const int32_t* ahead = a.prog + (k - 1) * G + (lane == 0 ? m : lane == 1 ? (m + 1 < G ? m + 1 : 0)
-                                                                                           : (t > 0 ? m : 0));
-            const int target = t + 2 < Tp ? t + 2 : Tp;
-            const int seen = waits ? aload(ahead) : 0;      // beside the stores still in flight
-            // the previous step's stores: published by the wave whose stores
-            // complete last
-            if (t > 0) {
-                wait_memory();
-                if (lane == 0 && __hip_atomic_fetch_add(&stored, 1, __ATOMIC_RELAXED,
-                                                        __HIP_MEMORY_SCOPE_WORKGROUP) % NW == NW - 1)
-                    __hip_atomic_store(&prog[m], t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            if (waits) {
-                const bool ok = __builtin_amdgcn_ballot_w64(seen < target) == 0 || poll(a, ahead, target);
-                if (lane == 0) flag = ok;
-            }
-            lds_barrier();
-            if (k > 0 && __builtin_amdgcn_readfirstlane(flag) == 0) return;
-            {
-                double xd[SLICE / NT], xq[SLICE / NT], xk = 0.0;
-#pragma unroll
-                for (int h = 0; h < SLICE / NT; ++h) {
-                    const int e = tid + NT * h, i = e % S, q = e / S, s = m * S + i;
-                    xd[h] = s < L && q < L ? ld(w0 + s + q * cs) : 0.0;
-                    xq[h] = s < L && q < Lq ? ld(w0 + s + (q + nb) * cs) : 0.0;
-                }
-                if (t == 0 && tid < L) xk = ld(w0 - 1 + tid * cs);       // row k
-#pragma unroll
-                for (int h = 0; h < SLICE / NT; ++h) {
-                    const int e = tid + NT * h, i = e % S, q = e / S;
-                    D[i + q * ST] = xd[h];
-                    Q[i + q * ST] = xq[h];
-                }
-                if (t == 0 && tid < NBP) xr[tid] = xk;
-            }
-            lds_barrier();
-            if (t == 0) {
-                if (w == NW - 1) right_reflector(k, c, L);
-                lds_barrier();
-            }
-
-            // right update M -= tau (M v) v^T of rows rr + 1 .. c + L - 1
-            if (!low || t > 0) {
-                double* M = (low ? U : D) + rrow + rp * ST;
-                const double tau = srefl[1];
-                double x[16], v[16], p[2] = {0.0, 0.0};
-#pragma unroll
-                for (int u = 0; u < 16; ++u) {
-                    x[u] = M[u * PR * ST];
-                    v[u] = vr[rp + PR * u];
-                }
-#pragma unroll
-                for (int u = 0; u < 16; ++u) p[u & 1] = fma(x[u], v[u], p[u & 1]);
-                const double wt = tau * sum_parts<R>(p[0] + p[1]);
-#pragma unroll
-                for (int u = 0; u < 16; ++u) x[u] = fma(-wt, v[u], x[u]);
-                if (low) {
-                    // U is final; its row 0 is rr, stored cleared already
-                    const int s = m * S + rrow;
-                    if (s > 0 && s < nb) {
-#pragma unroll
-                        for (int u = 0; u < 16; ++u)
-                            if (rp + PR * u < L) st(w0 - nb + s + (rp + PR * u) * cs, x[u]);
-                    }
-                } else {
-#pragma unroll
-                    for (int u = 0; u < 16; ++u) M[u * PR * ST] = x[u];
-                }
-            }
-            lds_barrier();
-
-            // left update M -= tau v (v^T M) of columns c + 1 .. c + nb + Lq - 1,
-            // x_0 taken as zero; column c itself becomes (beta_l, 0, ..), but
-            // stays as it is in LDS, where every wave reads x
-            double beta_l;
-            {
-                double* M = (low ? D : Q) + lcol * ST + lp;
-                const bool top = m == 0 && lp == 0;             // element 0 is row 0
-                double x[16], y[16], p[2] = {0.0, 0.0};
-#pragma unroll
-                for (int u = 0; u < 16; ++u) {
-                    y[u] = M[u * PL];
-                    x[u] = D[lp + PL * u];
-                }
-                if (top) x[0] = 0.0;
-#pragma unroll
-                for (int u = 0; u < 16; ++u) p[u & 1] = fma(x[u], y[u], p[u & 1]);
-                double dot = p[0] + p[1], ss, row0, al;
-                if (PL == 4) dot = sum_rows(dot);
-                if (PL == 2) dot = sum_halves(dot);
-                if constexpr (!GROUPED) {
-                    row0 = (low ? D : Q)[lcol * ST];
-                    al = D[0];
-                    const double xi = lane > 0 ? D[lane] : 0.0;
-                    ss = sum_parts<1>(xi * xi);
-                } else {
-                    double* slot = area + (t & 1) * (int64_t)(G + 1) * 2 * NBP;
-                    const int q = (low ? 0 : NBP) + lcol;
-                    if (lp == 0) {
-                        st(slot + m * 2 * NBP + q, dot);
-                        if (m == 0) st(slot + G * 2 * NBP + q, y[0]);
-                    }
-                    wait_memory();
-                    lds_barrier();
-                    if (w == 0) {
-                        if (lane == 0)
-                            __hip_atomic_fetch_add(&a.bar[k], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        const bool ok = poll(a, &a.bar[k], (t + 1) * G);
-                        if (lane == 0) flag = ok;
-                    }
-                    lds_barrier();
-                    if (__builtin_amdgcn_readfirstlane(flag) == 0) return;
-                    double pd[GROUP_MAX], ps[GROUP_MAX];
-#pragma unroll
-                    for (int h = 0; h < GROUP_MAX; ++h) {
-                        pd[h] = h < G ? ld(slot + h * 2 * NBP + q) : 0.0;
-                        ps[h] = h < G ? ld(slot + h * 2 * NBP) : 0.0;
-                    }
-                    row0 = ld(slot + G * 2 * NBP + q);
-                    al = ld(slot + G * 2 * NBP);
-                    dot = ss = 0.0;
-#pragma unroll
-                    for (int h = 0; h < GROUP_MAX; ++h) {
-                        dot += pd[h];
-                        ss += ps[h];
-                    }
-                }
-                const Refl f = reflector(al, ss);
-                const double wt = f.tau * fma(f.scale, dot, row0);
-                const double ws = wt * f.scale;
-                beta_l = f.beta;
-                // row k, which every member has read by now, is stored cleared
-                if (low && t == 0 && m == 0 && tid < L) st(w0 - 1 + tid * cs, tid == 0 ? srefl[0] : 0.0);
-                if (!low || lcol > 0) {
-                    if (top) y[0] -= wt;
-#pragma unroll
-                    for (int u = 0; u < 16; ++u) M[u * PL] = fma(-ws, x[u], y[u]);  // (x_0 is zero)
-                }
-                if (!low && lp == 0) xr[lcol] = row0 - wt;      // the row the next step clears
-            }
-            lds_barrier();
-
-            // D is final: whole columns of the slice; the last wave first
-            // forms the next right reflector
-            if (w == NW - 1 && Lq > 0) right_reflector(c, c + nb, Lq);
-#pragma unroll
-            for (int h = 0; h < SLICE / NT; ++h) {
-                const int e = tid + NT * h, i = e % S, q = e / S, s = m * S + i;
-                const double v = q > 0 ? D[i + q * ST] : s == 0 ? beta_l : 0.0;
-                if (s < L && q < L) st(w0 + s + q * cs, v);
-            }
-        }
-        // the whole sweep
-        wait_memory();
-        __syncthreads();
-        if (tid == 0) {
-            stored = 0;
-            __hip_atomic_store(&prog[m], T, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
-}
-
-// ---- the chase with the band held in registers -----------------------------
-//
-// When every block row of the window has workgroups of its own, nothing of
-// the band has to move: block b keeps, through all sweeps, the nb rows below
-// row c = k + 1 + b nb and in them the columns c .. c + nb - 1 (D) and
-// c + nb .. c + 2 nb - 1 (Q), in registers, and sweeps pass through the
-// blocks.  In sweep k block b
-//   * receives from block b - 1 the row that the right reflector clears
-//     (its columns are D's), forms the reflector and applies it to D;
+// Block b holds the nb rows below row c - 1, c = k + 1 + b nb, and in them the
+// columns c .. c + nb - 1 (D) and c + nb .. c + 2 nb - 1 (Q).  In sweep k it
+//   * takes the row above that the right reflector clears (its columns are
+//     D's; from block b - 1, or row k), forms the reflector and applies it to D;
 //   * forms the left reflector of D's first column and applies it to D and Q;
-//   * sends the new first row of Q to block b + 1, as the row to be cleared
+//   * gives the new first row of Q to block b + 1, as the row to be cleared
 //     there, and applies its reflector to its own other rows of Q;
 //   * moves its window one row and one column on: its first row, finished for
-//     this block, goes to block b - 1 as that one's new last row (from block
-//     0 it is the row the next sweep clears), the last row comes from b + 1.
+//     this block, becomes block b - 1's new last row (of block 0, the row the
+//     next sweep clears), its last row was the first one of block b + 1.
 // Rows and columns are held in rings of nb: row or column c + i of sweep k,
-// of D and of Q, is in slot (k + i) mod nb, so the window moves without moving
-// anything but one column of Q, which becomes D's in the same lanes, and the
-// messages, indexed by slot, need no rotation.  Rows and columns past the
-// matrix are zeros and stay zeros; a zero column or row gives the identity.
+// of D and of Q, is in slot (k + i) mod nb, so a row keeps its slot through all
+// sweeps and the window moves without moving anything but one column of Q, which
+// becomes D's in the same lanes.  Rows and columns past the matrix are +0 and
+// stay so; a zero column or row gives the identity.
 //
 // Lane l holds the columns of slots l + 64 h, wave w and register i row slot
-// 8 i + w (+ 8 RW m for member m of a group, nb > 128).  Row sums go over the
-// lanes of a wave; column sums over a wave's registers, then the waves (LDS)
-// and, in a group, the members.
+// 8 i + w (+ 8 RW m for member m of a group of ceil(nb / 64) workgroups, nb >
+// 128).  Row sums go over the lanes of a wave; column sums over a wave's
+// registers, then the waves (LDS) and, in a group, the members.
 //
-// A message is its values: an inbox word holds MARK, a NaN no arithmetic
-// gives (and senders replace), until the value comes; the receiver polls the
-// words it needs and sets them back.  Two inboxes by parity are enough: what
-// a receiver reads in sweep k is set back before it leaves sweep k + 1, and
-// no value of sweep k + 2 can be sent to it before that.
-//
-// What bounds it: the chain of 2 n steps, a message (about 1.3 us from the
-// store to the polling load that sees it) and the step's own chain (reflector,
-// row sums, column sums over the waves, reflector) each; the rest of a step's
-// work falls into the time the block waits anyway, as a block works in every
-// other step only.  A step takes 1.8 us (nb = 32), 2.1 (64), 2.9 (128) and 4.6
-// (256, with the exchange between four members).  Against the chase by sweeps
-// below: 2000 at nb = 64 24.7 -> 8.0 ms, 8192 at nb = 256 232 -> 76.5 ms, 16384
-// at nb = 128 333 -> 96.4 ms, 9000 at nb = 16 99 -> 40 ms.
-//
-// All workgroups have to run at once, so they meet first; if they have not
-// met within MEET_SECONDS (other work holds compute units) the launch ends
-// without having done anything, and the chase by sweeps, which needs no more
-// than one running group, does the work.
+// Members exchange values through boxes whose words hold MARK, a NaN no
+// arithmetic gives (and senders replace), until a value comes; the receiver
+// polls the words it needs and sets them back.  Two boxes by the parity of the
+// step are enough: what a receiver reads in one step is set back before it
+// sends anything in the next, and no value of the one after that can be sent to
+// it before.
 constexpr uint64_t MARK = 0x7FF4B1D1A60CA11Eull;
-constexpr double MEET_SECONDS = 2e-3;
-
-struct HoldArgs {
-    const double* B;
-    int64_t rs, cs, n;
-    int nb;
-    int group;            // workgroups per block
-    int32_t* ctrl;
-    double* box;          // inboxes, per workgroup
-    double* d;
-    double* e;
-    int64_t watchdog_ticks, meet_ticks;
-};
-
-// An inbox: two rows to clear, two last rows (and a diagonal entry behind
-// each), for groups two sets of the members' column sums and of row 0.
-constexpr int box_row(int ch) { return 64 * ch; }
-constexpr int box_last(int ch) { return 64 * ch + 8; }
-constexpr int box_sums(int ch, int group) { return ch <= 2 ? 0 : (group + 1) * 128 * ch; }
-constexpr int box_doubles(int ch, int group) { return 2 * (box_row(ch) + box_last(ch) + box_sums(ch, group)); }
 
 __device__ __forceinline__ bool marked(double v) { return __builtin_bit_cast(uint64_t, v) == MARK; }
 __device__ __forceinline__ void send(double* p, double v) {
@@ -551,7 +207,7 @@ __device__ __forceinline__ void set_back(double* p) { st(p, __builtin_bit_cast(d
 // Called by a whole wave: v[h] = p[h * stride] where use, once none of them
 // is MARK; false when an error was reported or the watchdog fired.
 template <int N>
-__device__ __forceinline__ bool await(const HoldArgs& a, const double* p, int stride, const bool (&use)[N],
+__device__ __forceinline__ bool await(const Waits& a, const double* p, int stride, const bool (&use)[N],
                                       double (&v)[N]) {
     uint64_t t0 = 0;
     for (int tries = 0;; ++tries) {
@@ -573,26 +229,6 @@ __device__ __forceinline__ bool await(const HoldArgs& a, const double* p, int st
                 return false;
             }
         }
-    }
-}
-
-// One thread of each workgroup: whether all of them are running.
-__device__ __forceinline__ bool meet(const HoldArgs& a) {
-    const uint64_t t0 = wall_clock64();
-    int none = 0;
-    if (__hip_atomic_fetch_add(&a.ctrl[G_RUNNING], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-        (int)gridDim.x - 1)
-        __hip_atomic_compare_exchange_strong(&a.ctrl[G_MET], &none, (int)MET_GO, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT);
-    for (;;) {
-        const int met = aload(&a.ctrl[G_MET]);
-        if (met != 0) return met == MET_GO;
-        if ((int64_t)(wall_clock64() - t0) > a.meet_ticks) {
-            none = 0;
-            __hip_atomic_compare_exchange_strong(&a.ctrl[G_MET], &none, (int)MET_GIVE_UP, __ATOMIC_RELAXED,
-                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        __builtin_amdgcn_s_sleep(4);
     }
 }
 
@@ -657,20 +293,269 @@ __device__ __forceinline__ void wave_sums(double (&p)[RW]) {
     }
 }
 
-template <int CH, int RW>
-__global__ __launch_bounds__(NT) void hold_kernel(HoldArgs a) {
+// v for one comparison: a chain of them on one value becomes a switch, at whose
+// end every register that its cases change would be copied.
+__device__ __forceinline__ int apart(int v) {
+    asm("" : "+s"(v));
+    return v;
+}
+
+constexpr int box_sums(int ch, int group) { return ch <= 2 ? 0 : (group + 1) * 128 * ch; }
+
+// Workgroups that run a block: how many, which one this is, its boxes for the
+// others' column sums and row 0 (two parities), doubles between two members'.
+struct Group {
+    int G, m;
+    double* box;
+    int64_t stride;
+};
+
+template <int CH>
+struct StepLds {
+    double part[NW][128 * CH];          // column sums of each wave
+    double total[128 * CH];             // of the block
+    double row0[2][128 * CH];           // the first row, by parity of the step
+    int fail[2];
+};
+
+// par: the step's parity; i0: slot of the first row and column; v: the row to
+// clear; ok: whether the caller's waits were.  send_row(g) is given the row the
+// next block clears, send_last(fr, fl, fg, last) the rest of the finished first
+// row: last with fg's beta in slot i0, fl's beta on the diagonal.  The first
+// row's registers end as zeros.  Ends the workgroup where a wait failed (an exit
+// of the kernel, not a result: D and Q would be copied where the paths meet).
+template <int CH, int RW, class Row, class Last>
+__device__ __forceinline__ void block_step(const Waits& a, StepLds<CH>& s, const Group& gr, int par, int i0, bool ok,
+                                           double (&D)[RW][CH], double (&Q)[RW][CH], double (&v)[CH], Row&& send_row,
+                                           Last&& send_last) {
     constexpr int NBP = 64 * CH;
     constexpr int PARTS = NW * CH / 4;          // waves' sums a lane adds: 2, 4, 8
     constexpr bool GROUPED = CH == 4;
-    __shared__ double part[NW][2 * NBP];        // column sums of each wave
-    __shared__ double total[2 * NBP];           // of the block
-    __shared__ double row0[2][2 * NBP];         // the first row, by parity of the sweep
-    __shared__ int fail[2], go;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int G = GROUPED ? gr.G : 1, m = GROUPED ? gr.m : 0;
+    const int l0 = i0 % 64, h0 = i0 / 64;
+    auto first = [&](const double (&x)[CH]) {       // entry of slot i0, uniform
+        double y = x[0];
+#pragma unroll
+        for (int h = 1; h < CH; ++h) {
+            double z = x[h];
+            asm("" : "+v"(z));              // a value, not an address to choose
+            y = h == h0 ? z : y;
+        }
+        return lane_value(y, l0);
+    };
+    auto clear = [&](double (&x)[CH]) {             // row x becomes the reflector's v
+        double ss = 0.0;
+#pragma unroll
+        for (int h = 0; h < CH; ++h) {
+            const double y = lane + 64 * h == i0 ? 0.0 : x[h];
+            ss = fma(y, y, ss);
+        }
+        const Refl f = reflector(first(x), sum_parts<1>(ss));
+#pragma unroll
+        for (int h = 0; h < CH; ++h) x[h] = lane + 64 * h == i0 ? 1.0 : f.scale * x[h];
+        return f;
+    };
+    auto from_right = [&](double (&M)[RW][CH], const double (&x)[CH], double tau) {
+        double p[RW];
+#pragma unroll
+        for (int i = 0; i < RW; ++i) {
+            p[i] = M[i][0] * x[0];
+#pragma unroll
+            for (int h = 1; h < CH; ++h) p[i] = fma(M[i][h], x[h], p[i]);
+        }
+        wave_sums<RW>(p);
+        double tx[CH];
+#pragma unroll
+        for (int h = 0; h < CH; ++h) tx[h] = -tau * x[h];
+#pragma unroll
+        for (int i = 0; i < RW; ++i)
+#pragma unroll
+            for (int h = 0; h < CH; ++h) M[i][h] = fma(p[i], tx[h], M[i][h]);
+    };
+    const Refl fr = clear(v);
+    from_right(D, v, fr.tau);
+
+    // the first row leaves the registers
+    const bool gives = w == i0 % 8 && (!GROUPED || m == i0 / (8 * RW));
+    if (gives) {
+        const int reg = i0 / 8 % RW;
+#pragma unroll
+        for (int i = 0; i < RW; ++i)
+            if (__builtin_expect(i == apart(reg), 0)) {
+#pragma unroll
+                for (int h = 0; h < CH; ++h) {
+                    s.row0[par][lane + 64 * h] = D[i][h];
+                    s.row0[par][NBP + lane + 64 * h] = Q[i][h];
+                    D[i][h] = Q[i][h] = 0.0;
+                    asm volatile("" : "+v"(D[i][h]), "+v"(Q[i][h]));
+                }
+            }
+    }
+    // column sums x^T (D, Q), x the first column below the first row
+    double x[RW];
+    {
+        double pd[CH], pq[CH];
+#pragma unroll
+        for (int i = 0; i < RW; ++i) x[i] = first(D[i]);
+#pragma unroll
+        for (int h = 0; h < CH; ++h) {
+            pd[h] = pq[h] = 0.0;
+#pragma unroll
+            for (int i = 0; i < RW; ++i) {
+                pd[h] = fma(x[i], D[i][h], pd[h]);
+                pq[h] = fma(x[i], Q[i][h], pq[h]);
+            }
+            s.part[w][lane + 64 * h] = pd[h];
+            s.part[w][NBP + lane + 64 * h] = pq[h];
+        }
+    }
+    if (!ok) s.fail[par] = 1;
+    wait_memory();                          // words set back in the last step
+    lds_barrier();
+    if (__builtin_amdgcn_readfirstlane(s.fail[par]) != 0) __builtin_amdgcn_endpgm();
+    {
+        const int col = w * 16 * CH + lane % (16 * CH), sub = lane / (16 * CH);
+        double sum = 0.0;
+#pragma unroll
+        for (int h = 0; h < PARTS; ++h) sum += s.part[sub * PARTS + h][col];
+        if constexpr (CH == 1) sum = sum_rows(sum);
+        if constexpr (CH == 2) sum = sum_halves(sum);
+        if constexpr (GROUPED) {
+            // the members' sums and, from the one that has it, row 0
+            double* own = gr.box + par * (int64_t)box_sums(CH, G);
+            const int holder = i0 / (8 * RW);
+            const double r0 = s.row0[par][col];
+            for (int o = 1; o < G; ++o) {
+                const int to = m + o < G ? m + o : m + o - G;
+                double* other = own + (to - m) * gr.stride;
+                send(other + m * 2 * NBP + col, sum);
+                if (m == holder) send(other + G * 2 * NBP + col, r0);
+            }
+            // four members at most, row 0 behind them
+            bool from[4];
+            const bool from0[1] = {m != holder};
+#pragma unroll
+            for (int h = 0; h < 4; ++h) from[h] = h < G && h != m;
+            double y[4], y0[1];
+            bool ok2 = await(a, own + col, 2 * NBP, from, y);
+            ok2 = await(a, own + G * 2 * NBP + col, 0, from0, y0) && ok2;
+#pragma unroll
+            for (int h = 0; h < 4; ++h) {
+                if (from[h]) set_back(own + h * 2 * NBP + col);
+                y[h] = h == m ? sum : y[h];
+            }
+            if (from0[0]) {
+                set_back(own + G * 2 * NBP + col);
+                s.row0[par][col] = y0[0];
+            }
+            sum = (y[0] + y[1]) + (y[2] + y[3]);
+            if (!ok2) s.fail[par] = 1;
+        }
+        if (sub == 0) s.total[col] = sum;
+    }
+    lds_barrier();
+    if (GROUPED && __builtin_amdgcn_readfirstlane(s.fail[par]) != 0) __builtin_amdgcn_endpgm();
+
+    // left reflector; the new first row
+    const Refl fl = reflector(s.row0[par][i0], s.total[i0]);
+    double td[CH], tq[CH], g[CH], last[CH];
+#pragma unroll
+    for (int h = 0; h < CH; ++h) {
+        const double rd = s.row0[par][lane + 64 * h], rq = s.row0[par][NBP + lane + 64 * h];
+        td[h] = fma(fl.scale, s.total[lane + 64 * h], rd);
+        tq[h] = fma(fl.scale, s.total[NBP + lane + 64 * h], rq);
+        last[h] = fma(-fl.tau, td[h], rd);
+        g[h] = fma(-fl.tau, tq[h], rq);
+        td[h] *= -fl.tau * fl.scale;
+        tq[h] *= -fl.tau * fl.scale;
+    }
+    send_row(g);
+    const Refl fg = clear(g);
+    send_last(fr, fl, fg, last);
+    // the other rows: from the left, then Q from the right
+#pragma unroll
+    for (int i = 0; i < RW; ++i)
+#pragma unroll
+        for (int h = 0; h < CH; ++h) {
+            D[i][h] = fma(x[i], td[h], D[i][h]);
+            Q[i][h] = fma(x[i], tq[h], Q[i][h]);
+        }
+    from_right(Q, g, fg.tau);
+}
+
+// ---- the chase with the band held in registers -----------------------------
+//
+// Every block has its workgroups, which keep it through all sweeps: nothing of
+// the band moves, and what blocks give each other are messages of one row.  A
+// message is its values, in inboxes of MARK words as above, by the parity of
+// the sweep; indexed by slot, it needs no rotation.
+//
+// What bounds it: the chain of 2 n steps, a message (about 1.3 us from the
+// store to the polling load that sees it) and the step's own chain (reflector,
+// row sums, column sums over the waves, reflector) each; the rest of a step's
+// work falls into the time the block waits anyway, as a block works in every
+// other step only.  A step takes 1.8 us (nb = 32), 2.1 (64), 2.9 (128) and 4.6
+// (256, with the exchange between four members).
+//
+// All workgroups have to run at once, so they meet first; if they have not
+// met within MEET_SECONDS (other work holds compute units) the launch ends
+// without having done anything, and the chase by sweeps, which needs no more
+// than one running group, does the work.
+constexpr double MEET_SECONDS = 2e-3;
+
+struct HoldArgs {
+    Waits wait;
+    const double* B;
+    int64_t rs, cs, n;
+    int nb;
+    int group;            // workgroups per block
+    double* box;          // inboxes, per workgroup
+    double* d;
+    double* e;
+    int64_t meet_ticks;
+};
+
+// An inbox: two rows to clear, two last rows (and a diagonal entry behind
+// each), for groups the exchange's boxes.
+constexpr int box_row(int ch) { return 64 * ch; }
+constexpr int box_last(int ch) { return 64 * ch + 8; }
+constexpr int box_doubles(int ch, int group) { return 2 * (box_row(ch) + box_last(ch) + box_sums(ch, group)); }
+
+enum : int { MET_GO = 1, MET_GIVE_UP = 2 };     // the word G_MET
+
+// One thread of each workgroup: whether all of them are running.
+__device__ __forceinline__ bool meet(const HoldArgs& a) {
+    const uint64_t t0 = wall_clock64();
+    int none = 0;
+    if (__hip_atomic_fetch_add(&a.wait.ctrl[G_RUNNING], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+        (int)gridDim.x - 1)
+        __hip_atomic_compare_exchange_strong(&a.wait.ctrl[G_MET], &none, (int)MET_GO, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+    for (;;) {
+        const int met = aload(&a.wait.ctrl[G_MET]);
+        if (met != 0) return met == MET_GO;
+        if ((int64_t)(wall_clock64() - t0) > a.meet_ticks) {
+            none = 0;
+            __hip_atomic_compare_exchange_strong(&a.wait.ctrl[G_MET], &none, (int)MET_GIVE_UP, __ATOMIC_RELAXED,
+                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __builtin_amdgcn_s_sleep(4);
+    }
+}
+
+template <int CH, int RW>
+__global__ __launch_bounds__(NT) void hold_kernel(HoldArgs a) {
+    constexpr int NBP = 64 * CH;
+    constexpr bool GROUPED = CH == 4;
+    __shared__ StepLds<CH> lds;
+    __shared__ int go;
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (tid == 0) {
-        fail[0] = fail[1] = 0;
-        go = meet(a) && aload(&a.ctrl[G_ERROR]) == 0;   // (an error reported before stops the chase)
+        lds.fail[0] = lds.fail[1] = 0;
+        go = meet(a) && aload(&a.wait.ctrl[G_ERROR]) == 0;  // (an error reported before stops the chase)
     }
     __syncthreads();
     if (__builtin_amdgcn_readfirstlane(go) == 0) return;
@@ -679,7 +564,7 @@ __global__ __launch_bounds__(NT) void hold_kernel(HoldArgs a) {
     const int size = box_doubles(CH, G);
     double* box = a.box + (int64_t)blockIdx.x * size;
     double* box_l = box + 2 * box_row(CH);
-    double* box_x = box_l + 2 * box_last(CH);
+    const Group gr{G, m, box_l + 2 * box_last(CH), size};
     const int64_t K = a.n - 1 - (int64_t)b * nb, Kn = K - nb;   // sweeps of this block, of the next
     bool use[CH];
     double D[RW][CH], Q[RW][CH];
@@ -706,12 +591,12 @@ __global__ __launch_bounds__(NT) void hold_kernel(HoldArgs a) {
         if (takes) {
             double x[CH], diag[1];
             const bool one[1] = {true};
-            ok = await(a, box_l + (par ^ 1) * box_last(CH) + lane, 64, use, x);
-            ok = ok && await(a, box_l + (par ^ 1) * box_last(CH) + NBP, 0, one, diag);
+            ok = await(a.wait, box_l + (par ^ 1) * box_last(CH) + lane, 64, use, x);
+            ok = ok && await(a.wait, box_l + (par ^ 1) * box_last(CH) + NBP, 0, one, diag);
             const int reg = ip / 8 % RW;
 #pragma unroll
             for (int i = 0; i < RW; ++i)
-                if (i == reg) {
+                if (__builtin_expect(i == apart(reg), 0)) {
 #pragma unroll
                     for (int h = 0; h < CH; ++h) {
                         D[i][h] = lane + 64 * h == ip ? diag[0] : 0.0;
@@ -720,11 +605,10 @@ __global__ __launch_bounds__(NT) void hold_kernel(HoldArgs a) {
                     }
                 }
         }
-        // the row to clear, its reflector and D (I - tau v v^T)
-        const int l0 = i0 % 64, h0 = i0 / 64;
+        // the row to clear
         double v[CH];
         if (b > 0 || k > 0) {
-            ok = await(a, box + par * box_row(CH) + lane, 64, use, v) && ok;
+            ok = await(a.wait, box + par * box_row(CH) + lane, 64, use, v) && ok;
         } else {
 #pragma unroll
             for (int h = 0; h < CH; ++h) {
@@ -732,195 +616,52 @@ __global__ __launch_bounds__(NT) void hold_kernel(HoldArgs a) {
                 v[h] = use[h] && col < a.n ? a.B[col * a.cs] : 0.0;
             }
         }
-        auto first = [&](const double (&x)[CH]) {       // entry of slot i0, uniform
-            double y = x[0];
+        block_step<CH, RW>(
+            a.wait, lds, gr, par, i0, ok, D, Q, v,
+            [&](const double (&g)[CH]) {
+                if (w == 0 && k < Kn) {
+                    double* to = box + (int64_t)G * size + par * box_row(CH) + lane;
 #pragma unroll
-            for (int h = 1; h < CH; ++h) {
-                double z = x[h];
-                asm("" : "+v"(z));              // a value, not an address to choose
-                y = h == h0 ? z : y;
-            }
-            return lane_value(y, l0);
-        };
-        auto clear = [&](double (&x)[CH]) {             // row x becomes the reflector's v
-            double ss = 0.0;
+                    for (int h = 0; h < CH; ++h)
+                        if (use[h]) send(to + 64 * h, g[h]);
+                }
+            },
+            [&](const Refl& fr, const Refl& fl, const Refl& fg, const double (&last)[CH]) {
+                if (w == 1) {
+                    if (b > 0) {
+                        if (!GROUPED || m == i0 / (8 * RW)) {
+                            double* to = box_l - (int64_t)G * size + par * box_last(CH);
 #pragma unroll
-            for (int h = 0; h < CH; ++h) {
-                const double y = lane + 64 * h == i0 ? 0.0 : x[h];
-                ss = fma(y, y, ss);
-            }
-            const Refl f = reflector(first(x), sum_parts<1>(ss));
+                            for (int h = 0; h < CH; ++h)
+                                if (use[h]) send(to + lane + 64 * h, lane + 64 * h == i0 ? fg.beta : last[h]);
+                            if (lane == 0) send(to + NBP, fl.beta);
+                        }
+                    } else {
+                        if (k + 1 < K) {
+                            double* to = box + (par ^ 1) * box_row(CH) + lane;
 #pragma unroll
-            for (int h = 0; h < CH; ++h) x[h] = lane + 64 * h == i0 ? 1.0 : f.scale * x[h];
-            return f;
-        };
-        auto from_right = [&](double (&M)[RW][CH], const double (&x)[CH], double tau) {
-            double p[RW];
-#pragma unroll
-            for (int i = 0; i < RW; ++i) {
-                p[i] = M[i][0] * x[0];
-#pragma unroll
-                for (int h = 1; h < CH; ++h) p[i] = fma(M[i][h], x[h], p[i]);
-            }
-            wave_sums<RW>(p);
-            double tx[CH];
-#pragma unroll
-            for (int h = 0; h < CH; ++h) tx[h] = -tau * x[h];
-#pragma unroll
-            for (int i = 0; i < RW; ++i)
-#pragma unroll
-                for (int h = 0; h < CH; ++h) M[i][h] = fma(p[i], tx[h], M[i][h]);
-        };
-        const Refl fr = clear(v);
-        from_right(D, v, fr.tau);
-        if (b == 0 && m == 0 && tid == 0) a.e[k] = fr.beta;
-
-        // the first row leaves the registers
-        const bool gives = w == i0 % 8 && (!GROUPED || m == i0 / (8 * RW));
-        if (gives) {
-            const int reg = i0 / 8 % RW;
-#pragma unroll
-            for (int i = 0; i < RW; ++i)
-                if (i == reg) {
-#pragma unroll
-                    for (int h = 0; h < CH; ++h) {
-                        row0[par][lane + 64 * h] = D[i][h];
-                        row0[par][NBP + lane + 64 * h] = Q[i][h];
-                        D[i][h] = Q[i][h] = 0.0;
-                        asm volatile("" : "+v"(D[i][h]), "+v"(Q[i][h]));
+                            for (int h = 0; h < CH; ++h)
+                                if (use[h]) send(to + 64 * h, lane + 64 * h == i0 ? fg.beta : last[h]);
+                        }
+                        if (m == 0 && lane == 0) {
+                            a.e[k] = fr.beta;
+                            a.d[k + 1] = fl.beta;
+                        }
                     }
                 }
-        }
-        // column sums x^T (D, Q), x the first column below the first row
-        double x[RW];
-        {
-            double pd[CH], pq[CH];
-#pragma unroll
-            for (int i = 0; i < RW; ++i) x[i] = first(D[i]);
-#pragma unroll
-            for (int h = 0; h < CH; ++h) {
-                pd[h] = pq[h] = 0.0;
-#pragma unroll
-                for (int i = 0; i < RW; ++i) {
-                    pd[h] = fma(x[i], D[i][h], pd[h]);
-                    pq[h] = fma(x[i], Q[i][h], pq[h]);
-                }
-                part[w][lane + 64 * h] = pd[h];
-                part[w][NBP + lane + 64 * h] = pq[h];
-            }
-        }
-        if (!ok) fail[par] = 1;
-        wait_memory();                          // inbox words set back in the last sweep
-        lds_barrier();
-        if (__builtin_amdgcn_readfirstlane(fail[par]) != 0) return;
-        {
-            const int col = w * 16 * CH + lane % (16 * CH), sub = lane / (16 * CH);
-            double s = 0.0;
-#pragma unroll
-            for (int h = 0; h < PARTS; ++h) s += part[sub * PARTS + h][col];
-            if constexpr (CH == 1) s = sum_rows(s);
-            if constexpr (CH == 2) s = sum_halves(s);
-            if constexpr (GROUPED) {
-                // the members' sums and, from the one that has it, row 0
-                const int64_t slot = par * (int64_t)box_sums(CH, G);
-                const int holder = i0 / (8 * RW);
-                const double r0 = row0[par][col];
-                for (int o = 1; o < G; ++o) {
-                    const int to = m + o < G ? m + o : m + o - G;
-                    double* other = box_x + (int64_t)(to - m) * size + slot;
-                    send(other + m * 2 * NBP + col, s);
-                    if (m == holder) send(other + G * 2 * NBP + col, r0);
-                }
-                bool from[5];
-                double y[5];
-#pragma unroll
-                for (int h = 0; h < 4; ++h) from[h] = h < G && h != m;
-                from[4] = m != holder;
-                // four members at most, row 0 behind them
-                bool ok2 = true;
-                {
-                    const bool f4[4] = {from[0], from[1], from[2], from[3]};
-                    double y4[4], y1[1];
-                    const bool f1[1] = {from[4]};
-                    ok2 = await(a, box_x + slot + col, 2 * NBP, f4, y4);
-                    ok2 = await(a, box_x + slot + G * 2 * NBP + col, 0, f1, y1) && ok2;
-#pragma unroll
-                    for (int h = 0; h < 4; ++h) y[h] = h == m ? s : y4[h];
-                    y[4] = y1[0];
-                }
-#pragma unroll
-                for (int h = 0; h < 4; ++h)
-                    if (from[h]) set_back(box_x + slot + h * 2 * NBP + col);
-                if (from[4]) set_back(box_x + slot + G * 2 * NBP + col);
-                s = ((y[0] + y[1]) + (y[2] + y[3]));
-                if (from[4]) row0[par][col] = y[4];
-                if (!ok2) fail[par] = 1;
-            }
-            if (sub == 0) total[col] = s;
-        }
-        lds_barrier();
-        if (GROUPED && __builtin_amdgcn_readfirstlane(fail[par]) != 0) return;
-
-        // left reflector; the new first row
-        const Refl fl = reflector(row0[par][i0], total[i0]);
-        double td[CH], tq[CH], g[CH], last[CH];
-#pragma unroll
-        for (int h = 0; h < CH; ++h) {
-            const double rd = row0[par][lane + 64 * h], rq = row0[par][NBP + lane + 64 * h];
-            td[h] = fl.tau * fma(fl.scale, total[lane + 64 * h], rd);
-            tq[h] = fl.tau * fma(fl.scale, total[NBP + lane + 64 * h], rq);
-            last[h] = rd - td[h];
-            g[h] = rq - tq[h];
-            td[h] *= -fl.scale;
-            tq[h] *= -fl.scale;
-        }
-        if (w == 0 && k < Kn) {
-            double* to = box + (int64_t)G * size + par * box_row(CH) + lane;
-#pragma unroll
-            for (int h = 0; h < CH; ++h)
-                if (use[h]) send(to + 64 * h, g[h]);
-        }
-        const Refl fg = clear(g);
-        if (w == 1) {
-            if (b > 0) {
-                if (!GROUPED || m == i0 / (8 * RW)) {
-                    double* to = box_l - (int64_t)G * size + par * box_last(CH);
+                // words read in this sweep are set back
+                if (w == NW - 1 && (b > 0 || k > 0)) {
 #pragma unroll
                     for (int h = 0; h < CH; ++h)
-                        if (use[h]) send(to + lane + 64 * h, lane + 64 * h == i0 ? fg.beta : last[h]);
-                    if (lane == 0) send(to + NBP, fl.beta);
+                        if (use[h]) set_back(box + par * box_row(CH) + lane + 64 * h);
                 }
-            } else {
-                if (k + 1 < K) {
-                    double* to = box + (par ^ 1) * box_row(CH) + lane;
+                if (takes) {
 #pragma unroll
                     for (int h = 0; h < CH; ++h)
-                        if (use[h]) send(to + 64 * h, lane + 64 * h == i0 ? fg.beta : last[h]);
+                        if (use[h]) set_back(box_l + (par ^ 1) * box_last(CH) + lane + 64 * h);
+                    if (lane == 0) set_back(box_l + (par ^ 1) * box_last(CH) + NBP);
                 }
-                if (m == 0 && lane == 0) a.d[k + 1] = fl.beta;
-            }
-        }
-        // words read in this sweep are set back
-        if (w == NW - 1 && (b > 0 || k > 0)) {
-#pragma unroll
-            for (int h = 0; h < CH; ++h)
-                if (use[h]) set_back(box + par * box_row(CH) + lane + 64 * h);
-        }
-        if (takes) {
-#pragma unroll
-            for (int h = 0; h < CH; ++h)
-                if (use[h]) set_back(box_l + (par ^ 1) * box_last(CH) + lane + 64 * h);
-            if (lane == 0) set_back(box_l + (par ^ 1) * box_last(CH) + NBP);
-        }
-        // the other rows: from the left, then Q from the right
-#pragma unroll
-        for (int i = 0; i < RW; ++i)
-#pragma unroll
-            for (int h = 0; h < CH; ++h) {
-                D[i][h] = fma(x[i], td[h], D[i][h]);
-                Q[i][h] = fma(x[i], tq[h], Q[i][h]);
-            }
-        from_right(Q, g, fg.tau);
+            });
         // Q's first column becomes D's last
 #pragma unroll
         for (int h = 0; h < CH; ++h) {
@@ -936,6 +677,185 @@ __global__ __launch_bounds__(NT) void hold_kernel(HoldArgs a) {
     }
 }
 
+// ---- the chase by sweeps ----------------------------------------------------
+//
+// The band is copied into an array with room for the fill of the chase (nb - 1
+// diagonals below the main one, 2 nb - 1 above), by rows:
+//     W[(j - i + nb - 1) + i * 3 nb]  holds entry (i, j).
+// One persistent launch: each workgroup takes the next sweep, or the next
+// member's place in a group that runs one (tickets from an atomic counter, so
+// a sweep is only ever waited for by a later one that running workgroups hold:
+// no deadlock for any grid), and runs its blocks in order: it loads a member's
+// rows of the block, does the step, stores them, and keeps the row the next
+// block clears.  A row keeps its slot and so its member, and block b of sweep k
+// takes the rows that block b of sweep k - 1 left and, as its last one, the first
+// row of block b + 1, so member m waits for member m of the sweep ahead alone
+// (for row k also for the one that has it).  A block publishes its first row
+// before its others: less than two steps separate consecutive sweeps.
+//
+// The band array is written and read with agent-scope stores and loads (past
+// the XCD's L2, at the coherence point), so a counter is published once every
+// wave has waited for its own memory operations, with no L2 write-back, and the
+// loads that follow a counter's load see every store performed before it was
+// written, with no L2 invalidation; a wall-clock watchdog bounds every wait.
+//
+// What bounds it: the chain of about 2 n steps, in each the round trips to the
+// coherence point (the poll of the sweep ahead, a member's rows in, up to 256
+// KB, and out, for groups the exchange) and the step itself.  A block's stores
+// complete while the next one's wait is polled and its rows are loaded.
+// Measured, with slices of rows in LDS on up to 16 workgroups a sweep (whose sums
+// were others than the held chase's) and so: 20000 at nb = 16 300 and 169 ms, 50000
+// at nb = 64 760 and 652 ms, 40000 at nb = 128 1326 and 1135 ms, 20000 at nb =
+// 256 983 and 594 ms.  Where the band can be held: 2000 at nb = 64 15.8 ms (held
+// 7.7), 16384 at nb = 128 449 (96), 8192 at nb = 256 225 ms (74).
+struct SweepArgs {
+    Waits wait;
+    double* W;
+    int64_t n;
+    int nb;
+    int nsweeps;
+    int group;            // workgroups per sweep
+    int32_t* prog;        // t + 1: blocks < t and the first row of block t stored, per sweep and member
+                          // (T + 1: all T blocks)
+    double* xch;          // exchange areas (group > 1): two parities a member
+    int nareas;
+    double* d;
+    double* e;
+    const int32_t* met;   // the meeting of hold_kernel before this launch, or null
+};
+
+template <int CH, int RW>
+__global__ __launch_bounds__(NT) void sweep_kernel(SweepArgs a) {
+    constexpr bool GROUPED = CH == 4;
+    __shared__ StepLds<CH> lds;
+    __shared__ int sk, flag;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nb = a.nb, G = GROUPED ? a.group : 1;
+    const int64_t rowp = 3 * (int64_t)nb - 1;           // from entry (i, j) to (i + 1, j)
+    if (tid == 0) lds.fail[0] = lds.fail[1] = 0;
+    if (a.met && aload(a.met) == MET_GO) return;
+
+    for (;;) {
+        // ticket = sweep * G + member: a group's members are consecutive
+        // tickets, all taken by running workgroups before any of them can
+        // be needed by a later sweep
+        if (tid == 0) sk = __hip_atomic_fetch_add(&a.wait.ctrl[G_HEAD], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        const int ticket = __builtin_amdgcn_readfirstlane(sk);
+        __syncthreads();
+        const int64_t k = ticket / G;
+        const int m = ticket - (int)k * G;
+        if (k >= a.nsweeps) return;
+        const int T = (int)nsteps(a.n, nb, k);
+        const int Tp = k > 0 ? (int)nsteps(a.n, nb, k - 1) : 0;
+        int32_t* prog = a.prog + k * G;
+        const int64_t sums = 2 * (int64_t)box_sums(CH, G);
+        const Group gr{G, m, GROUPED ? a.xch + (k % a.nareas * G + m) * sums : nullptr, sums};
+        const int i0 = (int)(k % nb);                       // slot of the first row and column
+        const int ahead_holder = GROUPED && k > 0 ? (int)((k - 1) % nb) / (8 * RW) : 0;     // has row k
+        bool use[CH];
+        int off[CH];                                        // column of a slot, from the block's first
+        double v[CH];
+#pragma unroll
+        for (int h = 0; h < CH; ++h) {
+            const int q = lane + 64 * h;
+            use[h] = q < nb;
+            off[h] = q < i0 ? q - i0 + nb : q - i0;
+        }
+
+        for (int t = 0; t < T; ++t) {
+            const int64_t c = k + 1 + (int64_t)t * nb;
+            double* w0 = a.W + c * rowp + c + nb - 1;       // entry (c, c)
+            // block t of the sweep ahead and the first row of its block t + 1
+            const bool waits = k > 0 && w == 0;
+            const int32_t* ahead = a.prog + (k - 1) * G + (lane == 1 && t == 0 ? ahead_holder : m);
+            if (waits) {
+                const bool ok = poll(a.wait, ahead, t + 1 < Tp ? t + 2 : Tp + 1);
+                if (lane == 0) flag = ok;
+            }
+            lds_barrier();
+            if (k > 0 && __builtin_amdgcn_readfirstlane(flag) == 0) return;
+
+            // what does not exist is loaded from entry (c, c) or the row's
+            // first, so that no load is behind a branch, and taken as zero
+            const int64_t left = a.n - c;                   // rows and columns from c on
+            double D[RW][CH], Q[RW][CH];
+            int row[RW];                                    // from c; nb: does not exist
+#pragma unroll
+            for (int i = 0; i < RW; ++i) {
+                const int r = 8 * (RW * m + i) + w, o = r < i0 ? r - i0 + nb : r - i0;
+                row[i] = r < nb && o < left ? o : nb;
+                const double* p = w0 + (row[i] < nb ? row[i] * rowp : 0);
+#pragma unroll
+                for (int h = 0; h < CH; ++h) {
+                    D[i][h] = ld(p + (use[h] && off[h] < left ? off[h] : 0));
+                    Q[i][h] = ld(p + (use[h] && off[h] + nb < left ? off[h] + nb : 0));
+                }
+            }
+            if (t == 0) {
+#pragma unroll
+                for (int h = 0; h < CH; ++h) {
+                    const bool in = use[h] && off[h] < left;
+                    v[h] = ld(w0 - rowp + (in ? off[h] : 0));       // row k
+                    v[h] = in ? v[h] : 0.0;
+                }
+                if (k == 0 && m == 0 && tid == 0) a.d[0] = ld(a.W + nb - 1);
+            }
+#pragma unroll
+            for (int i = 0; i < RW; ++i)
+#pragma unroll
+                for (int h = 0; h < CH; ++h) {
+                    D[i][h] = row[i] < nb && use[h] && off[h] < left ? D[i][h] : 0.0;
+                    Q[i][h] = row[i] < nb && use[h] && off[h] + nb < left ? Q[i][h] : 0.0;
+                }
+
+            double next[CH];
+            block_step<CH, RW>(
+                a.wait, lds, gr, t & 1, i0, true, D, Q, v,
+                [&](const double (&g)[CH]) {
+#pragma unroll
+                    for (int h = 0; h < CH; ++h) next[h] = g[h];
+                },
+                [&](const Refl& fr, const Refl& fl, const Refl& fg, const double (&last)[CH]) {
+                    if (w == 1 && (!GROUPED || m == i0 / (8 * RW))) {       // the finished first row
+#pragma unroll
+                        for (int h = 0; h < CH; ++h) {
+                            if (use[h] && off[h] < left) st(w0 + off[h], off[h] == 0 ? fl.beta : last[h]);
+                            if (use[h] && off[h] + nb < left) st(w0 + off[h] + nb, off[h] == 0 ? fg.beta : 0.0);
+                        }
+                    }
+                    if (w == 1 && lane == 0 && t == 0 && m == 0) {
+                        a.e[k] = fr.beta;
+                        a.d[k + 1] = fl.beta;
+                    }
+                });
+            // The previous block's stores had completed in every wave at the
+            // step's first barrier, and the first row, which this block's
+            // rows below no longer touch, has in the wave that stored it.
+            if (w == 1) {
+                wait_memory();
+                if (lane == 0) __hip_atomic_store(&prog[m], t + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+#pragma unroll
+            for (int h = 0; h < CH; ++h) {
+                v[h] = next[h];
+#pragma unroll
+                for (int i = 0; i < RW; ++i) {
+                    if (row[i] == 0 || row[i] == nb) continue;      // uniform
+                    double* p = w0 + row[i] * rowp + off[h];
+                    if (use[h] && off[h] < left) st(p, off[h] == 0 ? 0.0 : D[i][h]);
+                    if (use[h] && off[h] + nb < left) st(p + nb, Q[i][h]);
+                }
+            }
+        }
+        // the whole sweep
+        wait_memory();
+        __syncthreads();
+        if (tid == 0) __hip_atomic_store(&prog[m], T + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
 // Control words and inboxes before hold_kernel.
 __global__ void hold_init_kernel(int32_t* ctrl, double* box, int64_t words, int keep_error) {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -946,32 +866,33 @@ __global__ void hold_init_kernel(int32_t* ctrl, double* box, int64_t words, int 
 // Copy the upper band of B into W (zero elsewhere), clear the control words
 // (the error word too unless keep_error: then a status already there, such as
 // the band reduction's in the one-shot pipeline, stops the chase at its
-// first wait and stays visible) and the progress counters.  Entry (i, j) of
-// the band is B[i rs + j cs]: rs = 1, cs = ldb for an upper band stored as
-// is, rs = ldb, cs = 1 for the transpose of a lower band.
-__global__ void pack_kernel(const double* B, int64_t rs, int64_t cs, int64_t n, int nb, double* W, int64_t ldw,
-                            int32_t* ctrl, int32_t* prog, int32_t* bar, int nsweeps, int group, int keep_error,
+// first wait and stays visible) and the progress counters, mark the exchange
+// areas.  Entry (i, j) of the band is B[i rs + j cs]: rs = 1, cs = ldb for an
+// upper band stored as is, rs = ldb, cs = 1 for the transpose of a lower band.
+__global__ void pack_kernel(const double* B, int64_t rs, int64_t cs, int64_t n, int nb, double* W, int32_t* ctrl,
+                            int32_t* prog, int64_t nprog, double* xch, int64_t nxch, int keep_error,
                             const int32_t* met) {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     if (met && aload(met) == MET_GO) return;
-    if (g < G_WORDS && g != G_MET && !(keep_error && g == G_ERROR)) ctrl[g] = 0;
-    for (int64_t s = g; s < (int64_t)nsweeps * group; s += stride) prog[s] = 0;
-    for (int64_t s = g; s < nsweeps; s += stride) bar[s] = 0;
-    const int64_t total = ldw * n;
+    if (g < G_WORDS && !(met && g == G_MET) && !(keep_error && g == G_ERROR)) ctrl[g] = 0;
+    for (int64_t x = g; x < nprog; x += stride) prog[x] = 0;
+    for (int64_t x = g; x < nxch; x += stride) xch[x] = __builtin_bit_cast(double, MARK);
+    const int64_t ldw = 3 * (int64_t)nb, total = ldw * n;
     for (int64_t x = g; x < total; x += stride) {
-        const int64_t j = x / ldw;
-        const int64_t i = j + (x - j * ldw) - (2 * nb - 1);
-        W[x] = (i >= 0 && i <= j && j - i <= nb) ? B[i * rs + j * cs] : 0.0;
+        const int64_t i = x / ldw;
+        const int64_t j = i + (x - i * ldw) - (nb - 1);
+        W[x] = j >= i && j - i <= nb && j < n ? B[i * rs + j * cs] : 0.0;
     }
 }
 
-__global__ void extract_kernel(const double* W, int64_t ldw, int64_t n, int nb, double* d, double* e,
-                               const int32_t* met) {
+// A band that is bidiagonal as it is (nb = 1 or n <= 2).
+__global__ void diagonals_kernel(const double* B, int64_t rs, int64_t cs, int64_t n, double* d, double* e,
+                                 int32_t* ctrl, int keep_error) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n || (met && aload(met) == MET_GO)) return;
-    d[i] = W[(2 * nb - 1) + i * ldw];
-    if (i + 1 < n) e[i] = W[(2 * nb - 2) + (i + 1) * ldw];
+    if (i < G_WORDS && !(keep_error && i == G_ERROR)) ctrl[i] = 0;
+    if (i < n) d[i] = B[i * (rs + cs)];
+    if (i + 1 < n) e[i] = B[i * (rs + cs) + cs];
 }
 
 // Largest of v over the workgroup, in every thread; red holds a value a wave.
@@ -1114,45 +1035,47 @@ __global__ __launch_bounds__(BT) void bisect_kernel(const double* d, const doubl
     if (lane == 0 && j < n) sigma[j] = ldexp(0.5 * (lo + hi), ex);
 }
 
-// workspace: control words (256 B), the band array (3 nb n doubles), the
-// members' progress counters and the exchange counters (int32 per sweep and
-// member, and per sweep), the exchange areas
+// Instance for a bandwidth: slots of 64 CH columns, workgroups a block or a
+// sweep (of 8 RW row slots each), workgroups a compute unit: what the registers
+// of hold_kernel's instance allow (two waves a workgroup and SIMD).
+inline int ch_of(int nb) { return nb <= 64 ? 1 : nb <= 128 ? 2 : 4; }
+inline int group_of(int nb) { return nb <= 128 ? 1 : (nb + 63) / 64; }
+inline int per_cu(int nb) { return nb <= 32 ? 3 : nb <= 64 ? 2 : 1; }
+
 inline int64_t round256(int64_t b) { return (b + 255) / 256 * 256; }
 
-inline int nsweeps_of(int64_t n, int nb) { return nb <= 1 || n <= 2 ? 0 : (int)(n - 2); }
+inline int nsweeps_of(int64_t n, int nb) { return nb <= 1 || n <= 2 ? 0 : (int)(n - 1); }
 
-inline int64_t ws_prog_off(int64_t n, int nb) { return round256(256 + (int64_t)3 * nb * n * 8); }
-inline int64_t ws_bar_off(int64_t n, int nb) {
-    return ws_prog_off(n, nb) + round256((int64_t)nsweeps_of(n, nb) * group_of(nb) * 4);
-}
-inline int64_t ws_xch_off(int64_t n, int nb) {
-    return ws_bar_off(n, nb) + round256((int64_t)nsweeps_of(n, nb) * 4);
-}
-
-inline int64_t ws_sweep_bytes(int64_t n, int nb) {
-    const int g = group_of(nb);
-    const int64_t xch = g > 1 && nsweeps_of(n, nb) > 0 ? 8 * nareas_of(g) * area_doubles(nb, g) : 0;
-    return round256(ws_xch_off(n, nb) + xch);
+// Exchange areas of the chase by sweeps (groups only): sweep k uses area k %
+// nareas.  While a member m of sweep k is unfinished, so is member m of every
+// later sweep (it waits for the one ahead), and with it, but for the sweep k
+// itself, the others of its group (the last exchange needs it); each holds a
+// workgroup, of MAX_WG at most, so when a ticket of sweep k + nareas is taken
+// sweep k has finished and its area is all MARK again.
+inline int nareas_of(int64_t n, int nb) {
+    return group_of(nb) > 1 ? std::min(nsweeps_of(n, nb), MAX_WG / group_of(nb) + 2) : 0;
 }
 
-// Workgroups of a block and all inboxes of hold_kernel; none (0) where the
-// blocks do not fit on the chip at once, or nothing is chased.  Workgroups a
-// compute unit: what the registers of the instance allow (72, 88, 200, 224 of
-// 512 a lane and SIMD, two waves a workgroup and SIMD).
-inline int hold_ch(int nb) { return width_of(nb) / 64; }
-inline int hold_group(int nb) { return nb <= 128 ? 1 : (nb + 63) / 64; }
-inline int hold_per_cu(int nb) { return nb <= 32 ? 3 : nb <= 64 ? 2 : 1; }
+// Workspace: control words (256 B), the band array (3 nb n doubles), the
+// members' progress counters (int32 per sweep and member), the exchange areas,
+// hold_kernel's inboxes.
+inline int64_t prog_words(int64_t n, int nb) { return (int64_t)nsweeps_of(n, nb) * group_of(nb); }
+inline int64_t xch_words(int64_t n, int nb) {
+    return (int64_t)nareas_of(n, nb) * group_of(nb) * 2 * box_sums(ch_of(nb), group_of(nb));
+}
+// Workgroups of all blocks; none (0) where they do not fit on the chip at
+// once, or nothing is chased.
 inline int64_t hold_workgroups(int64_t n, int nb) {
-    const int64_t wg = (n - 1 + nb - 1) / nb * hold_group(nb);
-    return nsweeps_of(n, nb) > 0 && wg <= MAX_WG * hold_per_cu(nb) ? wg : 0;
+    const int64_t wg = (n - 1 + nb - 1) / nb * group_of(nb);
+    return nsweeps_of(n, nb) > 0 && wg <= MAX_WG * per_cu(nb) ? wg : 0;
 }
 inline int64_t hold_words(int64_t n, int nb) {
-    return hold_workgroups(n, nb) * box_doubles(hold_ch(nb), hold_group(nb));
+    return hold_workgroups(n, nb) * box_doubles(ch_of(nb), group_of(nb));
 }
-
-inline size_t ws_bytes(int64_t n, int nb) {
-    return (size_t)(ws_sweep_bytes(n, nb) + 8 * hold_words(n, nb));
-}
+inline int64_t ws_prog_off(int64_t n, int nb) { return round256(256 + (int64_t)3 * nb * n * 8); }
+inline int64_t ws_xch_off(int64_t n, int nb) { return ws_prog_off(n, nb) + round256(prog_words(n, nb) * 4); }
+inline int64_t ws_hold_off(int64_t n, int nb) { return ws_xch_off(n, nb) + round256(xch_words(n, nb) * 8); }
+inline size_t ws_bytes(int64_t n, int nb) { return (size_t)(ws_hold_off(n, nb) + 8 * hold_words(n, nb)); }
 
 int device_attr(hipDeviceAttribute_t attr, int fallback) {
     int dev = 0, v = 0;
@@ -1177,8 +1100,9 @@ int bb_bnd2bd_workspace(int64_t n, int nb, size_t* ws_bytes) {
 namespace bbg {
 
 // The chase after argument checks: band entry (i, j) at B[i rs + j cs].
+// by_sweeps: not held, whatever the size.
 int bnd2bd_launch(const double* B, int64_t rs, int64_t cs, int64_t n, int nb, double* d, double* e, void* ws,
-                  double watchdog_s, bool keep_error, void* stream);
+                  double watchdog_s, bool by_sweeps, bool keep_error, void* stream);
 
 }  // namespace bbg
 
@@ -1196,49 +1120,34 @@ int bb_bnd2bd_group(const double* B, int64_t ldb, int64_t n, int nb, double* d, 
     if (!ws && n > 0) return -7;
     if (ws_bytes < bbg::ws_bytes(n, nb)) return BB_EWORKSPACE;
     if (n == 0) return BB_OK;
-    return bbg::bnd2bd_launch(B, 1, ldb, n, nb, d, e, ws, watchdog_s, false, stream);
+    return bbg::bnd2bd_launch(B, 1, ldb, n, nb, d, e, ws, watchdog_s, group > 0, false, stream);
 }
 
 }  // extern "C"
 
 int bbg::bnd2bd_launch(const double* B, int64_t rs, int64_t cs, int64_t n, int nb, double* d, double* e,
-                       void* ws, double watchdog_s, bool keep_error, void* stream) {
+                       void* ws, double watchdog_s, bool by_sweeps, bool keep_error, void* stream) {
     hipStream_t s = (hipStream_t)stream;
+    int32_t* ctrl = (int32_t*)ws;
     const int nsw = bbg::nsweeps_of(n, nb);
-    bbg::ChaseArgs a;
-    a.W = (double*)((char*)ws + 256);
-    a.ldw = 3 * (int64_t)nb;
-    a.n = n;
-    a.nb = nb;
-    a.nsweeps = nsw;
-    a.ctrl = (int32_t*)ws;
-    a.prog = (int32_t*)((char*)ws + bbg::ws_prog_off(n, nb));
-    a.bar = (int32_t*)((char*)ws + bbg::ws_bar_off(n, nb));
-    a.xch = (double*)((char*)ws + bbg::ws_xch_off(n, nb));
-    a.group = bbg::group_of(nb);
-    a.nareas = bbg::nareas_of(a.group);
+    if (nsw == 0) {
+        hipLaunchKernelGGL(bbg::diagonals_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, B, rs, cs, n, d,
+                           e, ctrl, keep_error ? 1 : 0);
+        return hipGetLastError() == hipSuccess ? BB_OK : BB_EHIP;
+    }
     const double khz = (double)bbg::device_attr(hipDeviceAttributeWallClockRate, 100000);
-    a.watchdog_ticks = (int64_t)((watchdog_s > 0 ? watchdog_s : 30.0) * khz * 1000.0);
+    const bbg::Waits wait{ctrl, (int64_t)((watchdog_s > 0 ? watchdog_s : 30.0) * khz * 1000.0)};
     const int cus = bbg::device_attr(hipDeviceAttributeMultiprocessorCount, 256);
+    const int group = bbg::group_of(nb);
+    if (cus < group) return BB_ENOTSUP;
     const int64_t wgs = bbg::hold_workgroups(n, nb);
-    a.met = nullptr;
-    if (wgs > 0 && wgs <= (int64_t)cus * bbg::hold_per_cu(nb)) {
-        bbg::HoldArgs h;
-        h.B = B;
-        h.rs = rs;
-        h.cs = cs;
-        h.n = n;
-        h.nb = nb;
-        h.group = bbg::hold_group(nb);
-        h.ctrl = a.ctrl;
-        h.box = (double*)((char*)ws + bbg::ws_sweep_bytes(n, nb));
-        h.d = d;
-        h.e = e;
-        h.watchdog_ticks = a.watchdog_ticks;
-        h.meet_ticks = (int64_t)(bbg::MEET_SECONDS * khz * 1000.0);
+    const int32_t* met = nullptr;
+    if (!by_sweeps && wgs > 0 && wgs <= (int64_t)cus * bbg::per_cu(nb)) {
+        const bbg::HoldArgs h{wait, B, rs, cs, n, nb, group, (double*)((char*)ws + bbg::ws_hold_off(n, nb)),
+                              d, e, (int64_t)(bbg::MEET_SECONDS * khz * 1000.0)};
         const int64_t words = bbg::hold_words(n, nb);
         hipLaunchKernelGGL(bbg::hold_init_kernel, dim3((unsigned)std::min<int64_t>((words + 255) / 256, cus)),
-                           dim3(256), 0, s, a.ctrl, h.box, words, keep_error ? 1 : 0);
+                           dim3(256), 0, s, ctrl, h.box, words, keep_error ? 1 : 0);
         if (hipGetLastError() != hipSuccess) return BB_EHIP;
         const dim3 grid((unsigned)wgs), block(bbg::NT);
         if (nb <= 32)
@@ -1250,30 +1159,30 @@ int bbg::bnd2bd_launch(const double* B, int64_t rs, int64_t cs, int64_t n, int n
         else
             hipLaunchKernelGGL((bbg::hold_kernel<4, 8>), grid, block, 0, s, h);
         if (hipGetLastError() != hipSuccess) return BB_EHIP;
-        a.met = &a.ctrl[bbg::G_MET];
+        met = &ctrl[bbg::G_MET];
         keep_error = true;
     }
     // the chase by sweeps; after a launch above that held the band, these end at once
-    const int64_t total = a.ldw * n;
-    int blocks = (int)std::min<int64_t>((total + 255) / 256, 8 * (int64_t)cus);
-    hipLaunchKernelGGL(bbg::pack_kernel, dim3(blocks < 1 ? 1 : blocks), dim3(256), 0, s, B, rs, cs, n, nb, a.W,
-                       a.ldw, a.ctrl, a.prog, a.bar, nsw, a.group, keep_error ? 1 : 0, a.met);
+    const bbg::SweepArgs a{wait, (double*)((char*)ws + 256), n, nb, nsw, group,
+                           (int32_t*)((char*)ws + bbg::ws_prog_off(n, nb)),
+                           (double*)((char*)ws + bbg::ws_xch_off(n, nb)), std::max(1, bbg::nareas_of(n, nb)), d, e, met};
+    const int64_t total = (int64_t)3 * nb * n;
+    const int blocks = (int)std::min<int64_t>((total + 255) / 256, 8 * (int64_t)cus);
+    hipLaunchKernelGGL(bbg::pack_kernel, dim3(blocks), dim3(256), 0, s, B, rs, cs, n, nb, a.W, ctrl, a.prog,
+                       bbg::prog_words(n, nb), a.xch, bbg::xch_words(n, nb), keep_error ? 1 : 0, met);
     if (hipGetLastError() != hipSuccess) return BB_EHIP;
-    if (nsw > 0) {
-        // whole groups, at least one, one workgroup a CU (MAX_WG at most: the
-        // exchange areas are counted for that)
-        const int wg = std::min(cus, bbg::MAX_WG);
-        if (wg < a.group) return BB_ENOTSUP;
-        const dim3 grid((unsigned)std::min<int64_t>((int64_t)nsw * a.group, wg / a.group * a.group));
-        switch (bbg::width_of(nb)) {
-            case 64: hipLaunchKernelGGL(bbg::chase_kernel<64>, grid, dim3(bbg::NT), 0, s, a); break;
-            case 128: hipLaunchKernelGGL(bbg::chase_kernel<128>, grid, dim3(bbg::NT), 0, s, a); break;
-            default: hipLaunchKernelGGL(bbg::chase_kernel<256>, grid, dim3(bbg::NT), 0, s, a); break;
-        }
-        if (hipGetLastError() != hipSuccess) return BB_EHIP;
-    }
-    hipLaunchKernelGGL(bbg::extract_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a.W, a.ldw, n,
-                       nb, d, e, a.met);
+    // whole groups, one workgroup a CU and MAX_WG at most (the exchange areas
+    // are counted for that); without groups as many as the registers allow
+    const int64_t room = group > 1 ? std::min(cus, bbg::MAX_WG) / group * group : (int64_t)cus * bbg::per_cu(nb);
+    const dim3 grid((unsigned)std::min<int64_t>((int64_t)nsw * group, room)), block(bbg::NT);
+    if (nb <= 32)
+        hipLaunchKernelGGL((bbg::sweep_kernel<1, 4>), grid, block, 0, s, a);
+    else if (nb <= 64)
+        hipLaunchKernelGGL((bbg::sweep_kernel<1, 8>), grid, block, 0, s, a);
+    else if (nb <= 128)
+        hipLaunchKernelGGL((bbg::sweep_kernel<2, 16>), grid, block, 0, s, a);
+    else
+        hipLaunchKernelGGL((bbg::sweep_kernel<4, 8>), grid, block, 0, s, a);
     return hipGetLastError() == hipSuccess ? BB_OK : BB_EHIP;
 }
 
@@ -1347,8 +1256,8 @@ int bb_ge2val(void* A, int64_t m, int64_t n, int64_t lda, int nb, int tree, int 
     // m >= n: upper band in the leading n x n part; m < n: lower band in the
     // leading m x m part, chased as its transpose
     const double* B = (const double*)A;
-    rc = m >= n ? bbg::bnd2bd_launch(B, 1, lda, k, nb, d, e, ws, opts ? opts->watchdog_s : 0.0, true, stream)
-                : bbg::bnd2bd_launch(B, lda, 1, k, nb, d, e, ws, opts ? opts->watchdog_s : 0.0, true, stream);
+    rc = m >= n ? bbg::bnd2bd_launch(B, 1, lda, k, nb, d, e, ws, opts ? opts->watchdog_s : 0.0, false, true, stream)
+                : bbg::bnd2bd_launch(B, lda, 1, k, nb, d, e, ws, opts ? opts->watchdog_s : 0.0, false, true, stream);
     if (rc != BB_OK) return rc;
     return bb_bd2val(d, e, k, sigma, stream);
 }
