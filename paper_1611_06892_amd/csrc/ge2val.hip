@@ -134,7 +134,9 @@ __device__ __forceinline__ double sum_halves(double v) {
 
 // Householder reflector of (al, x) with ss = x^T x: beta = -sign(al) nrm,
 // tau = (beta - al) / beta, scale = 1 / (al - beta) (v = (1, scale x)); a
-// zero tail gives the identity.  1 / nrm and scale take one step of third
+// zero tail gives the identity, tau = 0.  Its sums are taken as zeros, so that
+// infinities and NaN elsewhere stay where they are (0.6 % of a chase at nb = 128,
+// 1.2 % at 256).  1 / nrm and scale take one step of third
 // order from the hardware approximations.
 struct Refl {
     double beta, tau, scale;
@@ -260,8 +262,9 @@ __device__ __forceinline__ double fold(double a, double b) {
 // Sums over the wave of RW = 4, 8 or 16 values a lane, each made uniform:
 // values are paired off while lanes are folded, so half as many are left at
 // each of the first levels.
+// none: zeros instead.
 template <int RW>
-__device__ __forceinline__ void wave_sums(double (&p)[RW]) {
+__device__ __forceinline__ void wave_sums(double (&p)[RW], bool none) {
     const int lane = threadIdx.x & 63;
     double q[RW / 4];
 #pragma unroll
@@ -285,6 +288,7 @@ __device__ __forceinline__ void wave_sums(double (&p)[RW]) {
     }
     q[0] += dpp<0x4E>(q[0]);            // quad_perm:[2,3,0,1]
     q[0] += dpp<0xB1>(q[0]);            // quad_perm:[1,0,3,2]
+    q[0] = none ? 0.0 : q[0];
 #pragma unroll
     for (int i = 0; i < RW; ++i) {
         const int half = i / (RW / 2), r = i % (RW / 2), row = r / (RW / 4), s = r % (RW / 4);
@@ -357,7 +361,7 @@ __device__ __forceinline__ void block_step(const Waits& a, StepLds<CH>& s, const
         for (int h = 0; h < CH; ++h) x[h] = lane + 64 * h == i0 ? 1.0 : f.scale * x[h];
         return f;
     };
-    auto from_right = [&](double (&M)[RW][CH], const double (&x)[CH], double tau) {
+    auto from_right = [&](double (&M)[RW][CH], const double (&x)[CH], const Refl& f) {
         double p[RW];
 #pragma unroll
         for (int i = 0; i < RW; ++i) {
@@ -365,17 +369,17 @@ __device__ __forceinline__ void block_step(const Waits& a, StepLds<CH>& s, const
 #pragma unroll
             for (int h = 1; h < CH; ++h) p[i] = fma(M[i][h], x[h], p[i]);
         }
-        wave_sums<RW>(p);
+        wave_sums<RW>(p, f.tau == 0.0);
         double tx[CH];
 #pragma unroll
-        for (int h = 0; h < CH; ++h) tx[h] = -tau * x[h];
+        for (int h = 0; h < CH; ++h) tx[h] = -f.tau * x[h];
 #pragma unroll
         for (int i = 0; i < RW; ++i)
 #pragma unroll
             for (int h = 0; h < CH; ++h) M[i][h] = fma(p[i], tx[h], M[i][h]);
     };
     const Refl fr = clear(v);
-    from_right(D, v, fr.tau);
+    from_right(D, v, fr);
 
     // the first row leaves the registers
     const bool gives = w == i0 % 8 && (!GROUPED || m == i0 / (8 * RW));
@@ -466,6 +470,8 @@ __device__ __forceinline__ void block_step(const Waits& a, StepLds<CH>& s, const
         const double rd = s.row0[par][lane + 64 * h], rq = s.row0[par][NBP + lane + 64 * h];
         td[h] = fma(fl.scale, s.total[lane + 64 * h], rd);
         tq[h] = fma(fl.scale, s.total[NBP + lane + 64 * h], rq);
+        td[h] = fl.tau == 0.0 ? 0.0 : td[h];
+        tq[h] = fl.tau == 0.0 ? 0.0 : tq[h];
         last[h] = fma(-fl.tau, td[h], rd);
         g[h] = fma(-fl.tau, tq[h], rq);
         td[h] *= -fl.tau * fl.scale;
@@ -482,7 +488,7 @@ __device__ __forceinline__ void block_step(const Waits& a, StepLds<CH>& s, const
             D[i][h] = fma(x[i], td[h], D[i][h]);
             Q[i][h] = fma(x[i], tq[h], Q[i][h]);
         }
-    from_right(Q, g, fg.tau);
+    from_right(Q, g, fg);
 }
 
 // ---- the chase with the band held in registers -----------------------------

@@ -120,3 +120,20 @@ def test_the_bits_do_not_depend_on_what_else_runs(bb, n, nb):
         if way(ws) == GIVEN_UP:
             break
     assert way(ws) == GIVEN_UP
+
+
+@pytest.mark.parametrize("n,nb", [(70, 16), (200, 64), (300, 128), (600, 256)])
+@pytest.mark.parametrize("group", [0, 1])
+def test_a_bidiagonal_passes_as_it_is(bb, n, nb, group):
+    """Every reflector is the identity, which changes nothing: the entries come
+    out bit by bit, and infinities, NaN and the largest numbers stay where they
+    are."""
+    print("case chase of a bidiagonal", n, nb, group, flush=True)
+    rng = np.random.default_rng(8400 + n)
+    d, e = rng.standard_normal(n), rng.standard_normal(n - 1)
+    d[[3, n // 2]] = np.inf, -1e308
+    e[[0, 5, n - 2]] = -np.inf, np.nan, 1e-308
+    S = torch.from_numpy(np.ascontiguousarray((np.diag(d) + np.diag(e, 1)).T)).cuda()
+    dg, eg = bb.bnd2bd(S, n, n, nb, watchdog_s=20.0, group=group)
+    assert np.array_equal(dg.cpu().numpy(), d)
+    assert np.array_equal(eg.cpu().numpy(), e, equal_nan=True)
