@@ -1042,8 +1042,9 @@ __global__ __launch_bounds__(BT) void bisect_kernel(const double* d, const doubl
 }
 
 // Instance for a bandwidth: slots of 64 CH columns, workgroups a block or a
-// sweep (of 8 RW row slots each), workgroups a compute unit: what the registers
-// of hold_kernel's instance allow (two waves a workgroup and SIMD).
+// sweep (of 8 RW row slots each), workgroups a compute unit that the workspace
+// has room for: what the registers of hold_kernel's instance allow (68, 85, 199,
+// 217 of 512 a lane and SIMD, two waves a workgroup and SIMD).
 inline int ch_of(int nb) { return nb <= 64 ? 1 : nb <= 128 ? 2 : 4; }
 inline int group_of(int nb) { return nb <= 128 ? 1 : (nb + 63) / 64; }
 inline int per_cu(int nb) { return nb <= 32 ? 3 : nb <= 64 ? 2 : 1; }
@@ -1105,6 +1106,25 @@ int bb_bnd2bd_workspace(int64_t n, int nb, size_t* ws_bytes) {
 
 namespace bbg {
 
+// f(hold_kernel, sweep_kernel) of the instance for nb.
+template <class F>
+void with_instance(int nb, F&& f) {
+    if (nb <= 32) f(hold_kernel<1, 4>, sweep_kernel<1, 4>);
+    else if (nb <= 64) f(hold_kernel<1, 8>, sweep_kernel<1, 8>);
+    else if (nb <= 128) f(hold_kernel<2, 16>, sweep_kernel<2, 16>);
+    else f(hold_kernel<4, 8>, sweep_kernel<4, 8>);
+}
+
+// Workgroups of hold_kernel that a compute unit runs at once: per_cu, which
+// sizes the workspace, or fewer where the build's kernel takes more registers.
+int hold_per_cu(int nb) {
+    int n = 0;
+    with_instance(nb, [&](auto hold, auto) {
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, hold, NT, 0) != hipSuccess) n = 0;
+    });
+    return std::min(n, per_cu(nb));
+}
+
 // The chase after argument checks: band entry (i, j) at B[i rs + j cs].
 // by_sweeps: not held, whatever the size.
 int bnd2bd_launch(const double* B, int64_t rs, int64_t cs, int64_t n, int nb, double* d, double* e, void* ws,
@@ -1148,22 +1168,16 @@ int bbg::bnd2bd_launch(const double* B, int64_t rs, int64_t cs, int64_t n, int n
     if (cus < group) return BB_ENOTSUP;
     const int64_t wgs = bbg::hold_workgroups(n, nb);
     const int32_t* met = nullptr;
-    if (!by_sweeps && wgs > 0 && wgs <= (int64_t)cus * bbg::per_cu(nb)) {
+    if (!by_sweeps && wgs > 0 && wgs <= (int64_t)cus * bbg::hold_per_cu(nb)) {
         const bbg::HoldArgs h{wait, B, rs, cs, n, nb, group, (double*)((char*)ws + bbg::ws_hold_off(n, nb)),
                               d, e, (int64_t)(bbg::MEET_SECONDS * khz * 1000.0)};
         const int64_t words = bbg::hold_words(n, nb);
         hipLaunchKernelGGL(bbg::hold_init_kernel, dim3((unsigned)std::min<int64_t>((words + 255) / 256, cus)),
                            dim3(256), 0, s, ctrl, h.box, words, keep_error ? 1 : 0);
         if (hipGetLastError() != hipSuccess) return BB_EHIP;
-        const dim3 grid((unsigned)wgs), block(bbg::NT);
-        if (nb <= 32)
-            hipLaunchKernelGGL((bbg::hold_kernel<1, 4>), grid, block, 0, s, h);
-        else if (nb <= 64)
-            hipLaunchKernelGGL((bbg::hold_kernel<1, 8>), grid, block, 0, s, h);
-        else if (nb <= 128)
-            hipLaunchKernelGGL((bbg::hold_kernel<2, 16>), grid, block, 0, s, h);
-        else
-            hipLaunchKernelGGL((bbg::hold_kernel<4, 8>), grid, block, 0, s, h);
+        bbg::with_instance(nb, [&](auto hold, auto) {
+            hipLaunchKernelGGL(hold, dim3((unsigned)wgs), dim3(bbg::NT), 0, s, h);
+        });
         if (hipGetLastError() != hipSuccess) return BB_EHIP;
         met = &ctrl[bbg::G_MET];
         keep_error = true;
@@ -1180,15 +1194,8 @@ int bbg::bnd2bd_launch(const double* B, int64_t rs, int64_t cs, int64_t n, int n
     // whole groups, one workgroup a CU and MAX_WG at most (the exchange areas
     // are counted for that); without groups as many as the registers allow
     const int64_t room = group > 1 ? std::min(cus, bbg::MAX_WG) / group * group : (int64_t)cus * bbg::per_cu(nb);
-    const dim3 grid((unsigned)std::min<int64_t>((int64_t)nsw * group, room)), block(bbg::NT);
-    if (nb <= 32)
-        hipLaunchKernelGGL((bbg::sweep_kernel<1, 4>), grid, block, 0, s, a);
-    else if (nb <= 64)
-        hipLaunchKernelGGL((bbg::sweep_kernel<1, 8>), grid, block, 0, s, a);
-    else if (nb <= 128)
-        hipLaunchKernelGGL((bbg::sweep_kernel<2, 16>), grid, block, 0, s, a);
-    else
-        hipLaunchKernelGGL((bbg::sweep_kernel<4, 8>), grid, block, 0, s, a);
+    const dim3 grid((unsigned)std::min<int64_t>((int64_t)nsw * group, room));
+    bbg::with_instance(nb, [&](auto, auto sweep) { hipLaunchKernelGGL(sweep, grid, dim3(bbg::NT), 0, s, a); });
     return hipGetLastError() == hipSuccess ? BB_OK : BB_EHIP;
 }
 

@@ -137,3 +137,18 @@ def test_a_bidiagonal_passes_as_it_is(bb, n, nb, group):
     dg, eg = bb.bnd2bd(S, n, n, nb, watchdog_s=20.0, group=group)
     assert np.array_equal(dg.cpu().numpy(), d)
     assert np.array_equal(eg.cpu().numpy(), e, equal_nan=True)
+
+
+@pytest.mark.parametrize("n,nb", [(768 * 17 + 1, 17), (512 * 33 + 1, 33), (256 * 65 + 1, 65), (85 * 129 + 1, 129),
+                                  (64 * 193 + 1, 193)])
+def test_the_largest_bands_are_held(bb, n, nb):
+    """As many blocks as every instance has room for on the whole chip: three, two
+    and one workgroup a compute unit, groups of three and of four."""
+    print("case chase largest held", n, nb, flush=True)
+    S = random_band(n, nb, 8500 + nb)
+    ws = workspace(bb, n, nb)
+    held = bb.bnd2bd(S, n, n, nb, ws=ws, watchdog_s=20.0)
+    assert way(ws) == HELD
+    swept = bb.bnd2bd(S, n, n, nb, ws=ws, watchdog_s=20.0, group=1)
+    assert way(ws) == BY_SWEEPS
+    assert torch.equal(held[0], swept[0]) and torch.equal(held[1], swept[1])
