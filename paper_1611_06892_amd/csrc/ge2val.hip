@@ -21,10 +21,10 @@
 // columns c .. c + 2 nb - 1.  One block of one sweep (block_step) is the unit
 // of work, and there are two ways to bring the blocks to it:
 //   * where all blocks' workgroups find room on the chip at once, they hold
-//     the blocks in registers and the sweeps pass through them (hold_kernel);
+//     the blocks in registers and the sweeps pass through them (hold_blocks);
 //   * else, for larger matrices or beside work that holds compute units, each
 //     sweep is run by workgroups of its own over the band in memory
-//     (sweep_kernel), any number of them.
+//     (run_sweeps), any number of them.
 // Both run the same block_step on the same values in the same lanes, so the
 // result does not depend on the way, bit by bit.  Multiply-adds are written
 // out and contraction is off, so that the compiler cannot round the two
@@ -297,13 +297,6 @@ __device__ __forceinline__ void wave_sums(double (&p)[RW], bool none) {
     }
 }
 
-// v for one comparison: a chain of them on one value becomes a switch, at whose
-// end every register that its cases change would be copied.
-__device__ __forceinline__ int apart(int v) {
-    asm("" : "+s"(v));
-    return v;
-}
-
 constexpr int box_sums(int ch, int group) { return ch <= 2 ? 0 : (group + 1) * 128 * ch; }
 
 // Workgroups that run a block: how many, which one this is, its boxes for the
@@ -384,10 +377,12 @@ __device__ __forceinline__ void block_step(const Waits& a, StepLds<CH>& s, const
     // the first row leaves the registers
     const bool gives = w == i0 % 8 && (!GROUPED || m == i0 / (8 * RW));
     if (gives) {
-        const int reg = i0 / 8 % RW;
+        // (a bit a register: comparisons of one value become a switch, at whose
+        // end every register that its cases change would be copied)
+        const uint32_t reg = 1u << i0 / 8 % RW;
 #pragma unroll
         for (int i = 0; i < RW; ++i)
-            if (__builtin_expect(i == apart(reg), 0)) {
+            if (__builtin_expect(reg >> i & 1, 0)) {
 #pragma unroll
                 for (int h = 0; h < CH; ++h) {
                     s.row0[par][lane + 64 * h] = D[i][h];
@@ -421,9 +416,12 @@ __device__ __forceinline__ void block_step(const Waits& a, StepLds<CH>& s, const
     if (__builtin_amdgcn_readfirstlane(s.fail[par]) != 0) __builtin_amdgcn_endpgm();
     {
         const int col = w * 16 * CH + lane % (16 * CH), sub = lane / (16 * CH);
-        double sum = 0.0;
+        double each[PARTS], sum = 0.0;
 #pragma unroll
-        for (int h = 0; h < PARTS; ++h) sum += s.part[sub * PARTS + h][col];
+        for (int h = 0; h < PARTS; ++h) each[h] = s.part[sub * PARTS + h][col];
+        __builtin_amdgcn_sched_barrier(0);      // (all of them are read before the first is added)
+#pragma unroll
+        for (int h = 0; h < PARTS; ++h) sum += each[h];
         if constexpr (CH == 1) sum = sum_rows(sum);
         if constexpr (CH == 2) sum = sum_halves(sum);
         if constexpr (GROUPED) {
@@ -462,18 +460,25 @@ __device__ __forceinline__ void block_step(const Waits& a, StepLds<CH>& s, const
     lds_barrier();
     if (GROUPED && __builtin_amdgcn_readfirstlane(s.fail[par]) != 0) __builtin_amdgcn_endpgm();
 
-    // left reflector; the new first row
-    const Refl fl = reflector(s.row0[par][i0], s.total[i0]);
+    // left reflector; the new first row (its terms are read while the reflector
+    // is formed)
     double td[CH], tq[CH], g[CH], last[CH];
 #pragma unroll
     for (int h = 0; h < CH; ++h) {
-        const double rd = s.row0[par][lane + 64 * h], rq = s.row0[par][NBP + lane + 64 * h];
-        td[h] = fma(fl.scale, s.total[lane + 64 * h], rd);
-        tq[h] = fma(fl.scale, s.total[NBP + lane + 64 * h], rq);
+        last[h] = s.row0[par][lane + 64 * h];
+        g[h] = s.row0[par][NBP + lane + 64 * h];
+        td[h] = s.total[lane + 64 * h];
+        tq[h] = s.total[NBP + lane + 64 * h];
+    }
+    const Refl fl = reflector(s.row0[par][i0], s.total[i0]);
+#pragma unroll
+    for (int h = 0; h < CH; ++h) {
+        td[h] = fma(fl.scale, td[h], last[h]);
+        tq[h] = fma(fl.scale, tq[h], g[h]);
         td[h] = fl.tau == 0.0 ? 0.0 : td[h];
         tq[h] = fl.tau == 0.0 ? 0.0 : tq[h];
-        last[h] = fma(-fl.tau, td[h], rd);
-        g[h] = fma(-fl.tau, tq[h], rq);
+        last[h] = fma(-fl.tau, td[h], last[h]);
+        g[h] = fma(-fl.tau, tq[h], g[h]);
         td[h] *= -fl.tau * fl.scale;
         tq[h] *= -fl.tau * fl.scale;
     }
@@ -506,9 +511,9 @@ __device__ __forceinline__ void block_step(const Waits& a, StepLds<CH>& s, const
 // (256, with the exchange between four members).
 //
 // All workgroups have to run at once, so they meet first; if they have not
-// met within MEET_SECONDS (other work holds compute units) the launch ends
-// without having done anything, and the chase by sweeps, which needs no more
-// than one running group, does the work.
+// met within MEET_SECONDS (other work holds compute units), those that run do
+// the chase by sweeps, which needs no more than one group, and those that start
+// later join them.
 constexpr double MEET_SECONDS = 2e-3;
 
 struct HoldArgs {
@@ -531,8 +536,8 @@ constexpr int box_doubles(int ch, int group) { return 2 * (box_row(ch) + box_las
 
 enum : int { MET_GO = 1, MET_GIVE_UP = 2 };     // the word G_MET
 
-// One thread of each workgroup: whether all of them are running.
-__device__ __forceinline__ bool meet(const HoldArgs& a) {
+// One thread of each workgroup: whether all of them are running (MET_GO).
+__device__ __forceinline__ int meet(const HoldArgs& a) {
     const uint64_t t0 = wall_clock64();
     int none = 0;
     if (__hip_atomic_fetch_add(&a.wait.ctrl[G_RUNNING], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
@@ -541,7 +546,7 @@ __device__ __forceinline__ bool meet(const HoldArgs& a) {
                                              __HIP_MEMORY_SCOPE_AGENT);
     for (;;) {
         const int met = aload(&a.wait.ctrl[G_MET]);
-        if (met != 0) return met == MET_GO;
+        if (met != 0) return met;
         if ((int64_t)(wall_clock64() - t0) > a.meet_ticks) {
             none = 0;
             __hip_atomic_compare_exchange_strong(&a.wait.ctrl[G_MET], &none, (int)MET_GIVE_UP, __ATOMIC_RELAXED,
@@ -552,19 +557,11 @@ __device__ __forceinline__ bool meet(const HoldArgs& a) {
 }
 
 template <int CH, int RW>
-__global__ __launch_bounds__(NT) void hold_kernel(HoldArgs a) {
+__device__ __forceinline__ void hold_blocks(const HoldArgs& a, StepLds<CH>& lds) {
     constexpr int NBP = 64 * CH;
     constexpr bool GROUPED = CH == 4;
-    __shared__ StepLds<CH> lds;
-    __shared__ int go;
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if (tid == 0) {
-        lds.fail[0] = lds.fail[1] = 0;
-        go = meet(a) && aload(&a.wait.ctrl[G_ERROR]) == 0;  // (an error reported before stops the chase)
-    }
-    __syncthreads();
-    if (__builtin_amdgcn_readfirstlane(go) == 0) return;
     const int nb = a.nb, G = GROUPED ? a.group : 1;
     const int b = (int)blockIdx.x / G, m = (int)blockIdx.x % G;
     const int size = box_doubles(CH, G);
@@ -599,10 +596,10 @@ __global__ __launch_bounds__(NT) void hold_kernel(HoldArgs a) {
             const bool one[1] = {true};
             ok = await(a.wait, box_l + (par ^ 1) * box_last(CH) + lane, 64, use, x);
             ok = ok && await(a.wait, box_l + (par ^ 1) * box_last(CH) + NBP, 0, one, diag);
-            const int reg = ip / 8 % RW;
+            const uint32_t reg = 1u << ip / 8 % RW;
 #pragma unroll
             for (int i = 0; i < RW; ++i)
-                if (__builtin_expect(i == apart(reg), 0)) {
+                if (__builtin_expect(reg >> i & 1, 0)) {
 #pragma unroll
                     for (int h = 0; h < CH; ++h) {
                         D[i][h] = lane + 64 * h == ip ? diag[0] : 0.0;
@@ -710,10 +707,10 @@ __global__ __launch_bounds__(NT) void hold_kernel(HoldArgs a) {
 // KB, and out, for groups the exchange) and the step itself.  A block's stores
 // complete while the next one's wait is polled and its rows are loaded.
 // Measured, with slices of rows in LDS on up to 16 workgroups a sweep (whose sums
-// were others than the held chase's) and so: 20000 at nb = 16 300 and 169 ms, 50000
-// at nb = 64 760 and 652 ms, 40000 at nb = 128 1326 and 1135 ms, 20000 at nb =
-// 256 983 and 594 ms.  Where the band can be held: 2000 at nb = 64 15.8 ms (held
-// 7.7), 16384 at nb = 128 449 (96), 8192 at nb = 256 225 ms (74).
+// were others than the held chase's) and so: 20000 at nb = 16 300 and 172 ms, 50000
+// at nb = 64 760 and 649 ms, 40000 at nb = 128 1326 and 1138 ms, 20000 at nb =
+// 256 983 and 650 ms.  Where the band can be held: 2000 at nb = 64 16 ms (held
+// 7.7), 16384 at nb = 128 450 (96), 8192 at nb = 256 255 ms (75).
 struct SweepArgs {
     Waits wait;
     double* W;
@@ -727,20 +724,15 @@ struct SweepArgs {
     int nareas;
     double* d;
     double* e;
-    const int32_t* met;   // the meeting of hold_kernel before this launch, or null
 };
 
 template <int CH, int RW>
-__global__ __launch_bounds__(NT) void sweep_kernel(SweepArgs a) {
+__device__ __forceinline__ void run_sweeps(const SweepArgs& a, StepLds<CH>& lds, int& sk, int& flag) {
     constexpr bool GROUPED = CH == 4;
-    __shared__ StepLds<CH> lds;
-    __shared__ int sk, flag;
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nb = a.nb, G = GROUPED ? a.group : 1;
     const int64_t rowp = 3 * (int64_t)nb - 1;           // from entry (i, j) to (i + 1, j)
-    if (tid == 0) lds.fail[0] = lds.fail[1] = 0;
-    if (a.met && aload(a.met) == MET_GO) return;
 
     for (;;) {
         // ticket = sweep * G + member: a group's members are consecutive
@@ -862,33 +854,65 @@ __global__ __launch_bounds__(NT) void sweep_kernel(SweepArgs a) {
     }
 }
 
-// Control words and inboxes before hold_kernel.
-__global__ void hold_init_kernel(int32_t* ctrl, double* box, int64_t words, int keep_error) {
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g < G_WORDS && !(keep_error && g == G_ERROR)) ctrl[g] = 0;
-    for (int64_t i = g; i < words; i += (int64_t)gridDim.x * blockDim.x) box[i] = __builtin_bit_cast(double, MARK);
+// tries: the blocks are held if the workgroups (as many as they need) meet; one
+// kernel for both ways, as a launch that finds nothing left to do waits for
+// room beside other work like any other.
+template <int CH, int RW>
+__global__ __launch_bounds__(NT) void chase_kernel(HoldArgs h, SweepArgs a, int tries) {
+    __shared__ StepLds<CH> lds;
+    __shared__ int met, flag;
+    if (threadIdx.x == 0) {
+        lds.fail[0] = lds.fail[1] = 0;
+        met = tries ? meet(h) : (int)MET_GIVE_UP;
+        if (aload(&a.wait.ctrl[G_ERROR]) != 0) met = 0;     // an error reported before stops the chase
+    }
+    __syncthreads();
+    const int way = __builtin_amdgcn_readfirstlane(met);
+    __syncthreads();
+    if (way == MET_GO) {
+        hold_blocks<CH, RW>(h, lds);
+        __builtin_amdgcn_endpgm();          // (what the sweeps need is not kept through this)
+    }
+    if (way == MET_GIVE_UP) run_sweeps<CH, RW>(a, lds, met, flag);
 }
 
-// Copy the upper band of B into W (zero elsewhere), clear the control words
-// (the error word too unless keep_error: then a status already there, such as
-// the band reduction's in the one-shot pipeline, stops the chase at its
-// first wait and stays visible) and the progress counters, mark the exchange
-// areas.  Entry (i, j) of the band is B[i rs + j cs]: rs = 1, cs = ldb for an
-// upper band stored as is, rs = ldb, cs = 1 for the transpose of a lower band.
-__global__ void pack_kernel(const double* B, int64_t rs, int64_t cs, int64_t n, int nb, double* W, int32_t* ctrl,
-                            int32_t* prog, int64_t nprog, double* xch, int64_t nxch, int keep_error,
-                            const int32_t* met) {
+// Everything the chase finds in the workspace, for either way: the control
+// words cleared (not the error word where keep_error: a status already there,
+// such as the band reduction's in the one-shot pipeline, stops the chase at its
+// start and stays visible) and the progress counters, exchange areas and
+// inboxes marked, the upper band of B copied into W (zero elsewhere).  Entry
+// (i, j) of the band is B[i rs + j cs]: rs = 1, cs = ldb for an upper band stored
+// as is, rs = ldb, cs = 1 for the transpose of a lower band.
+// The band is copied before it is known whether it can be held, for one launch
+// less: beside work that fills the chip every launch waits for room of its own
+// (a matrix product's last workgroups, say), and the copy takes less than 1 % of a
+// chase.
+struct PrepareArgs {
+    const double* B;
+    int64_t rs, cs, n;
+    int nb;
+    int32_t* ctrl;
+    int keep_error;
+    double* W;
+    int32_t* prog;
+    int64_t nprog;
+    double *xch, *box;
+    int64_t nxch, nbox;
+};
+
+__global__ void prepare_kernel(PrepareArgs a) {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    if (met && aload(met) == MET_GO) return;
-    if (g < G_WORDS && !(met && g == G_MET) && !(keep_error && g == G_ERROR)) ctrl[g] = 0;
-    for (int64_t x = g; x < nprog; x += stride) prog[x] = 0;
-    for (int64_t x = g; x < nxch; x += stride) xch[x] = __builtin_bit_cast(double, MARK);
-    const int64_t ldw = 3 * (int64_t)nb, total = ldw * n;
+    const double mark = __builtin_bit_cast(double, MARK);
+    if (g < G_WORDS && !(a.keep_error && g == G_ERROR)) a.ctrl[g] = 0;
+    for (int64_t x = g; x < a.nprog; x += stride) a.prog[x] = 0;
+    for (int64_t x = g; x < a.nxch; x += stride) a.xch[x] = mark;
+    for (int64_t x = g; x < a.nbox; x += stride) a.box[x] = mark;
+    const int64_t ldw = 3 * (int64_t)a.nb, total = ldw * a.n;
     for (int64_t x = g; x < total; x += stride) {
         const int64_t i = x / ldw;
-        const int64_t j = i + (x - i * ldw) - (nb - 1);
-        W[x] = j >= i && j - i <= nb && j < n ? B[i * rs + j * cs] : 0.0;
+        const int64_t j = i + (x - i * ldw) - (a.nb - 1);
+        a.W[x] = j >= i && j - i <= a.nb && j < a.n ? a.B[i * a.rs + j * a.cs] : 0.0;
     }
 }
 
@@ -1043,8 +1067,8 @@ __global__ __launch_bounds__(BT) void bisect_kernel(const double* d, const doubl
 
 // Instance for a bandwidth: slots of 64 CH columns, workgroups a block or a
 // sweep (of 8 RW row slots each), workgroups a compute unit that the workspace
-// has room for: what the registers of hold_kernel's instance allow (68, 85, 199,
-// 217 of 512 a lane and SIMD, two waves a workgroup and SIMD).
+// has room for: what the registers of chase_kernel's instance allow (69, 86, 227,
+// 247 of 512 a lane and SIMD, two waves a workgroup and SIMD).
 inline int ch_of(int nb) { return nb <= 64 ? 1 : nb <= 128 ? 2 : 4; }
 inline int group_of(int nb) { return nb <= 128 ? 1 : (nb + 63) / 64; }
 inline int per_cu(int nb) { return nb <= 32 ? 3 : nb <= 64 ? 2 : 1; }
@@ -1065,7 +1089,7 @@ inline int nareas_of(int64_t n, int nb) {
 
 // Workspace: control words (256 B), the band array (3 nb n doubles), the
 // members' progress counters (int32 per sweep and member), the exchange areas,
-// hold_kernel's inboxes.
+// the held blocks' inboxes.
 inline int64_t prog_words(int64_t n, int nb) { return (int64_t)nsweeps_of(n, nb) * group_of(nb); }
 inline int64_t xch_words(int64_t n, int nb) {
     return (int64_t)nareas_of(n, nb) * group_of(nb) * 2 * box_sums(ch_of(nb), group_of(nb));
@@ -1106,23 +1130,13 @@ int bb_bnd2bd_workspace(int64_t n, int nb, size_t* ws_bytes) {
 
 namespace bbg {
 
-// f(hold_kernel, sweep_kernel) of the instance for nb.
+// f(chase_kernel) of the instance for nb.
 template <class F>
 void with_instance(int nb, F&& f) {
-    if (nb <= 32) f(hold_kernel<1, 4>, sweep_kernel<1, 4>);
-    else if (nb <= 64) f(hold_kernel<1, 8>, sweep_kernel<1, 8>);
-    else if (nb <= 128) f(hold_kernel<2, 16>, sweep_kernel<2, 16>);
-    else f(hold_kernel<4, 8>, sweep_kernel<4, 8>);
-}
-
-// Workgroups of hold_kernel that a compute unit runs at once: per_cu, which
-// sizes the workspace, or fewer where the build's kernel takes more registers.
-int hold_per_cu(int nb) {
-    int n = 0;
-    with_instance(nb, [&](auto hold, auto) {
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, hold, NT, 0) != hipSuccess) n = 0;
-    });
-    return std::min(n, per_cu(nb));
+    if (nb <= 32) f(chase_kernel<1, 4>);
+    else if (nb <= 64) f(chase_kernel<1, 8>);
+    else if (nb <= 128) f(chase_kernel<2, 16>);
+    else f(chase_kernel<4, 8>);
 }
 
 // The chase after argument checks: band entry (i, j) at B[i rs + j cs].
@@ -1166,36 +1180,46 @@ int bbg::bnd2bd_launch(const double* B, int64_t rs, int64_t cs, int64_t n, int n
     const int cus = bbg::device_attr(hipDeviceAttributeMultiprocessorCount, 256);
     const int group = bbg::group_of(nb);
     if (cus < group) return BB_ENOTSUP;
+    // A chase's workgroups take their compute units' LDS, each an equal part of
+    // it, so that no other kernel's that use LDS run there: a matrix product's waves
+    // on the same SIMDs, whose FP64 pipe they share, make a step of 2 us take 45.
+    // Beside FP64 products on another stream, with 11 KB a workgroup and so: 300 at
+    // nb = 64 28 and 12 ms, 1000 at nb = 64 62 and 14 ms.  Alone it costs nothing.
+    const int64_t blocks = (n - 1 + nb - 1) / nb * group;
+    const int per = (int)std::min<int64_t>(bbg::per_cu(nb), (blocks + cus - 1) / cus);
     const int64_t wgs = bbg::hold_workgroups(n, nb);
-    const int32_t* met = nullptr;
-    if (!by_sweeps && wgs > 0 && wgs <= (int64_t)cus * bbg::hold_per_cu(nb)) {
-        const bbg::HoldArgs h{wait, B, rs, cs, n, nb, group, (double*)((char*)ws + bbg::ws_hold_off(n, nb)),
-                              d, e, (int64_t)(bbg::MEET_SECONDS * khz * 1000.0)};
-        const int64_t words = bbg::hold_words(n, nb);
-        hipLaunchKernelGGL(bbg::hold_init_kernel, dim3((unsigned)std::min<int64_t>((words + 255) / 256, cus)),
-                           dim3(256), 0, s, ctrl, h.box, words, keep_error ? 1 : 0);
-        if (hipGetLastError() != hipSuccess) return BB_EHIP;
-        bbg::with_instance(nb, [&](auto hold, auto) {
-            hipLaunchKernelGGL(hold, dim3((unsigned)wgs), dim3(bbg::NT), 0, s, h);
-        });
-        if (hipGetLastError() != hipSuccess) return BB_EHIP;
-        met = &ctrl[bbg::G_MET];
-        keep_error = true;
-    }
-    // the chase by sweeps; after a launch above that held the band, these end at once
+    int room = 0;                               // workgroups of this build a compute unit runs
+    size_t lds = 0;
+    bbg::with_instance(nb, [&](auto kernel) {
+        const int all = bbg::device_attr(hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, 65536);
+        hipFuncAttributes fa;
+        if (hipFuncGetAttributes(&fa, (const void*)kernel) != hipSuccess) return;
+        const int most = all - (int)fa.sharedSizeBytes;         // (the same for every call)
+        if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, most) == hipSuccess)
+            lds = (size_t)std::max(0, most - (all - all / per)) / 1280 * 1280;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&room, kernel, bbg::NT, lds) != hipSuccess) room = 0;
+    });
+    const bool hold = !by_sweeps && wgs > 0 && wgs <= (int64_t)cus * room;
+    double* box = (double*)((char*)ws + bbg::ws_hold_off(n, nb));
+    const bbg::HoldArgs h{wait, B, rs, cs, n, nb, group, box, d, e, (int64_t)(bbg::MEET_SECONDS * khz * 1000.0)};
     const bbg::SweepArgs a{wait, (double*)((char*)ws + 256), n, nb, nsw, group,
                            (int32_t*)((char*)ws + bbg::ws_prog_off(n, nb)),
-                           (double*)((char*)ws + bbg::ws_xch_off(n, nb)), std::max(1, bbg::nareas_of(n, nb)), d, e, met};
+                           (double*)((char*)ws + bbg::ws_xch_off(n, nb)), std::max(1, bbg::nareas_of(n, nb)), d, e};
+    const bbg::PrepareArgs p{B, rs, cs, n, nb, ctrl, keep_error ? 1 : 0, a.W, a.prog, bbg::prog_words(n, nb),
+                             a.xch, box, bbg::xch_words(n, nb), hold ? bbg::hold_words(n, nb) : 0};
     const int64_t total = (int64_t)3 * nb * n;
-    const int blocks = (int)std::min<int64_t>((total + 255) / 256, 8 * (int64_t)cus);
-    hipLaunchKernelGGL(bbg::pack_kernel, dim3(blocks), dim3(256), 0, s, B, rs, cs, n, nb, a.W, ctrl, a.prog,
-                       bbg::prog_words(n, nb), a.xch, bbg::xch_words(n, nb), keep_error ? 1 : 0, met);
+    hipLaunchKernelGGL(bbg::prepare_kernel, dim3((unsigned)std::min<int64_t>((total + 255) / 256, 8 * (int64_t)cus)),
+                       dim3(256), 0, s, p);
     if (hipGetLastError() != hipSuccess) return BB_EHIP;
-    // whole groups, one workgroup a CU and MAX_WG at most (the exchange areas
-    // are counted for that); without groups as many as the registers allow
-    const int64_t room = group > 1 ? std::min(cus, bbg::MAX_WG) / group * group : (int64_t)cus * bbg::per_cu(nb);
-    const dim3 grid((unsigned)std::min<int64_t>((int64_t)nsw * group, room));
-    bbg::with_instance(nb, [&](auto, auto sweep) { hipLaunchKernelGGL(sweep, grid, dim3(bbg::NT), 0, s, a); });
+    // a workgroup a block to hold it (the sweeps, if they do not meet, make do
+    // with those too); else whole groups, one workgroup a CU and MAX_WG at most
+    // (the exchange areas are counted for that), without groups as many as run
+    const int64_t grid = hold ? wgs
+                         : std::min<int64_t>((int64_t)nsw * group, group > 1 ? std::min(cus, bbg::MAX_WG) / group * group
+                                                                             : (int64_t)cus * per);
+    bbg::with_instance(nb, [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(bbg::NT), lds, s, h, a, hold ? 1 : 0);
+    });
     return hipGetLastError() == hipSuccess ? BB_OK : BB_EHIP;
 }
 

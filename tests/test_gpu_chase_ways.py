@@ -10,6 +10,8 @@ elsewhere or where a caller asks for them (bb_bnd2bd_group with a group).
 Control word 2 of the workspace tells the way: 1 held, 2 the blocks did not
 find room in time, 0 not tried.
 """
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -152,3 +154,21 @@ def test_the_largest_bands_are_held(bb, n, nb):
     swept = bb.bnd2bd(S, n, n, nb, ws=ws, watchdog_s=20.0, group=1)
     assert way(ws) == BY_SWEEPS
     assert torch.equal(held[0], swept[0]) and torch.equal(held[1], swept[1])
+
+
+@pytest.mark.parametrize("n,nb", [(300, 64), (600, 256), (1541, 2)])
+def test_a_call_takes_three_launches_at_most(bb, n, nb):
+    """Beside work that fills the chip every launch waits for room of its own, so
+    a small chase costs as many such waits as it has launches."""
+    S = random_band(n, nb, 8600)
+    ws = workspace(bb, n, nb)
+    bb.bnd2bd(S, n, n, nb, ws=ws)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(g):
+        bb.bnd2bd(S, n, n, nb, ws=ws, check=False)
+    with open("/proc/self/maps") as maps:
+        hip = ctypes.CDLL(next(line.split()[-1] for line in maps if "libamdhip64" in line))
+    count = ctypes.c_size_t()
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(g.raw_cuda_graph()), None, ctypes.byref(count)) == 0
+    assert count.value <= 3
