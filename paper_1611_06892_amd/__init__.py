@@ -201,13 +201,22 @@ def cache_clear():
 
 
 # Plans of band_autograd, least recently used first: as many as the library
-# keeps for the one-shot entry points.  A plan holds no state of a run (its
+# keeps for the one-shot entry points, and no more than _PLANS_BYTES of graphs but
+# for the latest one's (8192 x 1024 at nb = 128 has 1 MB, 16384 x 16384 739 MB, in
+# pinned host memory).  A plan holds no state of a run (its
 # buffers belong to the caller), so threads and streams may share one; a plan
 # in use stays alive with its user.  Building the three graphs of a pass takes
 # the host 4 ms at 8192 x 1024, nb = 128 (a third of the pass).
 _PLANS_MAX = 16
+_PLANS_BYTES = 256 << 20
 _plans = collections.OrderedDict()
 _plans_lock = threading.Lock()
+
+
+def _graph_bytes(plan):
+    """Of a pass's three graphs, which are of about the same size: the
+    reduction's, copied into its workspace, and the two that apply Q and P."""
+    return 3 * plan.workspace()[1]
 
 
 def _shared_plan(m, n, nb, tree, variant, device):
@@ -222,8 +231,10 @@ def _shared_plan(m, n, nb, tree, variant, device):
     with _plans_lock:
         plan = _plans.setdefault(key, plan)
         _plans.move_to_end(key)
-        while len(_plans) > _PLANS_MAX:
-            dropped.append(_plans.popitem(last=False))
+        total = sum(map(_graph_bytes, _plans.values()))
+        while len(_plans) > 1 and (len(_plans) > _PLANS_MAX or total > _PLANS_BYTES):
+            dropped.append(_plans.popitem(last=False)[1])
+            total -= _graph_bytes(dropped[-1])
     del dropped                     # destroyed outside the lock
     return plan
 

@@ -441,3 +441,17 @@ def test_autograd_plans_are_shared_bounded_and_dropped():
                                                                                            "rbidiag", 0)
     bb.cache_clear()
     assert not mod._plans and held.stats()["ntasks"] > 0
+
+
+def test_autograd_plans_are_bounded_in_bytes(monkeypatch):
+    """Graphs of many megabytes do not stay for sixteen shapes; the latest plan
+    does, whatever its size."""
+    import paper_1611_06892_amd as mod
+    monkeypatch.setattr(mod, "_PLANS_BYTES", 4 << 20, raising=False)
+    bb.cache_clear()
+    for n in range(1000, 1010):
+        plan = mod._shared_plan(2048, n, 32, "greedy", "rbidiag", 0)
+        sizes = [3 * p.workspace()[1] for p in mod._plans.values()]
+        assert list(mod._plans.values())[-1] is plan
+        assert len(sizes) == 1 or sum(sizes) <= 4 << 20
+    bb.cache_clear()
