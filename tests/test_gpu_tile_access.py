@@ -92,3 +92,18 @@ def test_last_tiles_of_any_height_and_width(bb, nb, rest):
         Bo, _ = oracle.band_reduce(np.ascontiguousarray(At), nb)
         d = np.linalg.norm(oracle.sign_normalize(np.ascontiguousarray(Bt), nb) - oracle.sign_normalize(Bo, nb))
         assert d <= 50 * n * EPS * np.linalg.norm(A), d
+
+
+@pytest.mark.parametrize("nb", [32, 64, 128])
+def test_same_bits_on_both_sides_of_the_buffer_limit(bb, nb):
+    """Contiguous columns go through buffer accesses while lda nb < 2^27 and by
+    element beyond: one below, at and one above, whole and ragged tiles."""
+    m, n = 2 * nb + 3, nb + 5
+    A = workloads.gaussian(m, n, seed=nb + 1)
+    plan = bb.Plan(m, n, nb, "flatts", "bidiag")
+    B0, vt0 = reduce_at(bb, A, plan, m, 0)
+    limit = (1 << 27) // nb
+    for lda in (limit - 1, limit, limit + 1):
+        B, vt = reduce_at(bb, A, plan, lda, 0)
+        assert np.array_equal(B, B0), lda
+        assert torch.equal(vt, vt0), lda
