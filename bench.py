@@ -221,7 +221,7 @@ def chase_bytes(n, nb):
 
 
 def chase_traffic(n, nb):
-    """HBM bytes of one bulge chase (n, nb) from the committed PMC summary
+    """HBM bytes of one held bulge chase (n, nb) from the committed PMC summary
     (FETCH_SIZE + WRITE_SIZE, calibrated on a copy of known size), only while
     the chase's source is the one measured; else None."""
     summary = os.path.join(HERE, "profiles", "chase_kernel_traffic_square_%d.md" % n)
@@ -256,6 +256,7 @@ def ge2val_stage(bb, torch, np, S, m, n, nb, s_ref, e2bnd_ms):
     st = bb.poll_error(ws)
     if st != 0:
         raise RuntimeError("bulge chase error %d" % st)
+    held = int(ws[8:12].view(torch.int32)[0]) == 1        # the workspace's word for the way it ran
     chase_ms = ev[0].elapsed_time(ev[1])
     bd_ms = ev[1].elapsed_time(ev[2])
     err = None
@@ -268,10 +269,12 @@ def ge2val_stage(bb, torch, np, S, m, n, nb, s_ref, e2bnd_ms):
     return {"nb": nb, "ge2bnd_ms": round(e2bnd_ms, 3), "bnd2bd_ms": round(chase_ms, 3),
             "bd2val_ms": round(bd_ms, 3), "total_ms": round(e2bnd_ms + chase_ms + bd_ms, 3),
             "sigma_max_rel_err": err, "tol": 50 * n * np.finfo(np.float64).eps,
-            "bnd2bd_roofline": {"bound": "mfma", "achieved": round(tflops, 3), "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
-                                "frac": round(tflops / FP64_PEAK_TFLOPS, 5), "traffic": chase_traffic(n, nb),
-                                "kernel": "hold_kernel", "algorithmic_flops": flops,
-                                "algorithmic_bytes": nbytes}}
+            # a chain of 2 n dependent steps; priced against FP64 vector work, which a step consists of
+            "bnd2bd_roofline": {"bound": "latency", "achieved": round(tflops, 3), "peak": FP64_PEAK_TFLOPS,
+                                "unit": "TFLOP/s", "frac": round(tflops / FP64_PEAK_TFLOPS, 5),
+                                "traffic": chase_traffic(n, nb) if held else None,
+                                "kernel": "chase_kernel (%s)" % ("held" if held else "by sweeps"),
+                                "algorithmic_flops": flops, "algorithmic_bytes": nbytes}}
 
 
 def bench_square(args, bb, torch, np, workloads, nb=None, tree=None, prec=None, steps=None,

@@ -451,7 +451,11 @@ int bb_choose(int64_t m, int64_t n, int nb, const bb_opts* opts, int* tree, int*
  * member of its group, the groups' exchange areas and the held blocks'
  * messages), overwritten.  watchdog_s: seconds a sweep (or a
  * held block) may wait for the one before it (0 = 30); when it fires the launch stops and bb_poll_error(ws)
- * reports BB_ETIMEOUT.  Arguments: B (1), ldb >= max(1, n) (2), n >= 0 (3),
+ * reports BB_ETIMEOUT.  Word 2 of ws (int32) tells afterwards how the call ran:
+ * 1 held, 2 no room to hold it in time, 0 by sweeps without a try.
+ * A zero tail gives the identity reflector, so a band that is bidiagonal
+ * comes out as it is, infinities and NaN included; elsewhere they spread.
+ * Arguments: B (1), ldb >= max(1, n) (2), n >= 0 (3),
  * 1 <= nb <= 256 (4), d (5), e (6), ws (7), ws_bytes (8, BB_EWORKSPACE when
  * too small), watchdog_s (9), stream (10).  Asynchronous.
  */
@@ -472,7 +476,8 @@ int bb_bnd2bd_group(const double* B, int64_t ldb, int64_t n, int nb, double* d, 
  * order, into sigma[0..n-1] (device).  Bisection (multisection, 1 to 64
  * lanes per singular value) on the Sturm counts of B^T B - x^2 I, the pivot
  * pairs of the 2n x 2n Golub-Kahan tridiagonal, all values at once, to an absolute accuracy of a few
- * eps * ||B||.  Arguments: d (1), e (2), n >= 0
+ * eps * ||B||.  A NaN in d or e gives NaN for every value, an infinity (and no
+ * NaN) infinity, all zeros zero.  Arguments: d (1), e (2), n >= 0
  * (3), sigma (4), stream (5).  Asynchronous; no workspace.
  */
 int bb_bd2val(const double* d, const double* e, int64_t n, double* sigma, void* stream);

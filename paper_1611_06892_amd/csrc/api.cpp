@@ -161,10 +161,12 @@ const double kUnit[bb::NKINDS] = {4.0, 6.0, 2.0, 6.0, 12.0, 6.0, 6.0, 12.0, 6.0}
 //    UNMQR / TSMQR / TTMQR tile updates ~41 / 60 / 53 us;
 //  - nb = 256: panels ~397 / 506 / 353 us, updates (two 128-column halves
 //    side by side) ~104 / 176 / 116 us.
-// (Since then panels take ~74 / 80 / 70 and 360 / 450 / 334 us, updates ~38 /
-// 50 / 44 and 96 / 154 / 99 us.  Only ratios matter here, panels to updates
-// 1.6 to 2 and 3 to 3.7 now, and trees and variants are chosen by this model
-// too, so the table stays.)
+// (Since then panels take 73 / 76 / 68 and 351 / 448 / 329 us, updates 32 / 43 /
+// 34 and 95 / 153 / 97 us: panels cost 1.8 to 2.3 updates at nb = 128, 2.9 to 3.7
+// at nb = 256, where the table has 2.3 to 2.4 and 2.9 to 3.8.  bb_choose ranks
+// trees and variants by this model, and the signs of B follow the tree, so
+// other numbers here would change results.  Ordering units by a table of its own
+// would not; that has not been measured.)
 const double kGpuCost[bb::NKINDS] = {10.0, 13.5, 12.0, 4.1, 6.0, 5.3, 4.1, 6.0, 5.3};
 const double kGpuCost256[bb::NKINDS] = {39.7, 50.6, 35.3, 10.4, 17.6, 11.6, 10.4, 17.6, 11.6};
 

@@ -845,7 +845,7 @@ __device__ __forceinline__ int u_at(int row, int col) {
 // loaded run, before and after: nb = 32 TTQRT 17 -> 12 us, nb = 64 TSQRT
 // 39 -> 27 us, nb = 128 GEQRT 86 -> 74 and TTQRT 90 -> 65 us, nb = 256 (its
 // trailing tiles used to wait in scratch memory between blocks) GEQRT
-// 390 -> 330 us.
+// 390 -> 347 us.
 template <int NB, bool CO>
 __device__ __forceinline__ void panel(const KArgs& a, const DevTask& tk, double* lds, Prev& prev) {
     using S = Shape<NB>;
