@@ -1,8 +1,9 @@
 """GPU tests of the tile kernels' two ways to a tile in memory: 16-byte accesses
-for whole tiles with contiguous, 16-byte aligned columns, element accesses for
-everything else (odd leading dimension, base aligned to 8 bytes only, ragged
-tiles, LQ steps).  The arithmetic does not depend on the way, so a matrix
-reduced at any leading dimension and base gives the same bits, records
+through a buffer descriptor for contiguous columns (for nb <= 128 at any base and
+any leading dimension below the descriptor's limit, in updates of ragged tiles
+too; for nb = 256 whole, 16-byte aligned tiles), element accesses for everything
+else (LQ steps).  The arithmetic does not depend on the way, so a
+matrix reduced at any leading dimension and base gives the same bits, records
 included, and never touches the padding between columns."""
 import numpy as np
 import pytest
