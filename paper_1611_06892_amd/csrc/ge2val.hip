@@ -518,8 +518,8 @@ constexpr double MEET_SECONDS = 2e-3;
 
 struct HoldArgs {
     Waits wait;
-    const double* B;
-    int64_t rs, cs, n;
+    const double* W;      // the band array
+    int64_t n;
     int nb;
     int group;            // workgroups per block
     double* box;          // inboxes, per workgroup
@@ -569,6 +569,9 @@ __device__ __forceinline__ void hold_blocks(const HoldArgs& a, StepLds<CH>& lds)
     double* box_l = box + 2 * box_row(CH);
     const Group gr{G, m, box_l + 2 * box_last(CH), size};
     const int64_t K = a.n - 1 - (int64_t)b * nb, Kn = K - nb;   // sweeps of this block, of the next
+    // (from the band array, not from B: d and e, written from here on, may lie there)
+    const int64_t rowp = 3 * (int64_t)nb - 1;           // from entry (i, j) to (i + 1, j)
+    const double* w0 = a.W + nb - 1;                    // entry (0, 0)
     bool use[CH];
     double D[RW][CH], Q[RW][CH];
 #pragma unroll
@@ -579,11 +582,11 @@ __device__ __forceinline__ void hold_blocks(const HoldArgs& a, StepLds<CH>& lds)
             const int r = 8 * (RW * m + i) + w, q = lane + 64 * h;
             const int64_t row = 1 + (int64_t)b * nb + r, col = 1 + (int64_t)b * nb + q;
             const bool in = r < nb && use[h] && row < a.n;
-            D[i][h] = in && col >= row && col < a.n ? a.B[row * a.rs + col * a.cs] : 0.0;
-            Q[i][h] = in && col <= row && col + nb < a.n ? a.B[row * a.rs + (col + nb) * a.cs] : 0.0;
+            D[i][h] = in && col < a.n ? w0[row * rowp + col] : 0.0;
+            Q[i][h] = in && col + nb < a.n ? w0[row * rowp + col + nb] : 0.0;
         }
     }
-    if (blockIdx.x == 0 && tid == 0) a.d[0] = a.B[0];
+    if (blockIdx.x == 0 && tid == 0) a.d[0] = w0[0];
 
     int i0 = 0, ip = 0;                         // slots of the first row and column: of this sweep, of the last
     for (int64_t k = 0; k < K; ++k) {
@@ -616,7 +619,7 @@ __device__ __forceinline__ void hold_blocks(const HoldArgs& a, StepLds<CH>& lds)
 #pragma unroll
             for (int h = 0; h < CH; ++h) {
                 const int64_t col = 1 + lane + 64 * h;
-                v[h] = use[h] && col < a.n ? a.B[col * a.cs] : 0.0;
+                v[h] = use[h] && col < a.n ? w0[col] : 0.0;
             }
         }
         block_step<CH, RW>(
@@ -883,10 +886,8 @@ __global__ __launch_bounds__(NT) void chase_kernel(HoldArgs h, SweepArgs a, int 
 // inboxes marked, the upper band of B copied into W (zero elsewhere).  Entry
 // (i, j) of the band is B[i rs + j cs]: rs = 1, cs = ldb for an upper band stored
 // as is, rs = ldb, cs = 1 for the transpose of a lower band.
-// The band is copied before it is known whether it can be held, for one launch
-// less: beside work that fills the chip every launch waits for room of its own
-// (a matrix product's last workgroups, say), and the copy takes less than 1 % of a
-// chase.
+// One launch for both ways: beside work that fills the chip every launch waits
+// for room of its own (a matrix product's last workgroups, say).
 struct PrepareArgs {
     const double* B;
     int64_t rs, cs, n;
@@ -1201,11 +1202,12 @@ int bbg::bnd2bd_launch(const double* B, int64_t rs, int64_t cs, int64_t n, int n
     });
     const bool hold = !by_sweeps && wgs > 0 && wgs <= (int64_t)cus * room;
     double* box = (double*)((char*)ws + bbg::ws_hold_off(n, nb));
-    const bbg::HoldArgs h{wait, B, rs, cs, n, nb, group, box, d, e, (int64_t)(bbg::MEET_SECONDS * khz * 1000.0)};
-    const bbg::SweepArgs a{wait, (double*)((char*)ws + 256), n, nb, nsw, group,
+    double* W = (double*)((char*)ws + 256);
+    const bbg::HoldArgs h{wait, W, n, nb, group, box, d, e, (int64_t)(bbg::MEET_SECONDS * khz * 1000.0)};
+    const bbg::SweepArgs a{wait, W, n, nb, nsw, group,
                            (int32_t*)((char*)ws + bbg::ws_prog_off(n, nb)),
                            (double*)((char*)ws + bbg::ws_xch_off(n, nb)), std::max(1, bbg::nareas_of(n, nb)), d, e};
-    const bbg::PrepareArgs p{B, rs, cs, n, nb, ctrl, keep_error ? 1 : 0, a.W, a.prog, bbg::prog_words(n, nb),
+    const bbg::PrepareArgs p{B, rs, cs, n, nb, ctrl, keep_error ? 1 : 0, W, a.prog, bbg::prog_words(n, nb),
                              a.xch, box, bbg::xch_words(n, nb), hold ? bbg::hold_words(n, nb) : 0};
     const int64_t total = (int64_t)3 * nb * n;
     hipLaunchKernelGGL(bbg::prepare_kernel, dim3((unsigned)std::min<int64_t>((total + 255) / 256, 8 * (int64_t)cus)),

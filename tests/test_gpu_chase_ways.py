@@ -172,3 +172,21 @@ def test_a_call_takes_three_launches_at_most(bb, n, nb):
     count = ctypes.c_size_t()
     assert hip.hipGraphGetNodes(ctypes.c_void_p(g.raw_cuda_graph()), None, ctypes.byref(count)) == 0
     assert count.value <= 3
+
+
+@pytest.mark.parametrize("n,nb", [(1000, 64), (1000, 128), (900, 256)])
+@pytest.mark.parametrize("group", [0, 1])
+def test_outputs_may_lie_in_the_input(bb, n, nb, group):
+    """B is read before d and e are written, so they may take its place: d over
+    the band of two columns, e over that of the first ones."""
+    S = random_band(n, nb, 8700)
+    want = bb.bnd2bd(S, n, n, nb, watchdog_s=20.0, group=group)
+    ws = workspace(bb, n, nb)
+    base = S.data_ptr()
+    d, e = base + 8 * (n * (n // 2) + n // 2 - 20), base
+    rc = bb.lib().bb_bnd2bd_group(base, n, n, nb, d, e, ws.data_ptr(), ws.numel(), 20.0, group,
+                                  torch.cuda.current_stream().cuda_stream)
+    assert rc == 0 and bb.poll_error(ws) == 0
+    flat = S.view(-1)
+    at = n * (n // 2) + n // 2 - 20
+    assert torch.equal(flat[at:at + n], want[0]) and torch.equal(flat[:n - 1], want[1])
