@@ -917,13 +917,12 @@ __global__ void prepare_kernel(PrepareArgs a) {
     }
 }
 
-// A band that is bidiagonal as it is (nb = 1 or n <= 2).
-__global__ void diagonals_kernel(const double* B, int64_t rs, int64_t cs, int64_t n, double* d, double* e,
-                                 int32_t* ctrl, int keep_error) {
+// A band that is bidiagonal as it is (nb = 1 or n <= 2), from the band array.
+__global__ void diagonals_kernel(const double* W, int64_t n, int nb, double* d, double* e) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < G_WORDS && !(keep_error && i == G_ERROR)) ctrl[i] = 0;
-    if (i < n) d[i] = B[i * (rs + cs)];
-    if (i + 1 < n) e[i] = B[i * (rs + cs) + cs];
+    const double* w = W + nb - 1 + i * 3 * nb;
+    if (i < n) d[i] = w[0];
+    if (i + 1 < n) e[i] = w[1];
 }
 
 // Largest of v over the workgroup, in every thread; red holds a value a wave.
@@ -1171,22 +1170,17 @@ int bbg::bnd2bd_launch(const double* B, int64_t rs, int64_t cs, int64_t n, int n
     hipStream_t s = (hipStream_t)stream;
     int32_t* ctrl = (int32_t*)ws;
     const int nsw = bbg::nsweeps_of(n, nb);
-    if (nsw == 0) {
-        hipLaunchKernelGGL(bbg::diagonals_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, B, rs, cs, n, d,
-                           e, ctrl, keep_error ? 1 : 0);
-        return hipGetLastError() == hipSuccess ? BB_OK : BB_EHIP;
-    }
     const double khz = (double)bbg::device_attr(hipDeviceAttributeWallClockRate, 100000);
     const bbg::Waits wait{ctrl, (int64_t)((watchdog_s > 0 ? watchdog_s : 30.0) * khz * 1000.0)};
     const int cus = bbg::device_attr(hipDeviceAttributeMultiprocessorCount, 256);
     const int group = bbg::group_of(nb);
-    if (cus < group) return BB_ENOTSUP;
+    if (nsw > 0 && cus < group) return BB_ENOTSUP;
     // A chase's workgroups take their compute units' LDS, each an equal part of
     // it, so that no other kernel's that use LDS run there: a matrix product's waves
     // on the same SIMDs, whose FP64 pipe they share, make a step of 2 us take 45.
     // Beside FP64 products on another stream, with 11 KB a workgroup and so: 300 at
     // nb = 64 28 and 12 ms, 1000 at nb = 64 62 and 14 ms.  Alone it costs nothing.
-    const int64_t blocks = (n - 1 + nb - 1) / nb * group;
+    const int64_t blocks = std::max<int64_t>(1, (n - 1 + nb - 1) / nb) * group;
     const int per = (int)std::min<int64_t>(bbg::per_cu(nb), (blocks + cus - 1) / cus);
     const int64_t wgs = bbg::hold_workgroups(n, nb);
     int room = 0;                               // workgroups of this build a compute unit runs
@@ -1213,6 +1207,10 @@ int bbg::bnd2bd_launch(const double* B, int64_t rs, int64_t cs, int64_t n, int n
     hipLaunchKernelGGL(bbg::prepare_kernel, dim3((unsigned)std::min<int64_t>((total + 255) / 256, 8 * (int64_t)cus)),
                        dim3(256), 0, s, p);
     if (hipGetLastError() != hipSuccess) return BB_EHIP;
+    if (nsw == 0) {
+        hipLaunchKernelGGL(bbg::diagonals_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, W, n, nb, d, e);
+        return hipGetLastError() == hipSuccess ? BB_OK : BB_EHIP;
+    }
     // a workgroup a block to hold it (the sweeps, if they do not meet, make do
     // with those too); else whole groups, one workgroup a CU and MAX_WG at most
     // (the exchange areas are counted for that), without groups as many as run

@@ -174,7 +174,7 @@ def test_a_call_takes_three_launches_at_most(bb, n, nb):
     assert count.value <= 3
 
 
-@pytest.mark.parametrize("n,nb", [(1000, 64), (1000, 128), (900, 256)])
+@pytest.mark.parametrize("n,nb", [(1000, 1), (1000, 64), (1000, 128), (900, 256)])
 @pytest.mark.parametrize("group", [0, 1])
 def test_outputs_may_lie_in_the_input(bb, n, nb, group):
     """B is read before d and e are written, so they may take its place: d over
