@@ -768,11 +768,16 @@ __device__ __forceinline__ void run_sweeps(const SweepArgs& a, StepLds<CH>& lds,
         for (int t = 0; t < T; ++t) {
             const int64_t c = k + 1 + (int64_t)t * nb;
             double* w0 = a.W + c * rowp + c + nb - 1;       // entry (c, c)
-            // block t of the sweep ahead and the first row of its block t + 1
-            const bool waits = k > 0 && w == 0;
-            const int32_t* ahead = a.prog + (k - 1) * G + (lane == 1 && t == 0 ? ahead_holder : m);
-            if (waits) {
-                const bool ok = poll(a.wait, ahead, t + 1 < Tp ? t + 2 : Tp + 1);
+            // block t of the sweep ahead and the first row of its block t + 1;
+            // at the start also its row k and the area's last user
+            if (k > 0 && w == 0) {
+                const int32_t* ahead = a.prog + (k - 1) * G + (lane == 1 && t == 0 ? ahead_holder : m);
+                int target = t + 1 < Tp ? t + 2 : Tp + 1;
+                if (GROUPED && t == 0 && k >= a.nareas && lane >= 2 && lane < 2 + G) {
+                    ahead = a.prog + (k - a.nareas) * G + lane - 2;
+                    target = (int)nsteps(a.n, nb, k - a.nareas) + 1;
+                }
+                const bool ok = poll(a.wait, ahead, target);
                 if (lane == 0) flag = ok;
             }
             lds_barrier();
@@ -1078,11 +1083,9 @@ inline int64_t round256(int64_t b) { return (b + 255) / 256 * 256; }
 inline int nsweeps_of(int64_t n, int nb) { return nb <= 1 || n <= 2 ? 0 : (int)(n - 1); }
 
 // Exchange areas of the chase by sweeps (groups only): sweep k uses area k %
-// nareas.  While a member m of sweep k is unfinished, so is member m of every
-// later sweep (it waits for the one ahead), and with it, but for the sweep k
-// itself, the others of its group (the last exchange needs it); each holds a
-// workgroup, of MAX_WG at most, so when a ticket of sweep k + nareas is taken
-// sweep k has finished and its area is all MARK again.
+// nareas, once every member of the sweep that had it before has ended (and with
+// it set its words back).  So many that this is never waited for: no more than
+// MAX_WG / group + 1 sweeps have running workgroups.
 inline int nareas_of(int64_t n, int nb) {
     return group_of(nb) > 1 ? std::min(nsweeps_of(n, nb), MAX_WG / group_of(nb) + 2) : 0;
 }
@@ -1188,11 +1191,13 @@ int bbg::bnd2bd_launch(const double* B, int64_t rs, int64_t cs, int64_t n, int n
     bbg::with_instance(nb, [&](auto kernel) {
         const int all = bbg::device_attr(hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, 65536);
         hipFuncAttributes fa;
-        if (hipFuncGetAttributes(&fa, (const void*)kernel) != hipSuccess) return;
-        const int most = all - (int)fa.sharedSizeBytes;         // (the same for every call)
-        if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, most) == hipSuccess)
-            lds = (size_t)std::max(0, most - (all - all / per)) / 1280 * 1280;
+        if (hipFuncGetAttributes(&fa, (const void*)kernel) == hipSuccess) {
+            const int most = all - (int)fa.sharedSizeBytes;     // (the same for every call)
+            if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, most) == hipSuccess)
+                lds = (size_t)std::max(0, most - (all - all / per)) / 1280 * 1280;
+        }
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&room, kernel, bbg::NT, lds) != hipSuccess) room = 0;
+        (void)hipGetLastError();                // (without an answer the sweeps run, in the LDS they need)
     });
     const bool hold = !by_sweeps && wgs > 0 && wgs <= (int64_t)cus * room;
     double* box = (double*)((char*)ws + bbg::ws_hold_off(n, nb));
@@ -1211,12 +1216,13 @@ int bbg::bnd2bd_launch(const double* B, int64_t rs, int64_t cs, int64_t n, int n
         hipLaunchKernelGGL(bbg::diagonals_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, W, n, nb, d, e);
         return hipGetLastError() == hipSuccess ? BB_OK : BB_EHIP;
     }
-    // a workgroup a block to hold it (the sweeps, if they do not meet, make do
-    // with those too); else whole groups, one workgroup a CU and MAX_WG at most
-    // (the exchange areas are counted for that), without groups as many as run
+    // A workgroup (group) a block: to hold it, and for the sweeps, of which no
+    // more than blocks are in progress (two are never at one block).  Without
+    // room for all, whole groups, one workgroup a CU and MAX_WG at most (the
+    // exchange areas are counted for that), without groups as many as run.
     const int64_t grid = hold ? wgs
-                         : std::min<int64_t>((int64_t)nsw * group, group > 1 ? std::min(cus, bbg::MAX_WG) / group * group
-                                                                             : (int64_t)cus * per);
+                              : std::min<int64_t>(blocks, group > 1 ? std::min(cus, bbg::MAX_WG) / group * group
+                                                                    : (int64_t)cus * per);
     bbg::with_instance(nb, [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(bbg::NT), lds, s, h, a, hold ? 1 : 0);
     });
